@@ -188,7 +188,7 @@ bool force_generic()
 
 // Weight-gradient kernel family for a shape; the workspace query and the
 // call must agree, so both go through this choice.
-enum class WgradPath { Generic, Fused, Small, Bf16Mfma32, Bf16Mfma };
+enum class WgradPath { Generic, Fused, Small, Bf16Mfma32, Bf16Mfma, Any };
 
 WgradPath wgrad_path(const ConvShape &sh, Dtype d)
 {
@@ -201,8 +201,11 @@ WgradPath wgrad_path(const ConvShape &sh, Dtype d)
     if (hexk::smallc_bwd_fused_ok(sh, d))
         return WgradPath::Fused;
     const bool small = hexk::smallc_wgrad_ok(sh);
+    const WgradPath rest = small                        ? WgradPath::Small
+                           : hexk::wgrad_any_ok(sh, d) ? WgradPath::Any
+                                                        : WgradPath::Generic;
     if (d == hexk::F32)
-        return small ? WgradPath::Small : WgradPath::Generic;
+        return rest;
     // bf16 with few input channels: the small-channel kernel stages x once
     // per 16 output channels, so it wins only for one such block at k <= 2
     // (1 -> 16 channels, 40x40, N = 256: 27 -> 18 us at k = 1, 26 -> 23 us
@@ -216,7 +219,7 @@ WgradPath wgrad_path(const ConvShape &sh, Dtype d)
         return WgradPath::Bf16Mfma32;
     if (hexk::bf16_wgrad_ok(sh))
         return WgradPath::Bf16Mfma;
-    return small ? WgradPath::Small : WgradPath::Generic;
+    return rest;
 }
 
 // Fused data + weight gradient (hexconv_bwd) for this shape?
@@ -236,6 +239,8 @@ size_t wgrad_workspace(const ConvShape &sh, Dtype d)
         return hexk::bf16_wgrad32_workspace(sh);
     case WgradPath::Bf16Mfma:
         return hexk::bf16_wgrad_workspace(sh);
+    case WgradPath::Any:
+        return hexk::wgrad_any_workspace(sh, d);
     default:
         return hexk::wgrad_generic_workspace(sh);
     }
@@ -358,6 +363,8 @@ int hexconv_fwd(const void *x, const void *w, const void *bias, void *y, int N, 
             return launched(hexk::bf16_wide_conv(x, w, bias, y, sh, false, relu, st));
         if (d == hexk::BF16 && hexk::bf16_gen_fwd_ok(sh))
             return launched(hexk::bf16_gen_fwd(x, w, bias, y, sh, relu, st));
+        if (hexk::conv_any_ok(sh, d, false))
+            return launched(hexk::conv_any(x, w, bias, y, sh, d, false, relu, st));
     }
     if (!hexk::conv_fwd_generic_ok(sh))
         return HEX_ERR_UNSUPPORTED;
@@ -385,10 +392,17 @@ int hexconv_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in, i
         // 29 against 59 us)
         if (d == hexk::BF16 && hexk::bf16_wide_ok(sh, sh.Co, sh.Ci))
             return launched(hexk::bf16_wide_conv(dy, w, nullptr, dx, sh, true, false, st));
+        // at fewer output channels too the bf16 matrix cores win (64 images
+        // of 41 x 43, 4 -> 32 channels, k = 1: 52 -> 10 us; 1 -> 8: 9.2 -> 8.0;
+        // the small-channel kernel's arithmetic is fp32 on the vector units)
+        if (d == hexk::BF16 && hexk::smallc_bwd_data_ok(sh) && hexk::conv_any_ok(sh, d, true))
+            return launched(hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st));
         if (hexk::smallc_bwd_data_ok(sh))
             return launched(hexk::smallc_bwd_data(dy, w, dx, sh, d, st));
         if (d == hexk::BF16 && hexk::bf16_gen_dgrad_ok(sh))
             return launched(hexk::bf16_gen_dgrad(dy, w, dx, sh, st));
+        if (hexk::conv_any_ok(sh, d, true))
+            return launched(hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st));
     }
     if (!hexk::conv_bwd_data_generic_ok(sh))
         return HEX_ERR_UNSUPPORTED;
@@ -435,6 +449,8 @@ int hexconv_bwd_weight(const void *x, const void *dy, float *dw, float *db, void
         return launched(hexk::bf16_wgrad32(x, dy, dw, db, ws, sh, st));
     case WgradPath::Bf16Mfma:
         return launched(hexk::bf16_wgrad(x, dy, dw, db, ws, sh, st));
+    case WgradPath::Any:
+        return launched(hexk::wgrad_any(x, dy, dw, db, ws, sh, d, st));
     default:
         return launched(hexk::wgrad_generic(x, dy, dw, db, ws, sh, d, st));
     }
@@ -589,6 +605,10 @@ int hexconv3d_fwd(const void *x, const void *w, const void *bias, void *y, int N
         return launched(hexk::smallc_fwd(x, w, bias, y, sh, static_cast<Dtype>(dt),
                                          (flags & HEX_FLAG_RELU) != 0,
                                          static_cast<hipStream_t>(stream)));
+    if (!force_generic() && hexk::conv_any_ok(sh, static_cast<Dtype>(dt), false))
+        return launched(hexk::conv_any(x, w, bias, y, sh, static_cast<Dtype>(dt), false,
+                                       (flags & HEX_FLAG_RELU) != 0,
+                                       static_cast<hipStream_t>(stream)));
     if (!hexk::conv_fwd_generic_ok(sh))
         return HEX_ERR_UNSUPPORTED;
     return launched(hexk::conv_fwd_generic(x, w, bias, y, sh, static_cast<Dtype>(dt),
@@ -613,6 +633,9 @@ int hexconv3d_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in,
     if (!force_generic() && sh.Ho > 0 && hexk::smallc3d_bwd_data_ok(sh))
         return launched(hexk::smallc3d_bwd_data(dy, w, dx, sh, static_cast<Dtype>(dt),
                                                 static_cast<hipStream_t>(stream)));
+    if (!force_generic() && hexk::conv_any_ok(sh, static_cast<Dtype>(dt), true))
+        return launched(hexk::conv_any(dy, w, nullptr, dx, sh, static_cast<Dtype>(dt), true,
+                                       false, static_cast<hipStream_t>(stream)));
     if (!hexk::conv_bwd_data_generic_ok(sh))
         return HEX_ERR_UNSUPPORTED;
     return launched(hexk::conv_bwd_data_generic(dy, w, dx, sh, static_cast<Dtype>(dt),
@@ -621,16 +644,27 @@ int hexconv3d_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in,
 
 namespace {
 // 3-D weight gradient: the small-channel kernel with the planes around each
-// output plane staged as channels where it applies, else the generic one
-bool wgrad3d_smallc(const ConvShape &sh)
+// output plane staged as channels where it applies, then the matrix-core
+// kernel for any size, else the generic one
+WgradPath wgrad3d_path(const ConvShape &sh, Dtype d)
 {
-    return !force_generic() && hexk::smallc_wgrad_ok(sh);
+    if (force_generic())
+        return WgradPath::Generic;
+    if (hexk::smallc_wgrad_ok(sh))
+        return WgradPath::Small;
+    return hexk::wgrad_any_ok(sh, d) ? WgradPath::Any : WgradPath::Generic;
 }
 
-size_t wgrad3d_workspace(const ConvShape &sh)
+size_t wgrad3d_workspace(const ConvShape &sh, Dtype d)
 {
-    return wgrad3d_smallc(sh) ? hexk::smallc_wgrad_workspace(sh)
-                              : hexk::wgrad_generic_workspace(sh);
+    switch (wgrad3d_path(sh, d)) {
+    case WgradPath::Small:
+        return hexk::smallc_wgrad_workspace(sh);
+    case WgradPath::Any:
+        return hexk::wgrad_any_workspace(sh, d);
+    default:
+        return hexk::wgrad_generic_workspace(sh);
+    }
 }
 } // namespace
 
@@ -642,7 +676,7 @@ size_t hexconv3d_bwd_weight_workspace(int N, int C_in, int C_out, int D, int H, 
         return 0;
     if (N == 0 || sh.Ho == 0)
         return 0;
-    return wgrad3d_workspace(sh);
+    return wgrad3d_workspace(sh, static_cast<Dtype>(dt));
 }
 
 int hexconv3d_bwd_weight(const void *x, const void *dy, float *dw, float *db, void *ws,
@@ -658,16 +692,21 @@ int hexconv3d_bwd_weight(const void *x, const void *dy, float *dw, float *db, vo
     const bool empty = (N == 0 || sh.Ho == 0);
     if (!empty && (x == nullptr || dy == nullptr))
         return HEX_ERR_INVALID_ARG;
-    const size_t need = empty ? 0 : wgrad3d_workspace(sh);
+    const size_t need = empty ? 0 : wgrad3d_workspace(sh, static_cast<Dtype>(dt));
     if (need > 0 && (ws == nullptr || ws_bytes < need))
         return HEX_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (empty)
         return launched(hexk::fill_zero_f32(dw, db, sh, st));
-    if (wgrad3d_smallc(sh))
-        return launched(
-            hexk::smallc_wgrad(x, dy, dw, db, ws, sh, static_cast<Dtype>(dt), st));
-    return launched(hexk::wgrad_generic(x, dy, dw, db, ws, sh, static_cast<Dtype>(dt), st));
+    const Dtype d = static_cast<Dtype>(dt);
+    switch (wgrad3d_path(sh, d)) {
+    case WgradPath::Small:
+        return launched(hexk::smallc_wgrad(x, dy, dw, db, ws, sh, d, st));
+    case WgradPath::Any:
+        return launched(hexk::wgrad_any(x, dy, dw, db, ws, sh, d, st));
+    default:
+        return launched(hexk::wgrad_generic(x, dy, dw, db, ws, sh, d, st));
+    }
 }
 
 int hexpool3d_fwd(const void *x, void *y, uint16_t *argmax, int N, int C, int D, int H, int W,

@@ -1,0 +1,619 @@
+// k_wgrad_any.hip -- weight and bias gradient on the matrix cores for planes
+// of any size, any channel count and any stride, in bfloat16 and float32,
+// two- and three-dimensional; takes what the tuned bfloat16 kernels
+// (k_wgrad32.hip, k_wgrad_bf16.hip: whole 16-byte rows) and the small-channel
+// kernels do not.
+//
+//   D_t[co][ci] = sum over output pixels p of dy[co][p] x[ci][p + tap t]
+//
+// one 32x32 product per tap with the pixels as the contraction.  A block (8
+// waves) holds up to 64 output channels, up to 64 input channels and one
+// window plane dz, and walks tiles of whole output rows: dy as a list of
+// pixels and x as a window, both channel-last in LDS (chanlast.h).  Any
+// pixel-to-slot map then serves as the contraction's index: a table in LDS
+// gives each output pixel's centre slot, a tap adds a fixed offset (one row
+// more for odd tap columns at odd centre columns), so odd row lengths,
+// strides and parities cost nothing.
+//  - bfloat16: an operand holds 8 pixels of one channel; the transposing LDS
+//    read (ds_read_b64_tr_b16: 16 lanes read four slots of 16 channels, lane
+//    i receives channel i of the four) gathers it from channel-last slots.
+//    32x32x16 products.
+//  - float32: an operand is one 4-byte read, lanes 0-31 the channels of one
+//    pixel and lanes 32-63 of the next. 32x32x2 products.
+// The bias gradient is one more "tap" whose x operand is all ones.
+//
+// Wave roles: G groups of TPW taps (T + 1 of them with the bias), A blocks of
+// 32 input channels, and the rest splits the pixels (KS); each wave holds
+// TPW x NCO accumulators, so a dy operand serves TPW products and an x
+// operand NCO.  The pixel splits are added through LDS at the end, the
+// block's sums go to a slot of the workspace and reduce_any_k adds the slots
+// in order (deterministic).
+//
+// Pixels past a tile's end: both operands are zeroed (by masks), so that no
+// product of a stray infinity reaches a sum.
+#include <algorithm>
+#include <type_traits>
+
+#include "chanlast.h"
+#include "kernels.h"
+
+namespace hexk {
+namespace {
+
+using namespace hexgeom;
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+
+constexpr int kWThreads = 512;
+
+struct WAnyArgs {
+    int N, Ci, Co, D, H, W, Do, Ho, Wo;
+    int s, sz, kz, Z;
+    int TR, tiles, ntot;  // output rows per tile, tiles per plane, tiles of the batch
+    int rows, RP, WCs;    // window
+    int nci, nco;         // channel blocks
+    int nslots;           // blocks per (dz, ci, co) type
+    int x_off, tab_off;   // LDS: dy at 0, x window, pixel table
+    int npix;             // table entries (multiple of 16)
+    int toff[37];         // byte offset of each tap
+};
+
+// Taps per wave and tap groups: T + 1 columns (the taps and the bias)
+template <int K> struct WRole;
+template <> struct WRole<1> {
+    static constexpr int TPW = 4, G = 2;
+};
+template <> struct WRole<2> {
+    static constexpr int TPW = 5, G = 4;
+};
+template <> struct WRole<3> {
+    static constexpr int TPW = 5, G = 8;
+};
+
+// Four pixels of a channel from a0 and four from a1, transposed (see above)
+__device__ __forceinline__ bf16x8 tr_read(unsigned char *a0, unsigned char *a1)
+{
+    using lp = __attribute__((address_space(3))) shortx4 *;
+    const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)a0);
+    const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)a1);
+    typedef short shortx8 __attribute__((ext_vector_type(8)));
+    const shortx8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+// NCO: 32-channel tiles of output channels (1 or 2); A: of input channels
+// U: items of x and of dy per thread.  PF: the next tile's items are loaded
+// during the products (where the registers hold them beside the sums).
+template <typename E, int K, int NCO, int A, int U, bool PF>
+__global__ __launch_bounds__(kWThreads) void wgrad_any_k(const E *x, const E *dy,
+                                                         float *__restrict__ part, WAnyArgs a)
+{
+    constexpr bool F32 = sizeof(E) == 4;
+    constexpr int PX = AnyE<E>::PX;
+    constexpr int T = num_taps(K);
+    constexpr TapTable<K> tab{};
+    constexpr int TPW = WRole<K>::TPW, G = WRole<K>::G;
+    constexpr int KS = 8 / (G * A);
+    constexpr int CB = 32 * sizeof(E);      // bytes of 32 channels
+    constexpr int XB = A * CB, DB = NCO * CB; // bytes per slot
+    constexpr int XG = XB / 16, DG = DB / 16; // 16-byte vectors per slot
+    extern __shared__ __align__(16) unsigned char smem[];
+    unsigned char *dyl = smem, *win = smem + a.x_off;
+    int *ptab = reinterpret_cast<int *>(smem + a.tab_off);
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = wave % G, ai = (wave / G) % A, ks = wave / (G * A);
+    const int types = a.Z * a.nci * a.nco;
+    const int type = blockIdx.x % types, slot = blockIdx.x / types;
+    const int cob = type % a.nco, cib = (type / a.nco) % a.nci, dz = type / (a.nco * a.nci);
+    const int co0 = cob * 32 * NCO, ci0 = cib * 32 * A;
+    const size_t HWx = static_cast<size_t>(a.H) * a.W, HWy = static_cast<size_t>(a.Ho) * a.Wo;
+    const size_t csx = HWx * a.D, csy = HWy * a.Do;
+    const WinGeom wg{a.rows, a.RP, a.WCs, a.s, K, a.W};
+
+    // byte address of every tile pixel's centre slot; bit 0: odd centre column
+    for (int p = threadIdx.x; p < a.npix; p += kWThreads) {
+        const int q = min(p, a.TR * a.Wo - 1);
+        const int i = q / a.Wo, j = q - i * a.Wo;
+        ptab[p] = ((a.s * i + (j & 1) * (a.s >> 1) + K) * a.RP + j) * XB | ((a.s * j) & 1);
+    }
+
+    struct Pos {
+        int tb, n, l, i0, zs;
+    };
+    // first tile from tb on (steps of nslots) whose source plane exists
+    auto settle = [&](Pos &p) {
+        const int per = a.Do * a.tiles;
+        for (; p.tb < a.ntot; p.tb += a.nslots) {
+            p.n = p.tb / per;
+            const int r = p.tb - p.n * per;
+            p.l = r / a.tiles;
+            p.i0 = (r - p.l * a.tiles) * a.TR;
+            p.zs = a.sz * p.l + dz - a.kz;
+            if (p.zs >= 0 && p.zs < a.D)
+                return true;
+        }
+        return false;
+    };
+    auto span = [&](const Pos &p, int &lo, int &run) {
+        const int r_lo = a.s * p.i0 - K;
+        lo = max(0, -r_lo);
+        const int hi = min(a.rows, a.H - r_lo);
+        run = (hi - lo) * a.W;
+        return hi;
+    };
+    AnyItem<E> ix[U], id[U];
+    auto load_x = [&](const Pos &p) {
+        int lo, run;
+        span(p, lo, run);
+        const E *xs = x + (static_cast<size_t>(p.n) * a.Ci + ci0) * csx +
+                      static_cast<size_t>(p.zs) * HWx +
+                      static_cast<size_t>(a.s * p.i0 - K + lo) * a.W;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = threadIdx.x + u * kWThreads;
+            ix[u].load(xs, csx, (i % XG) * PX, a.Ci - ci0, min((i / XG) * PX, run - PX));
+        }
+    };
+    auto load_dy = [&](const Pos &p) {
+        const E *ds = dy + (static_cast<size_t>(p.n) * a.Co + co0) * csy +
+                      static_cast<size_t>(p.l) * HWy + static_cast<size_t>(p.i0) * a.Wo;
+        const int M = min(a.TR, a.Ho - p.i0) * a.Wo;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = threadIdx.x + u * kWThreads;
+            id[u].load(ds, csy, (i % DG) * PX, a.Co - co0, min((i / DG) * PX, M - PX));
+        }
+    };
+    auto commit_x = [&](const Pos &p) {
+        int lo, run;
+        const int hi = span(p, lo, run);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = threadIdx.x + u * kWThreads;
+            if ((i / XG) * PX < run)
+                ix[u].template commit<XB>(win, wg, lo, min((i / XG) * PX, run - PX), i % XG);
+        }
+        zero_border<XB, XG, kWThreads>(win, wg, lo, hi);
+    };
+    auto commit_dy = [&](const Pos &p) {
+        const int M = min(a.TR, a.Ho - p.i0) * a.Wo;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = threadIdx.x + u * kWThreads;
+            if ((i / DG) * PX < M)
+                id[u].template commit_flat<DB>(dyl, min((i / DG) * PX, M - PX), i % DG);
+        }
+        // the slots past the last pixel, up to a whole step
+        const int Mp = (M + 15) & ~15;
+        for (int i = threadIdx.x; i < (Mp - M) * DG; i += kWThreads)
+            *reinterpret_cast<uint4 *>(dyl + (M + i / DG) * DB + 16 * (i % DG)) =
+                make_uint4(0, 0, 0, 0);
+    };
+
+    floatx16 acc[NCO][TPW];
+#pragma unroll
+    for (int c = 0; c < NCO; ++c)
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+            acc[c][t] = floatx16{};
+
+    unsigned char *xb = win + ai * CB;
+    const int prow = a.RP * XB;
+
+    // this wave's taps: offsets (wave-uniform), parity of their columns.  The
+    // bias is tap T; the taps past it compute sums that are not read.
+    int toff[TPW];
+    bool todd[TPW];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+        toff[t] = 0;
+        todd[t] = false;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            if (g * TPW + t < T && grp == g) {
+                toff[t] = a.toff[g * TPW + t];
+                todd[t] = (tab.dq[g * TPW + t] & 1) != 0;
+            }
+    }
+    const bool has_bias = grp == T / TPW;
+
+    // one step: 16 pixels of the tile from p0 on; TAIL: only `left` of them exist
+    auto step = [&](auto tail, int p0, int left) {
+        constexpr bool TAIL = decltype(tail)::value;
+        if constexpr (F32) {
+#pragma unroll
+            for (int h = 0; h < 8; ++h) {
+                const int p = p0 + 2 * h + (lane >> 5);
+                const int e = ptab[p];
+                const unsigned char *b0 = xb + (e & ~1) + 4 * (lane & 31);
+                const unsigned char *b1 = b0 + ((e & 1) ? prow : 0);
+                const bool live = 2 * h + (lane >> 5) < left;
+                float av[NCO];
+#pragma unroll
+                for (int c = 0; c < NCO; ++c)
+                    av[c] = *reinterpret_cast<const float *>(dyl + p * DB + c * CB +
+                                                             4 * (lane & 31));
+#pragma unroll
+                for (int t = 0; t < TPW; ++t) {
+                    float bv = *reinterpret_cast<const float *>((todd[t] ? b1 : b0) + toff[t]);
+                    if (t == T % TPW && has_bias)
+                        bv = 1.f;
+                    if (TAIL)
+                        bv = live ? bv : 0.f;
+#pragma unroll
+                    for (int c = 0; c < NCO; ++c)
+                        acc[c][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[c], bv, acc[c][t], 0,
+                                                                         0, 0);
+                }
+            }
+        } else {
+            // pixels 8 (lane / 32) + (lane % 16) / 4 and 4 further on;
+            // channels 16 ((lane / 16) % 2) + 4 (lane % 4) ..
+            const int pl = 8 * (lane >> 5) + ((lane & 15) >> 2);
+            const int cl = 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+            const int e0 = ptab[p0 + pl], e1 = ptab[p0 + pl + 4];
+            unsigned char *x00 = xb + (e0 & ~1) + cl, *x10 = xb + (e1 & ~1) + cl;
+            unsigned char *x01 = x00 + ((e0 & 1) ? prow : 0);
+            unsigned char *x11 = x10 + ((e1 & 1) ? prow : 0);
+            bf16x8 av[NCO];
+#pragma unroll
+            for (int c = 0; c < NCO; ++c) {
+                unsigned char *d = dyl + (p0 + pl) * DB + c * CB + cl;
+                av[c] = tr_read(d, d + 4 * DB);
+            }
+            // halves of the operand's dwords that lie past the tile's end
+            const int lv = left - 8 * (lane >> 5);
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) {
+                uint4 u = __builtin_bit_cast(uint4, tr_read((todd[t] ? x01 : x00) + toff[t],
+                                                            (todd[t] ? x11 : x10) + toff[t]));
+                if (t == T % TPW && has_bias)
+                    u = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+                if (TAIL) {
+                    u.x &= lv >= 2 ? 0xffffffffu : lv == 1 ? 0xffffu : 0u;
+                    u.y &= lv >= 4 ? 0xffffffffu : lv == 3 ? 0xffffu : 0u;
+                    u.z &= lv >= 6 ? 0xffffffffu : lv == 5 ? 0xffffu : 0u;
+                    u.w &= lv >= 8 ? 0xffffffffu : lv == 7 ? 0xffffu : 0u;
+                }
+                const bf16x8 bv = __builtin_bit_cast(bf16x8, u);
+#pragma unroll
+                for (int c = 0; c < NCO; ++c)
+                    acc[c][t] =
+                        __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[c], bv, acc[c][t], 0, 0, 0);
+            }
+        }
+    };
+
+    Pos cur{slot, 0, 0, 0, 0};
+    bool more = settle(cur);
+    if (PF && more) {
+        load_x(cur);
+        load_dy(cur);
+    }
+    while (more) {
+        Pos nxt = cur;
+        nxt.tb += a.nslots;
+        more = settle(nxt);
+        if (!PF)
+            load_x(cur);
+        __syncthreads(); // the previous tile's readers are done (and the table is written)
+        commit_x(cur);
+        if (!PF)
+            load_dy(cur);
+        commit_dy(cur);
+        __syncthreads();
+        if (PF && more) {
+            load_x(nxt);
+            load_dy(nxt);
+        }
+        const int M = min(a.TR, a.Ho - cur.i0) * a.Wo;
+        const int nst = M >> 4;
+        for (int q = ks; q < nst; q += KS)
+            step(std::false_type{}, q * 16, 16);
+        if ((M & 15) != 0 && nst % KS == ks)
+            step(std::true_type{}, nst * 16, M & 15);
+        cur = nxt;
+    }
+
+    // add the pixel splits, then one slot of partial sums:
+    // part[type][slot][wave role][tap][co tile][r][lane]
+    constexpr int WE = NCO * TPW * 16 * 64; // floats per wave
+    float *red = reinterpret_cast<float *>(smem);
+    const int role = wave % (G * A);
+#pragma unroll
+    for (int k = 1; k < KS; ++k) {
+        __syncthreads();
+        if (ks == k) {
+#pragma unroll
+            for (int c = 0; c < NCO; ++c)
+#pragma unroll
+                for (int t = 0; t < TPW; ++t)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        red[role * WE + ((t * NCO + c) * 16 + r) * 64 + lane] = acc[c][t][r];
+        }
+        __syncthreads();
+        if (ks == 0) {
+#pragma unroll
+            for (int c = 0; c < NCO; ++c)
+#pragma unroll
+                for (int t = 0; t < TPW; ++t)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        acc[c][t][r] += red[role * WE + ((t * NCO + c) * 16 + r) * 64 + lane];
+        }
+    }
+    if (ks == 0) {
+        float *o = part + ((static_cast<size_t>(type) * a.nslots + slot) * (G * A) + role) * WE;
+#pragma unroll
+        for (int c = 0; c < NCO; ++c)
+#pragma unroll
+            for (int t = 0; t < TPW; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    o[((t * NCO + c) * 16 + r) * 64 + lane] = acc[c][t][r];
+    }
+}
+
+// dw and db from the slots, in a fixed order: a block owns 64 consecutive
+// partial elements (one wave's width) and its waves every kRedWaves-th slot,
+// eight loads in flight each; the waves' sums are added through LDS.  One
+// thread per element over all slots was bound by its chain of loads (256
+// slots of 64 KB: 18.7 us).
+struct RedArgs {
+    int Ci, Co, Z, T, nci, nco, nslots, NCO, A, TPW, G, kz;
+    int per; // floats per slot
+};
+constexpr int kRedWaves = 8;
+
+__global__ __launch_bounds__(64 * kRedWaves) void reduce_any_k(const float *__restrict__ part,
+                                                               float *__restrict__ dw,
+                                                               float *__restrict__ db, RedArgs a)
+{
+    __shared__ float sums[kRedWaves][64];
+    const int type = blockIdx.y;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // what this block's elements are: [wave role][tap][co tile][r][lane]
+    const int r = blockIdx.x & 15;
+    int q = blockIdx.x >> 4;
+    const int c = q % a.NCO;
+    q /= a.NCO;
+    const int t = q % a.TPW;
+    q /= a.TPW;
+    const int tap = (q % a.G) * a.TPW + t, ai = q / a.G;
+    const int cob = type % a.nco, cib = (type / a.nco) % a.nci, dz = type / (a.nco * a.nci);
+    const bool bias = tap == a.T;
+    const int co0 = (cob * a.NCO + c) * 32 + 8 * (r >> 2) + (r & 3);
+    const int ci0 = (cib * a.A + ai) * 32;
+    if (tap > a.T || co0 >= a.Co || ci0 >= a.Ci ||
+        (bias && (db == nullptr || ci0 != 0 || dz != a.kz)))
+        return; // the same for the whole block
+    const float *p = part + static_cast<size_t>(type) * a.nslots * a.per + blockIdx.x * 64 + lane;
+    float s[8] = {};
+    int i = wave;
+    for (; i + 7 * kRedWaves < a.nslots; i += 8 * kRedWaves)
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            s[u] += p[static_cast<size_t>(i + u * kRedWaves) * a.per];
+    for (; i < a.nslots; i += kRedWaves)
+        s[0] += p[static_cast<size_t>(i) * a.per];
+    sums[wave][lane] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+    __syncthreads();
+    if (wave != 0)
+        return;
+    float v = 0.f;
+#pragma unroll
+    for (int k = 0; k < kRedWaves; ++k)
+        v += sums[k][lane];
+    const int co = co0 + 4 * (lane >> 5), ci = ci0 + (lane & 31);
+    if (co >= a.Co || ci >= a.Ci || (bias && ci != 0))
+        return;
+    if (bias)
+        db[co] = v;
+    else
+        dw[(static_cast<size_t>(co) * a.Ci + ci) * a.Z * a.T + dz * a.T + tap] = v;
+}
+
+// ------------------------------------------------------------------- host
+
+constexpr size_t kAnyLds = 160 * 1024;
+
+struct WAnyPlan {
+    WAnyArgs a;
+    int NCO, A, U, G, TPW;
+    size_t lds, ws;
+    int types;
+};
+
+// The largest tile for A input-channel tiles and U items per thread.
+bool plan_tile(const ConvShape &sh, Dtype d, int A, int U, WAnyPlan &pl)
+{
+    const int es = d == F32 ? 4 : 2, PX = 16 / es;
+    const int K = sh.k;
+    WAnyArgs &a = pl.a;
+    a = WAnyArgs{};
+    a.N = sh.N;
+    a.Ci = sh.Ci;
+    a.Co = sh.Co;
+    a.D = sh.D;
+    a.H = sh.H;
+    a.W = sh.W;
+    a.Do = sh.Do;
+    a.Ho = sh.Ho;
+    a.Wo = sh.Wo;
+    a.s = sh.s;
+    a.sz = sh.sz;
+    a.kz = sh.kz;
+    a.Z = sh.Z;
+    pl.TPW = K == 1 ? 4 : 5;
+    pl.G = K == 1 ? 2 : K == 2 ? 4 : 8;
+    pl.NCO = sh.Co > 32 ? 2 : 1;
+    pl.A = A;
+    pl.U = U;
+    a.nco = (sh.Co + 32 * pl.NCO - 1) / (32 * pl.NCO);
+    a.nci = (sh.Ci + 32 * A - 1) / (32 * A);
+    const int XB = A * 32 * es, DB = pl.NCO * 32 * es;
+    if (static_cast<long>(sh.D) * sh.H * sh.W * XB >= kAnyMaxSpan ||
+        static_cast<long>(sh.Do) * sh.Ho * sh.Wo * DB >= kAnyMaxSpan)
+        return false;
+    const int cols = sh.W + 2 * K;
+    a.WCs = (cols + a.s - 1) / a.s;
+    // slots of 64 bytes: rows of a multiple of 4 keep the 256-byte phase of
+    // consecutive columns when odd columns read one row further down
+    a.WCs = (a.WCs + 3) & ~3;
+    a.RP = a.s * a.WCs;
+    bool ok = false;
+    for (int TR = std::min(sh.Ho, std::max(1, 512 / sh.Wo)); TR >= 1 && !ok; --TR) {
+        const int tiles = (sh.Ho + TR - 1) / TR;
+        a.TR = (sh.Ho + tiles - 1) / tiles;
+        a.tiles = tiles;
+        a.rows = a.s * (a.TR - 1) + (sh.Wo > 1 ? a.s / 2 : 0) + 2 * K + 1;
+        const int M = a.TR * sh.Wo;
+        a.npix = (M + 15) & ~15;
+        const int ix = (XB / 16) * ((std::min(a.rows, sh.H) * sh.W + PX - 1) / PX);
+        const int id = (DB / 16) * ((M + PX - 1) / PX);
+        const size_t dyb = static_cast<size_t>(a.npix) * DB;
+        const size_t xb = static_cast<size_t>(a.rows) * a.RP * XB;
+        pl.lds = dyb + xb + static_cast<size_t>(a.npix) * 4;
+        if (pl.lds > kAnyLds || ix > U * kWThreads || id > U * kWThreads)
+            continue;
+        a.x_off = static_cast<int>(dyb);
+        a.tab_off = static_cast<int>(dyb + xb);
+        ok = true;
+    }
+    if (!ok)
+        return false;
+    int t = 0;
+    for (int dq = -K; dq <= K; ++dq)
+        for (int i = 0; i < col_len(K, dq); ++i, ++t) {
+            const int c = K + dq;
+            a.toff[t] = ((col_ds_lo(K, dq) + i + floor_half(dq)) * a.RP + (c % a.s) * a.WCs +
+                         c / a.s) * XB;
+        }
+    return true;
+}
+
+bool plan_wgrad(const ConvShape &sh, Dtype d, WAnyPlan &pl)
+{
+    if (sh.k < 1 || sh.k > 3 || sh.W < 8 || sh.Wo < 8 || sh.Ho < 1)
+        return false;
+    // two input-channel tiles share the dy tile (at k = 3 the taps take
+    // every wave); bfloat16 with one item per thread where that holds a tile
+    const int A = (sh.Ci > 32 && sh.k < 3) ? 2 : 1;
+    bool ok = false;
+    for (int aa = A; aa >= 1 && !ok; --aa)
+        for (int u = d == F32 ? 2 : 1; u <= 2 && !ok; ++u)
+            ok = plan_tile(sh, d, aa, u, pl);
+    if (!ok)
+        return false;
+    WAnyArgs &a = pl.a;
+    const int KS = 8 / (pl.G * pl.A);
+    const int we = pl.NCO * pl.TPW * 16 * 64;
+    if (KS > 1)
+        pl.lds = std::max(pl.lds, static_cast<size_t>(pl.G) * pl.A * we * 4);
+    const long ntot = static_cast<long>(sh.N) * sh.Do * a.tiles;
+    if (ntot > (1L << 30))
+        return false;
+    a.ntot = static_cast<int>(ntot);
+    pl.types = a.Z * a.nci * a.nco;
+    // one block per compute unit in all; every slot costs a write and a read
+    // of its partial sums
+    a.nslots = std::max(1, std::min(a.ntot, device_cus() / pl.types));
+    pl.ws = static_cast<size_t>(pl.types) * a.nslots * pl.G * pl.A * we * 4;
+    return true;
+}
+
+template <typename E, int K, int NCO, int A>
+hipError_t launch_u(const WAnyPlan &pl, const void *x, const void *dy, float *part, hipStream_t st)
+{
+    const dim3 grid(pl.types * pl.a.nslots), block(kWThreads);
+    const E *xe = static_cast<const E *>(x), *de = static_cast<const E *>(dy);
+    // the next tile's items fit beside the sums except at 160 sums per lane
+    // (k > 1, two tiles of output channels) and at 128 registers of items
+    constexpr bool sums = K == 1 || NCO == 1;
+    if constexpr (sizeof(E) == 4) {
+        HEX_LAUNCH((wgrad_any_k<E, K, NCO, A, 2, sums>), grid, block, pl.lds, st, xe, de, part,
+                   pl.a);
+    } else {
+        if (pl.U == 1)
+            HEX_LAUNCH((wgrad_any_k<E, K, NCO, A, 1, sums>), grid, block, pl.lds, st, xe, de,
+                       part, pl.a);
+        else
+            HEX_LAUNCH((wgrad_any_k<E, K, NCO, A, 2, false>), grid, block, pl.lds, st, xe, de,
+                       part, pl.a);
+    }
+    return hipGetLastError();
+}
+
+template <typename E, int K>
+hipError_t launch_k(const WAnyPlan &pl, const void *x, const void *dy, float *part, hipStream_t st)
+{
+    if constexpr (K < 3)
+        if (pl.A == 2)
+            return pl.NCO == 2 ? launch_u<E, K, 2, 2>(pl, x, dy, part, st)
+                               : launch_u<E, K, 1, 2>(pl, x, dy, part, st);
+    return pl.NCO == 2 ? launch_u<E, K, 2, 1>(pl, x, dy, part, st)
+                       : launch_u<E, K, 1, 1>(pl, x, dy, part, st);
+}
+
+template <typename E>
+hipError_t launch_e(const WAnyPlan &pl, int k, const void *x, const void *dy, float *part,
+                    hipStream_t st)
+{
+    switch (k) {
+    case 1:
+        return launch_k<E, 1>(pl, x, dy, part, st);
+    case 2:
+        return launch_k<E, 2>(pl, x, dy, part, st);
+    default:
+        return launch_k<E, 3>(pl, x, dy, part, st);
+    }
+}
+
+} // namespace
+
+bool wgrad_any_ok(const ConvShape &sh, Dtype d)
+{
+    // Few input channels leave most of a 32-channel tile empty; then the
+    // generic kernel is the faster one in fp32, whose products take 16 times
+    // as long (64 images of 41 x 43, us here against generic: fp32 k = 1
+    // 4 -> 16 channels 47 / 65, 3 -> 16 46 / 58, 2 -> 16 45 / 38; bf16 k = 1
+    // 1 -> 8 channels 15 / 21; 8 volumes of 12 planes, fp32 3 -> 16 channels
+    // 104 / 189, 2 -> 8 slower).
+    if (d == F32 && (sh.Ci * sh.T < 20 || (sh.Z > 1 && sh.Ci < 3)))
+        return false;
+    WAnyPlan pl;
+    return plan_wgrad(sh, d, pl);
+}
+
+size_t wgrad_any_workspace(const ConvShape &sh, Dtype d)
+{
+    WAnyPlan pl;
+    return plan_wgrad(sh, d, pl) ? pl.ws : 0;
+}
+
+hipError_t wgrad_any(const void *x, const void *dy, float *dw, float *db, void *ws,
+                     const ConvShape &sh, Dtype d, hipStream_t st)
+{
+    WAnyPlan pl;
+    if (!plan_wgrad(sh, d, pl))
+        return hipErrorInvalidValue;
+    float *part = static_cast<float *>(ws);
+    hipError_t e = d == F32 ? launch_e<float>(pl, sh.k, x, dy, part, st)
+                            : launch_e<bf16raw>(pl, sh.k, x, dy, part, st);
+    if (e != hipSuccess)
+        return e;
+    const WAnyArgs &a = pl.a;
+    const int per = pl.G * pl.A * pl.NCO * pl.TPW * 16 * 64;
+    const RedArgs r{a.Ci, a.Co, a.Z, sh.T, a.nci, a.nco, a.nslots, pl.NCO, pl.A,
+                    pl.TPW, pl.G, a.kz, per};
+    HEX_LAUNCH(reduce_any_k, dim3(per / 64, pl.types), dim3(64 * kRedWaves), 0, st, part, dw, db, r);
+    return hipGetLastError();
+}
+
+} // namespace hexk

@@ -169,4 +169,15 @@ size_t bf16_wgrad_workspace(const ConvShape &sh);
 hipError_t bf16_wgrad(const void *x, const void *dy, float *dw, float *db, void *ws,
                       const ConvShape &sh, hipStream_t st);
 
+// ---- matrix-core kernels for planes of any size and any channel count, k 1
+// to 3, bf16 and fp32, 2-D and 3-D (k_conv_any.hip, k_wgrad_any.hip) --------
+// forward, or (dgrad) the data gradient at in-plane and plane stride 1
+bool conv_any_ok(const ConvShape &sh, Dtype d, bool dgrad);
+hipError_t conv_any(const void *in, const void *w, const void *bias, void *out,
+                    const ConvShape &sh, Dtype d, bool dgrad, bool relu, hipStream_t st);
+bool wgrad_any_ok(const ConvShape &sh, Dtype d);
+size_t wgrad_any_workspace(const ConvShape &sh, Dtype d);
+hipError_t wgrad_any(const void *x, const void *dy, float *dw, float *db, void *ws,
+                     const ConvShape &sh, Dtype d, hipStream_t st);
+
 } // namespace hexk

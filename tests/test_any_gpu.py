@@ -1,0 +1,94 @@
+"""Matrix-core kernels for planes of any size and channel count
+(k_conv_any.hip, k_wgrad_any.hip) against the fp64 oracle, at the sizes where
+they can go wrong: rows of odd length and of the shortest length taken (8),
+one row, several tiles and a ragged last tile, channel counts just past a
+chunk or a 32-channel tile, k = 1 .. 3, strides, both dtypes, 3-D."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import check, torch_mod
+from paper_1903_01814_amd import inputs as gen
+from test_parity3d_gpu import run_bwd_data3, run_bwd_weight3, run_fwd3
+from test_parity_gpu import check_bwd_full, check_fwd_full
+
+pytestmark = pytest.mark.gpu
+
+# N, C_in, C_out, H, W, k, stride
+CASES = [
+    (2, 5, 7, 9, 8, 1, 1),         # shortest rows
+    (3, 24, 24, 1, 9, 1, 1),       # one row: every other window row is padding
+    (2, 16, 17, 18, 19, 2, 1),     # one half chunk (bf16), 17 = half chunk + 1 back
+    (2, 33, 65, 23, 43, 1, 1),     # one channel past a chunk and past two tiles
+    (1, 70, 100, 12, 25, 2, 1),    # several chunks, streamed weights, 4 tiles out
+    (1, 40, 36, 20, 250, 1, 1),    # one row per tile
+    (1, 32, 40, 21, 51, 3, 1),     # k = 3
+    (40, 12, 12, 20, 21, 1, 1),    # more tiles than a block's run
+    (2, 48, 32, 29, 31, 1, 2),     # strides: split columns, odd centres
+    (2, 40, 33, 31, 45, 2, 3),
+]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "N%d_ci%d_co%d_%dx%d_k%d_s%d" % c)
+def test_conv_any_shape(case, dt):
+    N, Ci, Co, H, W, k, s = case
+    rng = np.random.default_rng(300 + sum(case))
+    T = oracle.num_taps(k)
+    x = gen.round_to(rng.normal(size=(N, Ci, H, W)), dt)
+    w = gen.round_to(rng.normal(size=(Co, Ci, T)) / np.sqrt(Ci * T), dt)
+    b = gen.round_to(rng.normal(size=Co) * 0.1, dt)
+    check_fwd_full(x, w, b, k, s, dt, what="fwd")
+    check_fwd_full(x, w, None, k, s, dt, relu=True, what="fwd relu")
+    dy = gen.round_to(rng.normal(size=(N, Co) + oracle.out_shape(H, W, s)), dt)
+    check_bwd_full(x, w, dy, k, s, dt, what="bwd")
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [
+    # N, C_in, C_out, D, H, W, k, kz, stride, stride_z
+    (2, 6, 9, 3, 9, 11, 1, 1, 1, 1), (1, 17, 33, 4, 20, 19, 1, 1, 1, 1),
+    (1, 8, 8, 2, 10, 13, 2, 2, 1, 1), (1, 40, 12, 5, 11, 17, 1, 1, 2, 2)])
+def test_conv3d_any_shape(case, dt):
+    N, Ci, Co, D, H, W, k, kz, s, sz = case
+    rng = np.random.default_rng(400 + sum(case))
+    Z, T = 2 * kz + 1, oracle.num_taps(k)
+    x = gen.round_to(rng.normal(size=(N, Ci, D, H, W)), dt)
+    w = gen.round_to(rng.normal(size=(Co, Ci, Z, T)) / np.sqrt(Ci * Z * T), dt)
+    b = gen.round_to(rng.normal(size=Co) * 0.1, dt)
+    a = np.abs
+    check(dt, run_fwd3(x, w, b, k, kz, s, sz, dt), oracle.conv3d_fwd(x, w, b, k, kz, s, sz),
+          oracle.conv3d_fwd(a(x), a(w), a(b), k, kz, s, sz), "fwd")
+    Do, Ho, Wo = oracle.out_shape3d(D, H, W, s, sz)
+    dy = gen.round_to(rng.normal(size=(N, Co, Do, Ho, Wo)), dt)
+    check(dt, run_bwd_data3(dy, w, k, kz, s, sz, D, H, W, dt),
+          oracle.conv3d_bwd_data(dy, w, k, kz, s, sz, D, H, W),
+          oracle.conv3d_bwd_data(a(dy), a(w), k, kz, s, sz, D, H, W), "dx")
+    dw, db = run_bwd_weight3(x, dy, k, kz, s, sz, dt)
+    rw, rb = oracle.conv3d_bwd_weight(x, dy, k, kz, s, sz)
+    mw, mb = oracle.conv3d_bwd_weight(a(x), a(dy), k, kz, s, sz)
+    check(dt, dw, rw, mw, "dw")
+    check(dt, db, rb, mb, "db")
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_weight_gradient_keeps_infinities(dt):
+    """An infinity in x next to a tile's end reaches the sums of its own taps
+    as an infinity, and no other sum: 19 x 27 pixels end inside a step."""
+    torch = torch_mod()
+    from paper_1903_01814_amd import hexconv as hx
+    tdt = torch.float32 if dt == "f32" else torch.bfloat16
+    g = torch.Generator().manual_seed(0)
+    x = torch.rand((1, 8, 19, 27), generator=g).to(tdt)
+    dy = (torch.rand((1, 8, 19, 27), generator=g) + 0.5).to(tdt)
+    x[0, 3, 18, 26] = float("inf")
+    dw = torch.empty((8, 8, 7), device="cuda")
+    nws = hx.hexconv_bwd_weight_workspace(1, 8, 8, 19, 27, 1, 1, 0 if dt == "f32" else 1)
+    ws = torch.empty(nws, dtype=torch.uint8, device="cuda")
+    hx.hexconv_bwd_weight(x.cuda(), dy.cuda(), dw, None, ws, 1, 1)
+    dw = dw.cpu()
+    hit = torch.isinf(dw)
+    assert not torch.isnan(dw).any()
+    # corner (18, 26), an even column: the window centres that reach it inside
+    # the tensor are itself and its neighbours (17, 26), (18, 25), (17, 25)
+    assert hit[:, 3].sum(1).eq(4).all() and not hit[:, [0, 1, 2, 4, 5, 6, 7]].any()
