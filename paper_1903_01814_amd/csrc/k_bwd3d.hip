@@ -240,7 +240,7 @@ Bwd3Plan plan_bwd3(const ConvShape &sh)
     Bwd3Plan pl{};
     pl.ok = false;
     if (sh.s != 1 || sh.sz != 1 || (sh.k != 1 && sh.k != 2) || sh.kz > 2 ||
-        (sh.Ci != 1 && sh.Ci != 2) || sh.W % 4 != 0 || sh.W > 256 || sh.N < 1)
+        (sh.Ci != 1 && sh.Ci != 2) || sh.W < 4 || sh.W > 256 || sh.N < 1)
         return pl;
     const int K = sh.k;
     Bwd3Args &a = pl.a;
@@ -264,7 +264,7 @@ Bwd3Plan plan_bwd3(const ConvShape &sh)
     a.CC = a.nck == 1 ? sh.Co : (cdiv(sh.Co, a.nck) + 1) & ~1;
     pl.lds = per_ch * a.CC;
     // staging rows per thread (ShearPrefetch): one 4-column group per thread
-    const int groups = ShearPrefetch<1>::groups(sh.W + 2 * K);
+    const int groups = ShearPrefetch<1>::groups((sh.W + 3) / 4 * 4 + 2 * K);
     if (groups > pl.threads)
         return pl;
     // staging rows per thread: more threads (idle in the products) until a

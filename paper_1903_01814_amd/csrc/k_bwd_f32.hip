@@ -57,7 +57,7 @@ template <int K> struct Geo {
 };
 
 struct BwdTiling {
-    int W4;            // float4 groups per row
+    int W4;            // groups of 4 columns per row
     int CS;            // LDS words per x channel and per constant plane
     int CSD;           // LDS words per dy channel
     int xo, zo, oo;    // LDS offsets: x planes, zeros plane, ones plane
@@ -75,7 +75,10 @@ struct BwdTiling {
 // Where the staging items of a thread go: item i = tid + u * kThreads is
 // (channel, window row, float4 column group).  Its LDS word and its element
 // offset inside the image do not depend on the tile, so they are computed
-// once (pk: LDS word | window row << 16 | dy item << 24 | live << 25).
+// once (pk: LDS word | window row << 16 | dy item << 24 | live << 25 | odd
+// first column << 26).  The last group of a row whose length is no multiple
+// of 4 is moved back to end with it: it then starts at any column, and some
+// columns are written twice, with the same values.
 template <int K, int U> struct StageMap {
     int pk[U], goff[U];
 
@@ -87,15 +90,16 @@ template <int K, int U> struct StageMap {
         for (int u = 0; u < U; ++u) {
             const int i = threadIdx.x + u * kThreads;
             const int q = static_cast<int>(fdiv(static_cast<uint32_t>(i), bt.fdw4));
-            const int c4 = i - q * bt.W4;
+            const int c0 = min(4 * (i - q * bt.W4), sh.W - 4);
             const int ch = static_cast<int>(fdiv(static_cast<uint32_t>(q), bt.fdlr));
             const int rr = q - ch * G::LR;
             const bool live = i < bt.nitems;
             const bool isdy = ch < sh.Co;
             const int base = isdy ? ch * bt.CSD : bt.xo + (ch - sh.Co) * bt.CS;
-            const int dst = live ? base + G::colbase(4 * c4) + rr : bt.dummy;
-            pk[u] = dst | (rr << 16) | (isdy ? 1 << 24 : 0) | (live ? 1 << 25 : 0);
-            goff[u] = (isdy ? ch : ch - sh.Co) * HW + rr * sh.W + 4 * c4;
+            const int dst = live ? base + G::colbase(c0) + rr : bt.dummy;
+            pk[u] = dst | (rr << 16) | (isdy ? 1 << 24 : 0) | (live ? 1 << 25 : 0) |
+                    ((c0 & 1) << 26);
+            goff[u] = (isdy ? ch : ch - sh.Co) * HW + rr * sh.W + c0;
         }
     }
 };
@@ -135,12 +139,13 @@ template <typename TT, int U> struct StageBuf {
             const int rr = (m.pk[u] >> 16) & 0xff;
             const bool ok = ((m.pk[u] >> 25) & 1) && rr >= rlo && rr < rhi;
             const TT *b = ((m.pk[u] >> 24) & 1) ? dyn : xn;
-            v[u] = *reinterpret_cast<const Raw *>(ok ? b + m.goff[u] : x);
+            __builtin_memcpy(&v[u], ok ? b + m.goff[u] : x, sizeof(Raw)); // at any element
             okm |= ok ? 1u << u : 0u;
         }
     }
 
-    // columns 4c4 .. 4c4+3 of a row sit at +0, +P, +2P-1, +3P-1
+    // four columns of a row from an even one sit at +0, +P, +2P-1, +3P-1,
+    // from an odd one at +0, +P-1, +2P-1, +3P-2
     template <int K>
     __device__ __forceinline__ void commit(const StageMap<K, U> &m, float *__restrict__ lds) const
     {
@@ -149,10 +154,11 @@ template <typename TT, int U> struct StageBuf {
         for (int u = 0; u < U; ++u) {
             const float4 q = ((okm >> u) & 1) ? widen(v[u]) : make_float4(0.f, 0.f, 0.f, 0.f);
             float *d = lds + (m.pk[u] & 0xffff);
+            const int od = (m.pk[u] >> 26) & 1;
             d[0] = q.x;
-            d[G::P] = q.y;
+            d[G::P - od] = q.y;
             d[2 * G::P - 1] = q.z;
-            d[3 * G::P - 1] = q.w;
+            d[3 * G::P - 1 - od] = q.w;
         }
     }
 };
@@ -378,15 +384,17 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
         // Exactly CI stores per thread (CI * TR * W / 4 <= CI * kThreads for
         // W <= 256); a thread past the end repeats the last element's store
         // (same value, same address), so the count of stores in flight is
-        // fixed and the loads issued before them are not waited for.
+        // fixed and the loads issued before them are not waited for.  Where
+        // rows * W is no multiple of 4 the last store of a plane is moved
+        // back to end with the tile (some elements stored twice).
         if (do_dx != 0) {
-            const int perp4 = rows * W / 4;
+            const int perp4 = (rows * W + 3) / 4;
 #pragma unroll
             for (int u = 0; u < CI; ++u) {
                 const int e4 = min(tid + u * kThreads, CI * perp4 - 1);
                 {
                     const int ci = e4 >= perp4 ? 1 : 0;
-                    const int rem = 4 * (e4 - ci * perp4);
+                    const int rem = min(4 * (e4 - ci * perp4), rows * W - 4);
                     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
                     for (int gg = 0; gg < bt.G; ++gg) {
                         const float *q = dxp + (gg * CI + ci) * kTR * W + rem;
@@ -397,13 +405,9 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
                     }
                     TT *dst = dx + (static_cast<size_t>(n) * CI + ci) * sh.H * W +
                               static_cast<size_t>(r0) * W + rem;
-                    if constexpr (sizeof(TT) == 4) {
-                        *reinterpret_cast<float4 *>(dst) = s;
-                    } else {
-                        *reinterpret_cast<uint2 *>(dst) = make_uint2(
-                            from_f<bf16raw>(s.x) | (uint32_t(from_f<bf16raw>(s.y)) << 16),
-                            from_f<bf16raw>(s.z) | (uint32_t(from_f<bf16raw>(s.w)) << 16));
-                    }
+                    const TT r[4] = {from_f<TT>(s.x), from_f<TT>(s.y), from_f<TT>(s.z),
+                                     from_f<TT>(s.w)};
+                    __builtin_memcpy(dst, r, sizeof(r));
                 }
             }
         }
@@ -460,7 +464,7 @@ BwdTiling bwd_tiling(const ConvShape &sh)
 {
     BwdTiling bt;
     const int LR = kTR + 2 * sh.k, P = LR + 1, LC = sh.W + 2 * sh.k;
-    bt.W4 = sh.W / 4;
+    bt.W4 = cdiv(sh.W, 4);
     bt.CS = LC * P;
     // dy channel stride == 2 mod 32: the 16 channels x 4 rows of an A
     // fragment fall in distinct banks of each half-wave
@@ -574,7 +578,7 @@ hipError_t bwd_fused_t(const TT *x, const TT *dy, const TT *w, TT *dx, float *dw
 
 bool smallc_bwd_fused_ok(const ConvShape &sh, Dtype d)
 {
-    if (sh.s != 1 || sh.k < 1 || sh.k > 3 || sh.Ci > 2 || sh.Co > 32 || sh.W % 4 != 0 ||
+    if (sh.s != 1 || sh.k < 1 || sh.k > 3 || sh.Ci > 2 || sh.Co > 32 || sh.W < 4 ||
         sh.W > kDxThreads || sh.Ci * sh.T + 1 > 64)
         return false;
     const BwdTiling bt = bwd_tiling(sh);

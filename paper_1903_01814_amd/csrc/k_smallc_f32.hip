@@ -32,6 +32,7 @@
 // yields db.  Per-block partial sums are written to the workspace and added
 // in a fixed order by k_reduce.hip (deterministic).
 #include <algorithm>
+#include <type_traits>
 
 #include "hexdev.h"
 #include "kernels.h"
@@ -90,10 +91,10 @@ __device__ __forceinline__ ShearTile window_of(const TileOrigin &o, const Tiling
 
 // Row-major copy of a tile of `nch` planes (no halo) staged through
 // registers: dst[ch * dstride + pr * TW + pc].  Work split: one 4-column group
-// per thread, (channel, row) pairs strided by blockDim / groups.  Requires
-// W % 4 == 0 (so TW, the tile's columns and every group of 4 lie inside the
-// row): each item is one 16-byte (fp32) or 8-byte (bf16) load and, dstride
-// being even, two 8-byte LDS writes.
+// per thread, (channel, row) pairs strided by blockDim / groups; each item is
+// one 16-byte (fp32) or 8-byte (bf16) load.  The last group of a row whose
+// length is no multiple of 4 is moved back to end with it (some columns are
+// then written twice, with the same values).
 template <int U> struct PlainPrefetch {
     float v[U][4];
     int da[U];
@@ -113,14 +114,15 @@ template <int U> struct PlainPrefetch {
         const int ng = groups(TW);
         const int rstep = blockDim.x / ng;
         const int g = threadIdx.x % ng, fr0 = threadIdx.x / ng;
-        const int pc = 4 * g;
+        const bool in = 4 * g < o.cols;
+        const int pc = min(4 * g, o.cols - 4);
         const int total = nch * TR;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int fr = fr0 + u * rstep;
             const int ch = static_cast<int>(fdiv(static_cast<uint32_t>(fr), fdtr));
             const int pr = fr - ch * TR;
-            const bool ok = fr0 < rstep && fr < total && pr < o.rows && pc < o.cols;
+            const bool ok = fr0 < rstep && fr < total && pr < o.rows && in;
             da[u] = ok ? ch * dstride + pr * TW + pc : -1;
             // items without data read the plane's first group (always valid)
             const T *p =
@@ -134,8 +136,9 @@ template <int U> struct PlainPrefetch {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (da[u] >= 0) {
-                *reinterpret_cast<float2 *>(dst + da[u]) = make_float2(v[u][0], v[u][1]);
-                *reinterpret_cast<float2 *>(dst + da[u] + 2) = make_float2(v[u][2], v[u][3]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    dst[da[u] + j] = v[u][j];
             }
         }
     }
@@ -148,12 +151,15 @@ template <int U> struct PlainPrefetch {
 // the staged channels are the 2 kz + 1 planes around the centre plane of
 // every input channel (ch = ci * Z + dz), so the contraction runs over
 // (ci, dz, t) -- exactly the order of w[C_out][C_in][2kz+1][T].
-template <typename TT, int K, int KS, int U, bool D3>
+// RAG: W is no multiple of 4.  (A variant of its own: with the cut store as a
+// branch of the one kernel, even a uniform one, the M-tiles of a tile no
+// longer overlap: 64 volumes of 32 planes of 40 x 40, 1 -> 16 channels, 69 ->
+// 82 us.)
+template <typename TT, int K, int KS, int U, bool D3, bool RAG>
 __global__ __launch_bounds__(kThreads) void fwd_smallc_k(
     const TT *__restrict__ x, const TT *__restrict__ w, const TT *__restrict__ bias,
     TT *__restrict__ y, ConvShape sh, int relu, Tiling tg)
 {
-    // W % 4 == 0 (smallc_fwd_ok): every 4-pixel group of a tile row is whole
     constexpr int T = num_taps(K);
     extern __shared__ float xs[];
     const int NCH = D3 ? sh.Ci * sh.Z : sh.Ci; // staged channels
@@ -286,8 +292,8 @@ __global__ __launch_bounds__(kThreads) void fwd_smallc_k(
             for (int s = 0; s < KS; ++s)
                 acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kval[s] ? a[s] : 0.f, bw[s], acc, 0,
                                                            0, 0);
-            // D rows of this lane: slots q0..q0+3, one tile row (TW % 4 == 0,
-            // and W % 4 == 0 puts all four inside the tile or none)
+            // D rows of this lane: slots q0..q0+3, one tile row (TW % 4 == 0);
+            // where W % 4 != 0 the last group of a row is cut
             if (co >= sh.Co || (qrc[i] >> 16) >= o.rows || (qrc[i] & 0xffff) >= o.cols)
                 continue;
             float v[4];
@@ -298,12 +304,29 @@ __global__ __launch_bounds__(kThreads) void fwd_smallc_k(
                     v[j] = fmaxf(v[j], 0.f);
             }
             TT *dst = yb + qoff[i];
-            if constexpr (sizeof(TT) == 4) {
-                *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+            if constexpr (!RAG) {
+                if constexpr (sizeof(TT) == 4) {
+                    *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+                } else {
+                    const uint32_t lo =
+                        from_f<bf16raw>(v[0]) | (uint32_t(from_f<bf16raw>(v[1])) << 16);
+                    const uint32_t hi =
+                        from_f<bf16raw>(v[2]) | (uint32_t(from_f<bf16raw>(v[3])) << 16);
+                    *reinterpret_cast<uint2 *>(dst) = make_uint2(lo, hi);
+                }
             } else {
-                const uint32_t lo = from_f<bf16raw>(v[0]) | (uint32_t(from_f<bf16raw>(v[1])) << 16);
-                const uint32_t hi = from_f<bf16raw>(v[2]) | (uint32_t(from_f<bf16raw>(v[3])) << 16);
-                *reinterpret_cast<uint2 *>(dst) = make_uint2(lo, hi);
+                const TT r[4] = {from_f<TT>(v[0]), from_f<TT>(v[1]), from_f<TT>(v[2]),
+                                 from_f<TT>(v[3])};
+                const int nq = o.cols - (qrc[i] & 0xffff);
+                if (nq >= 4) {
+                    __builtin_memcpy(dst, r, sizeof(r));
+                } else {
+                    dst[0] = r[0];
+                    if (nq > 1)
+                        dst[1] = r[1];
+                    if (nq > 2)
+                        dst[2] = r[2];
+                }
             }
         }
     }
@@ -640,10 +663,17 @@ int bwd_ic_chunk(const ConvShape &sh, const Tiling &tg)
 
 // ------------------------------------------------------------- launchers
 
+// rows of whole 4-column groups, or rows that one tile holds whole (its last
+// group is then moved back to end with the row)
+static bool smallc_width_ok(const ConvShape &sh)
+{
+    return sh.W % 4 == 0 || (sh.W > 4 && sh.W <= 128);
+}
+
 bool smallc_fwd_ok(const ConvShape &sh)
 {
     const int nch = sh.Ci * sh.Z;
-    if (sh.s != 1 || sh.k < 1 || sh.k > 3 || nch * sh.T > 64 || sh.W % 4 != 0)
+    if (sh.s != 1 || sh.k < 1 || sh.k > 3 || nch * sh.T > 64 || !smallc_width_ok(sh))
         return false;
     const ConvShape e = fwd_view(sh);
     const Tiling tg = make_tiling(e, kFwdTarget);
@@ -652,7 +682,7 @@ bool smallc_fwd_ok(const ConvShape &sh)
 }
 
 namespace {
-template <typename TT>
+template <typename TT, bool RAG>
 hipError_t smallc_fwd_t(const TT *x, const TT *w, const TT *b, TT *y, const ConvShape &sh0,
                         bool relu, hipStream_t st)
 {
@@ -667,18 +697,23 @@ hipError_t smallc_fwd_t(const TT *x, const TT *w, const TT *b, TT *y, const Conv
 #define HEX_FWD_SC(KV, KSV, UV)                                                              \
     do {                                                                                     \
         if (d3)                                                                              \
-            HEX_LAUNCH((fwd_smallc_k<TT, KV, KSV, UV, true>), grid, dim3(kThreads), lds, st, \
-                       x, w, b, y, sh, relu ? 1 : 0, tg);                                 \
+            HEX_LAUNCH((fwd_smallc_k<TT, KV, KSV, UV, true, RAG>), grid, dim3(kThreads),     \
+                       lds, st, x, w, b, y, sh, relu ? 1 : 0, tg);                           \
         else                                                                                 \
-            HEX_LAUNCH((fwd_smallc_k<TT, KV, KSV, UV, false>), grid, dim3(kThreads), lds,    \
-                       st, x, w, b, y, sh, relu ? 1 : 0, tg);                             \
+            HEX_LAUNCH((fwd_smallc_k<TT, KV, KSV, UV, false, RAG>), grid, dim3(kThreads),    \
+                       lds, st, x, w, b, y, sh, relu ? 1 : 0, tg);                           \
     } while (0)
 #define HEX_FWD_SC_U(KV, KSV)                                                                \
     do {                                                                                     \
-        if (U == 1) HEX_FWD_SC(KV, KSV, 1);                                                  \
-        else if (U == 2) HEX_FWD_SC(KV, KSV, 2);                                             \
-        else if (U == 4) HEX_FWD_SC(KV, KSV, 4);                                             \
-        else HEX_FWD_SC(KV, KSV, 8);                                                         \
+        if constexpr (RAG) {                                                                 \
+            if (U <= 2) HEX_FWD_SC(KV, KSV, 2);                                              \
+            else HEX_FWD_SC(KV, KSV, 8);                                                     \
+        } else {                                                                             \
+            if (U == 1) HEX_FWD_SC(KV, KSV, 1);                                              \
+            else if (U == 2) HEX_FWD_SC(KV, KSV, 2);                                         \
+            else if (U == 4) HEX_FWD_SC(KV, KSV, 4);                                         \
+            else HEX_FWD_SC(KV, KSV, 8);                                                     \
+        }                                                                                    \
     } while (0)
     if (sh.k == 1) {
         if (KS <= 2) HEX_FWD_SC_U(1, 2);
@@ -702,11 +737,15 @@ hipError_t smallc_fwd_t(const TT *x, const TT *w, const TT *b, TT *y, const Conv
 hipError_t smallc_fwd(const void *x, const void *w, const void *b, void *y, const ConvShape &sh,
                       Dtype d, bool relu, hipStream_t st)
 {
-    if (d == F32)
-        return smallc_fwd_t(static_cast<const float *>(x), static_cast<const float *>(w),
-                            static_cast<const float *>(b), static_cast<float *>(y), sh, relu, st);
-    return smallc_fwd_t(static_cast<const bf16raw *>(x), static_cast<const bf16raw *>(w),
-                        static_cast<const bf16raw *>(b), static_cast<bf16raw *>(y), sh, relu, st);
+    auto run = [&](auto *p) {
+        using TT = std::remove_pointer_t<decltype(p)>;
+        const TT *xt = static_cast<const TT *>(x), *wt = static_cast<const TT *>(w);
+        const TT *bt = static_cast<const TT *>(b);
+        TT *yt = static_cast<TT *>(y);
+        return sh.W % 4 == 0 ? smallc_fwd_t<TT, false>(xt, wt, bt, yt, sh, relu, st)
+                             : smallc_fwd_t<TT, true>(xt, wt, bt, yt, sh, relu, st);
+    };
+    return d == F32 ? run(static_cast<float *>(nullptr)) : run(static_cast<bf16raw *>(nullptr));
 }
 
 bool smallc_bwd_data_ok(const ConvShape &sh)
@@ -763,7 +802,7 @@ bool smallc_wgrad_ok(const ConvShape &sh0)
 {
     const ConvShape sh = fwd_view(sh0);
     const int nch = sh.Ci * sh.Z;
-    if (sh.s != 1 || sh.k < 1 || sh.k > 3 || nch * sh.T + 1 > 64 || sh.W % 4 != 0)
+    if (sh.s != 1 || sh.k < 1 || sh.k > 3 || nch * sh.T + 1 > 64 || !smallc_width_ok(sh))
         return false;
     const Tiling tg = make_tiling(sh, kWgradTarget);
     return wgrad_lds(sh, tg) <= kLdsLimit && shear_depth(sh, tg, nch) > 0 &&

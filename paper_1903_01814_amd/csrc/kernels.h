@@ -123,7 +123,7 @@ bool smallc_bwd_data_ok(const ConvShape &sh);
 hipError_t smallc_bwd_data(const void *dy, const void *w, void *dx, const ConvShape &sh, Dtype d,
                            hipStream_t st);
 // Data gradient of a 3-D layer with 1 or 2 input channels, float32 or
-// bfloat16, plane and in-plane stride 1, k <= 2, kz <= 2, W % 4 == 0
+// bfloat16, plane and in-plane stride 1, k <= 2, kz <= 2, W >= 4
 // (k_bwd3d.hip).
 bool smallc3d_bwd_data_ok(const ConvShape &sh);
 hipError_t smallc3d_bwd_data(const void *dy, const void *w, void *dx, const ConvShape &sh,

@@ -49,11 +49,14 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv &f)
     return (__umulhi(f.m, n) + n) >> f.l;
 }
 
+// Four consecutive elements at any element address (global memory takes wide
+// loads at element alignment, so rows may start anywhere).
 template <typename T> struct Vec4Load;
 template <> struct Vec4Load<float> {
     __device__ __forceinline__ static void load(const float *p, float v[4])
     {
-        const float4 q = *reinterpret_cast<const float4 *>(p);
+        float4 q;
+        __builtin_memcpy(&q, p, 16);
         v[0] = q.x;
         v[1] = q.y;
         v[2] = q.z;
@@ -63,7 +66,8 @@ template <> struct Vec4Load<float> {
 template <> struct Vec4Load<bf16raw> {
     __device__ __forceinline__ static void load(const bf16raw *p, float v[4])
     {
-        const uint2 q = *reinterpret_cast<const uint2 *>(p);
+        uint2 q;
+        __builtin_memcpy(&q, p, 8);
         v[0] = __uint_as_float(q.x << 16);
         v[1] = __uint_as_float(q.x & 0xffff0000u);
         v[2] = __uint_as_float(q.y << 16);
@@ -253,7 +257,10 @@ __device__ __forceinline__ void stage_plain(float *__restrict__ dst, int dst_pla
 // issues the global loads of a window into registers (up to U float4 per
 // thread), commit() writes them to LDS later -- so the loads of the next
 // tile overlap the compute and stores of the current one.  The work split
-// is that of stage_shear; the launcher checks fits().
+// is that of stage_shear.  Where W is not a multiple of 4 (the window then
+// spans the whole plane, W >= 4), the last group is moved back to end with
+// the row: its first columns are written twice, with the same values, and
+// the groups right of the plane start at column W.
 template <int U> struct ShearPrefetch {
     float v[U][4];
     int da[U];    // LDS address of the group's first column (may be negative)
@@ -262,6 +269,30 @@ template <int U> struct ShearPrefetch {
     int base_c, c;
     bool wcol[4];
     int P;
+    int od; // 1 if the group's first column is odd
+
+    // the group of this thread: first column, row step and first row; whether it lies in the plane
+    __device__ __forceinline__ bool place(int W, const ShearTile &tl, int nt, int &rstep, int &fr0)
+    {
+        const int a4 = (tl.c_lo >= 0 ? tl.c_lo : tl.c_lo - 3) / 4 * 4;
+        const int pad = (4 - (W & 3)) & 3;
+        const int ng = (tl.c_lo + tl.LC + pad - a4 + 3) / 4;
+        rstep = nt / ng;
+        fr0 = threadIdx.x / ng;
+        c = a4 + 4 * static_cast<int>(threadIdx.x % ng);
+        const bool inside = c >= 0 && c < W;
+        if (inside)
+            c = min(c, W - 4);
+        else if (c > 0)
+            c -= pad;
+        P = tl.P;
+        od = c & 1;
+        base_c = (c - tl.c_lo) * P - ((c >> 1) - (tl.c_lo >> 1));
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            wcol[j] = (c + j >= tl.c_lo) && (c + j < tl.c_lo + tl.LC);
+        return inside;
+    }
 
     // column groups of a window of LCmax columns (upper bound) and the rows
     // each thread covers; the launcher checks groups <= threads, rows <= U
@@ -272,29 +303,17 @@ template <int U> struct ShearPrefetch {
         return rstep > 0 ? (nch * LRmax + rstep - 1) / rstep : 1 << 30;
     }
 
-    // Requires ceil(window columns / 4) + 1 <= blockDim.x (one column group
-    // per thread) and W % 4 == 0 (whole 4-column groups are inside or outside
-    // the plane).
+    // Requires groups(columns) <= blockDim.x (one column group per thread),
+    // for W rounded up to a multiple of 4 plus the halo.
     template <typename T>
     __device__ __forceinline__ void load(const T *__restrict__ src, size_t src_plane, int nch,
                                          int H, int W, const ShearTile &tl, int LRmax,
                                          const FastDiv &fdlr)
     {
-        const int nt = blockDim.x;
-        const int a4 = (tl.c_lo >= 0 ? tl.c_lo : tl.c_lo - 3) / 4 * 4;
-        const int ng = (tl.c_lo + tl.LC - a4 + 3) / 4;
-        const int rstep = nt / ng;
-        const int g = threadIdx.x % ng;
-        const int fr0 = threadIdx.x / ng;
+        int rstep, fr0;
+        const bool inside = place(W, tl, blockDim.x, rstep, fr0);
         const int cs = tl.chan_stride();
         const int total = nch * LRmax;
-        P = tl.P;
-        c = a4 + 4 * g;
-        base_c = (c - tl.c_lo) * P - ((c >> 1) - (tl.c_lo >> 1));
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            wcol[j] = (c + j >= tl.c_lo) && (c + j < tl.c_lo + tl.LC);
-        const bool inside = c >= 0 && c + 3 < W;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int fr = fr0 + u * rstep;
@@ -320,21 +339,10 @@ template <int U> struct ShearPrefetch {
                                           int nch, int H, int W, const ShearTile &tl, int LRmax,
                                           const FastDiv &fdlr)
     {
-        const int nt = blockDim.x;
-        const int a4 = (tl.c_lo >= 0 ? tl.c_lo : tl.c_lo - 3) / 4 * 4;
-        const int ng = (tl.c_lo + tl.LC - a4 + 3) / 4;
-        const int rstep = nt / ng;
-        const int g = threadIdx.x % ng;
-        const int fr0 = threadIdx.x / ng;
+        int rstep, fr0;
+        const bool inside = place(W, tl, blockDim.x, rstep, fr0);
         const int cs = tl.chan_stride();
         const int total = nch * LRmax;
-        P = tl.P;
-        c = a4 + 4 * g;
-        base_c = (c - tl.c_lo) * P - ((c >> 1) - (tl.c_lo >> 1));
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            wcol[j] = (c + j >= tl.c_lo) && (c + j < tl.c_lo + tl.LC);
-        const bool inside = c >= 0 && c + 3 < W;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int fr = fr0 + u * rstep;
@@ -354,7 +362,8 @@ template <int U> struct ShearPrefetch {
 
     __device__ __forceinline__ void commit(float *__restrict__ dst) const
     {
-        const int o1 = P, o2 = 2 * P - 1, o3 = 3 * P - 1;
+        // a column pair loses a row at its second (even) column
+        const int o1 = P - od, o2 = 2 * P - 1, o3 = 3 * P - 1 - od;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (live[u]) {

@@ -71,6 +71,31 @@ def test_conv3d_any_shape(case, dt):
     check(dt, db, rb, mb, "db")
 
 
+# Few input channels on rows that are no multiple of 4 (the last group of four
+# columns is moved back to end with the row): each remainder, the shortest and
+# the longest row that a tile holds whole, a row past it, one input row.
+SMALL = [
+    # N, C_in, C_out, H, W, k
+    (2, 1, 4, 9, 5, 1), (2, 1, 16, 21, 43, 2), (3, 2, 16, 25, 45, 1), (2, 2, 20, 17, 46, 2),
+    (1, 1, 32, 33, 127, 2), (2, 3, 16, 20, 21, 1), (2, 1, 17, 13, 6, 3), (2, 3, 33, 15, 49, 2),
+    (1, 1, 8, 20, 131, 1), (1, 2, 16, 7, 255, 1), (100, 1, 16, 24, 37, 1), (2, 2, 5, 1, 11, 1)]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("case", SMALL, ids=lambda c: "N%d_ci%d_co%d_%dx%d_k%d" % c)
+def test_few_channels_any_width(case, dt):
+    test_conv_any_shape(case + (1,), dt)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [
+    (2, 1, 8, 5, 20, 25, 1, 1, 1, 1), (1, 2, 16, 4, 13, 43, 1, 1, 1, 1),
+    (1, 1, 16, 3, 9, 130, 1, 1, 1, 1), (1, 2, 40, 4, 15, 19, 1, 1, 1, 1),
+    (1, 1, 8, 3, 10, 7, 2, 2, 1, 1), (1, 1, 12, 6, 17, 46, 1, 1, 1, 2)])
+def test_few_channels_any_width_3d(case, dt):
+    test_conv3d_any_shape(case, dt)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_weight_gradient_keeps_infinities(dt):
     """An infinity in x next to a tile's end reaches the sums of its own taps
