@@ -542,6 +542,8 @@ int hexpool_fwd(const void *x, void *y, uint8_t *argmax_tap, int N, int C, int H
     uint8_t *am = mode == HEX_POOL_MAX ? argmax_tap : nullptr;
     if (!force_generic() && hexk::pool_fast_ok(sh, d))
         return launched(hexk::pool_fwd_fast(x, y, am, sh, mode, d, st));
+    if (!force_generic() && hexk::pool_any_ok(sh, d, false, false, mode))
+        return launched(hexk::pool_any_fwd(x, y, am, sh, mode, d, false, st));
     return launched(hexk::pool_fwd_generic(x, y, am, sh, mode, d, false, st));
 }
 
@@ -563,8 +565,18 @@ int hexpool_bwd(const void *dy, const uint8_t *argmax_tap, const void *relu_y, v
         return HEX_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Dtype d = static_cast<Dtype>(dt);
+    // The mean's gradient at stride 1 gathers (512 x 32 planes of 48 x 48,
+    // bf16, k = 1: 228 -> 113 us, k = 2: 1306 -> 218; 64 x 64 of 40 x 40: 25 ->
+    // 27 and 70 -> 49), and so does the one-tap pool; every other shape of
+    // whole rows is at least as fast by phases (stride 2, max, 256 x 64 of
+    // 40 x 40: 21 us against 28).
+    if (!force_generic() && sh.Ho > 0 && mode == HEX_POOL_AVG && sh.s == 1 &&
+        hexk::pool_any_ok(sh, d, false, true, mode))
+        return launched(hexk::pool_any_bwd(dy, argmax_tap, relu_y, dx, sh, mode, d, false, st));
     if (!force_generic() && sh.Ho > 0 && hexk::pool_fast_ok(sh, d))
         return launched(hexk::pool_bwd_fast(dy, argmax_tap, relu_y, dx, sh, mode, d, st));
+    if (!force_generic() && hexk::pool_any_ok(sh, d, false, true, mode))
+        return launched(hexk::pool_any_bwd(dy, argmax_tap, relu_y, dx, sh, mode, d, false, st));
     return launched(hexk::pool_bwd_generic(dy, argmax_tap, relu_y, dx, sh, mode, d, false, st));
 }
 
@@ -725,9 +737,12 @@ int hexpool3d_fwd(const void *x, void *y, uint16_t *argmax, int N, int C, int D,
         return rc;
     if (sh.Ho == 0)
         return HEX_OK;
-    return launched(hexk::pool_fwd_generic(x, y, mode == HEX_POOL_MAX ? argmax : nullptr, sh,
-                                           mode, static_cast<Dtype>(dt), true,
-                                           static_cast<hipStream_t>(stream)));
+    const Dtype d = static_cast<Dtype>(dt);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    uint16_t *am = mode == HEX_POOL_MAX ? argmax : nullptr;
+    if (!force_generic() && hexk::pool_any_ok(sh, d, true, false, mode))
+        return launched(hexk::pool_any_fwd(x, y, am, sh, mode, d, true, st));
+    return launched(hexk::pool_fwd_generic(x, y, am, sh, mode, d, true, st));
 }
 
 int hexpool3d_bwd(const void *dy, const uint16_t *argmax, const void *relu_y, void *dx, int N,
@@ -746,9 +761,11 @@ int hexpool3d_bwd(const void *dy, const uint16_t *argmax, const void *relu_y, vo
         return rc;
     if (sh.Ho > 0 && (dy == nullptr || (mode == HEX_POOL_MAX && argmax == nullptr)))
         return HEX_ERR_INVALID_ARG;
-    return launched(hexk::pool_bwd_generic(dy, argmax, relu_y, dx, sh, mode,
-                                           static_cast<Dtype>(dt), true,
-                                           static_cast<hipStream_t>(stream)));
+    const Dtype d = static_cast<Dtype>(dt);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (!force_generic() && hexk::pool_any_ok(sh, d, true, true, mode))
+        return launched(hexk::pool_any_bwd(dy, argmax, relu_y, dx, sh, mode, d, true, st));
+    return launched(hexk::pool_bwd_generic(dy, argmax, relu_y, dx, sh, mode, d, true, st));
 }
 
 int hexconv_timing_begin(void)

@@ -114,6 +114,15 @@ hipError_t pool_fwd_fast(const void *x, void *y, uint8_t *am, const ConvShape &s
 hipError_t pool_bwd_fast(const void *dy, const uint8_t *am, const void *relu_y, void *dx,
                          const ConvShape &sh, int mode, Dtype dt, hipStream_t st);
 
+// ---- pooling on planes of any size and (d3) in three dimensions, k 1 to 3,
+// in-plane stride 1 to 3, and the gradient of the one-tap mean pool
+// (k_pool_any.hip); argmax uint8_t, d3: uint16_t -------------------------
+bool pool_any_ok(const ConvShape &sh, Dtype dt, bool d3, bool bwd, int mode);
+hipError_t pool_any_fwd(const void *x, void *y, void *am, const ConvShape &sh, int mode, Dtype dt,
+                        bool d3, hipStream_t st);
+hipError_t pool_any_bwd(const void *dy, const void *am, const void *relu_y, void *dx,
+                        const ConvShape &sh, int mode, Dtype dt, bool d3, hipStream_t st);
+
 // ---- few input channels (C_in*T <= 64), stride 1, fp32 or bf16 data,
 // fp32 arithmetic --------------------------------------------------------
 bool smallc_fwd_ok(const ConvShape &sh);

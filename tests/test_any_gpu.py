@@ -10,7 +10,7 @@ import oracle
 from gpu_helpers import check, torch_mod
 from paper_1903_01814_amd import inputs as gen
 from test_parity3d_gpu import run_bwd_data3, run_bwd_weight3, run_fwd3
-from test_parity_gpu import check_bwd_full, check_fwd_full
+from test_parity_gpu import check_bwd_full, check_fwd_full, run_pool_bwd, test_pool_sweep
 
 pytestmark = pytest.mark.gpu
 
@@ -94,6 +94,69 @@ def test_few_channels_any_width(case, dt):
     (1, 1, 8, 3, 10, 7, 2, 2, 1, 1), (1, 1, 12, 6, 17, 46, 1, 1, 1, 2)])
 def test_few_channels_any_width_3d(case, dt):
     test_conv3d_any_shape(case, dt)
+
+
+# Pools on planes that are no whole 16-byte rows, and 3-D pools: single rows and
+# columns, every stride's cells cut at the right and bottom border, planes
+# beside the volume; one-tap mean (the ReLU mask) with a tail past 16 bytes.
+POOL = [
+    # N, C, H, W, k, stride
+    (2, 3, 9, 11, 1, 2), (1, 2, 45, 51, 1, 2), (2, 5, 1, 7, 1, 1), (1, 3, 7, 1, 1, 2),
+    (2, 3, 13, 10, 2, 2), (1, 9, 22, 23, 2, 3), (1, 2, 17, 9, 3, 1), (3, 3, 8, 13, 3, 3),
+    (1, 3, 16, 16, 1, 1), (1, 2, 16, 24, 2, 1)]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("case", POOL, ids=lambda c: "N%d_c%d_%dx%d_k%d_s%d" % c)
+def test_pool_any_shape(case, mode, dt):
+    test_pool_sweep(case, mode, dt)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(1, 3, 5, 7), (2, 4, 16, 16), (1, 1, 1, 3)])
+def test_relu_mask_any_shape(shape, dt):
+    rng = np.random.default_rng(sum(shape))
+    dy = gen.round_to(rng.normal(size=shape), dt)
+    y = np.maximum(gen.round_to(rng.normal(size=shape), dt), 0.0)
+    H, W = shape[2:]
+    np.testing.assert_array_equal(run_pool_bwd(dy, None, y, 0, 1, 1, H, W, dt), dy * (y > 0))
+    np.testing.assert_array_equal(run_pool_bwd(dy, None, None, 0, 1, 1, H, W, dt), dy)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("case", [
+    (1, 2, 5, 9, 11, 1, 1, 2, 1), (2, 2, 7, 12, 10, 1, 1, 2, 2), (1, 3, 4, 8, 9, 2, 2, 1, 3),
+    (1, 2, 1, 5, 6, 1, 1, 3, 1), (1, 2, 10, 7, 8, 1, 4, 2, 5)])
+def test_pool3d_any_shape(case, mode, dt):
+    """Against the generic kernels, bit for bit: the same terms in the same order."""
+    import os
+    from paper_1903_01814_amd import hexconv as hx
+    torch = torch_mod()
+    N, C, D, H, W, k, kz, s, sz = case
+    tdt = torch.float32 if dt == "f32" else torch.bfloat16
+    g = torch.Generator().manual_seed(sum(case))
+    x = (torch.randn((N, C, D, H, W), generator=g) * 2).round().div(2).to(tdt).cuda()
+    shape = (N, C) + tuple(hx.hex_out_shape3d(D, H, W, k, kz, s, sz))
+    dy = torch.randn(shape, generator=g).to(tdt).cuda()
+    got = []
+    try:
+        for path in ("", "generic"):
+            os.environ["HEXCONV_PATH"] = path
+            y = torch.full(shape, float("nan"), dtype=tdt, device="cuda")
+            am = torch.zeros(shape, dtype=torch.int16, device="cuda") if mode == 0 else None
+            hx.hexpool3d_fwd(x, y, am, k, kz, s, sz, mode)
+            res = [y]
+            for relu in (None, x):
+                dx = torch.full(x.shape, float("nan"), dtype=tdt, device="cuda")
+                hx.hexpool3d_bwd(dy, am, relu, dx, k, kz, s, sz, mode)
+                res.append(dx)
+            got.append(res + ([am] if mode == 0 else []))
+    finally:
+        os.environ.pop("HEXCONV_PATH", None)
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
