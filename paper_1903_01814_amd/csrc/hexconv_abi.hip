@@ -212,10 +212,17 @@ WgradPath wgrad_path(const ConvShape &sh, Dtype d)
     // at k = 2; 32 or 64 output channels and k = 3 favour the bf16 kernels)
     if (small && sh.Co <= 16 && sh.k <= 2)
         return WgradPath::Small;
-    // several passes re-read x once per pass: then the single-pass kernel,
-    // where it applies, is the faster one
+    // one pass of the tuned kernel (64 -> 64 channels, 128 x 128, N = 64: 98 us
+    // against 149 on the kernel for any shape); several passes re-read x, and
+    // the kernel for any shape wins (64 -> 128 channels, 12 x 12, N = 512: 59 ->
+    // 35 us; 64 -> 96, 45 x 48, N = 96: 114 -> 56), as it does at strides above
+    // 1 and k = 3 (64 -> 64, 128 x 128: stride 2 171 -> 84, k = 3 223 -> 125)
     const int passes = hexk::bf16_wgrad32_passes(sh);
-    if (passes == 1 || (passes > 1 && !hexk::bf16_wgrad_ok(sh)))
+    if (passes == 1)
+        return WgradPath::Bf16Mfma32;
+    if (hexk::wgrad_any_ok(sh, d))
+        return WgradPath::Any;
+    if (passes > 1 && !hexk::bf16_wgrad_ok(sh))
         return WgradPath::Bf16Mfma32;
     if (hexk::bf16_wgrad_ok(sh))
         return WgradPath::Bf16Mfma;
@@ -359,12 +366,17 @@ int hexconv_fwd(const void *x, const void *w, const void *bias, void *y, int N, 
     if (!force_generic()) {
         if (hexk::smallc_fwd_ok(sh))
             return launched(hexk::smallc_fwd(x, w, bias, y, sh, d, relu, st));
-        if (d == hexk::BF16 && hexk::bf16_wide_ok(sh, sh.Ci, sh.Co))
+        // bf16: the tuned stride-1 kernels where they win, then the kernel for
+        // any shape; the others only where that one's window does not fit
+        const bool wide = d == hexk::BF16 && hexk::bf16_wide_ok(sh, sh.Ci, sh.Co);
+        if (wide && hexk::bf16_wide_first(sh, sh.Ci, sh.Co, false))
+            return launched(hexk::bf16_wide_conv(x, w, bias, y, sh, false, relu, st));
+        if (hexk::conv_any_ok(sh, d, false))
+            return launched(hexk::conv_any(x, w, bias, y, sh, d, false, relu, st));
+        if (wide)
             return launched(hexk::bf16_wide_conv(x, w, bias, y, sh, false, relu, st));
         if (d == hexk::BF16 && hexk::bf16_gen_fwd_ok(sh))
             return launched(hexk::bf16_gen_fwd(x, w, bias, y, sh, relu, st));
-        if (hexk::conv_any_ok(sh, d, false))
-            return launched(hexk::conv_any(x, w, bias, y, sh, d, false, relu, st));
     }
     if (!hexk::conv_fwd_generic_ok(sh))
         return HEX_ERR_UNSUPPORTED;
@@ -387,22 +399,24 @@ int hexconv_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in, i
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Dtype d = static_cast<Dtype>(dt);
     if (!force_generic() && sh.Ho > 0) {
-        // bf16 with 32 or more output channels: the matrix-core kernel
-        // before the small-channel one (1 -> 64 channels, 48x48, k = 2:
-        // 29 against 59 us)
-        if (d == hexk::BF16 && hexk::bf16_wide_ok(sh, sh.Co, sh.Ci))
+        // bf16 on the matrix cores first (64 images of 41 x 43, 4 -> 32
+        // channels, k = 1: 52 us on the small-channel kernel, whose fp32
+        // arithmetic runs on the vector units, 10 us here; 1 -> 8: 9.2 and
+        // 8.0), by the tuned kernels where they win
+        const bool wide = d == hexk::BF16 && hexk::bf16_wide_ok(sh, sh.Co, sh.Ci);
+        if (wide && hexk::bf16_wide_first(sh, sh.Co, sh.Ci, true))
             return launched(hexk::bf16_wide_conv(dy, w, nullptr, dx, sh, true, false, st));
-        // at fewer output channels too the bf16 matrix cores win (64 images
-        // of 41 x 43, 4 -> 32 channels, k = 1: 52 -> 10 us; 1 -> 8: 9.2 -> 8.0;
-        // the small-channel kernel's arithmetic is fp32 on the vector units)
-        if (d == hexk::BF16 && hexk::smallc_bwd_data_ok(sh) && hexk::conv_any_ok(sh, d, true))
+        const bool any = hexk::conv_any_ok(sh, d, true);
+        if (d == hexk::BF16 && any)
             return launched(hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st));
+        if (wide)
+            return launched(hexk::bf16_wide_conv(dy, w, nullptr, dx, sh, true, false, st));
         if (hexk::smallc_bwd_data_ok(sh))
             return launched(hexk::smallc_bwd_data(dy, w, dx, sh, d, st));
+        if (any)
+            return launched(hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st));
         if (d == hexk::BF16 && hexk::bf16_gen_dgrad_ok(sh))
             return launched(hexk::bf16_gen_dgrad(dy, w, dx, sh, st));
-        if (hexk::conv_any_ok(sh, d, true))
-            return launched(hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st));
     }
     if (!hexk::conv_bwd_data_generic_ok(sh))
         return HEX_ERR_UNSUPPORTED;

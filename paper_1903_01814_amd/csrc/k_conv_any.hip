@@ -31,9 +31,11 @@
 // channel and instruction; bfloat16 results go through LDS, one 32-channel
 // tile at a time, and leave as 16-byte vectors.
 #include <algorithm>
+#include <type_traits>
 
 #include "chanlast.h"
 #include "kernels.h"
+#include "shear.h" // FastDiv
 
 namespace hexk {
 namespace {
@@ -65,6 +67,7 @@ struct AnyArgs {
     int relu;
     int win_off;         // window (and bfloat16 result tile) after the weights
     int OP;              // result tile: bfloat16 per channel
+    FastDiv fper, ftiles; // by tiles per image (all planes) and per plane
     int toff[kMaxTaps];  // byte offset of each tap from its centre's slot
 };
 
@@ -85,28 +88,53 @@ __device__ __forceinline__ void stage_weights(unsigned char *__restrict__ wl,
 {
     constexpr int PX = AnyE<E>::PX;
     constexpr int WT = NB * 64 + 16;
-    for (int i = threadIdx.x; i < T * NB * 4; i += kAThreads) {
-        const int t = i % T, r = i / T;
-        const int o = r & 3, n = r >> 2;
-        const int c = c0 + o * PX, d = d0 + n;
-        const int j = a.reflect ? a.J - 1 - (z * T + t) : z * T + t;
-        E v[PX];
-        const bool dok = d < a.Cd;
-        const E *p = w + static_cast<size_t>(min(d, a.Cd - 1)) * a.sD + j;
+    constexpr int N = T * NB * 4; // 16-byte vectors
+    constexpr int UW = 4;
+    using I = std::conditional_t<sizeof(E) == 4, uint32_t, uint16_t>;
+    const I *wi = reinterpret_cast<const I *>(w);
+    // Loads without conditions (clamped, then masked), UW vectors at a time,
+    // all issued before the first is used: with a condition on each value
+    // the compiler made every one of the 2-byte loads a branch with its own
+    // wait, and a block spent tens of microseconds on its weights.
+    for (int i0 = threadIdx.x; i0 < N; i0 += UW * kAThreads) {
+        uint32_t v[UW][PX];
+        int at[UW], live[UW];
 #pragma unroll
-        for (int e = 0; e < PX; ++e) {
-            const E q = p[static_cast<size_t>(min(c + e, a.Cs - 1)) * a.sS];
-            v[e] = (dok && c + e < a.Cs) ? q : E(0);
+        for (int u = 0; u < UW; ++u) {
+            const int i = min(i0 + u * kAThreads, N - 1);
+            const int t = i % T, r = i / T;
+            const int o = r & 3, n = r >> 2;
+            const int c = c0 + o * PX, d = d0 + n;
+            const int j = a.reflect ? a.J - 1 - (z * T + t) : z * T + t;
+            const I *p = wi + static_cast<size_t>(min(d, a.Cd - 1)) * a.sD + j;
+            live[u] = d < a.Cd ? a.Cs - c : 0; // channels that exist
+            at[u] = t * WT + n * 64 + ((o ^ ((n >> 1) & 3)) << 4);
+#pragma unroll
+            for (int e = 0; e < PX; ++e)
+                v[u][e] = p[static_cast<size_t>(min(c + e, a.Cs - 1)) * a.sS];
         }
-        uint4 u;
-        __builtin_memcpy(&u, v, 16);
-        *reinterpret_cast<uint4 *>(wl + t * WT + n * 64 + ((o ^ ((n >> 1) & 3)) << 4)) = u;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < UW; ++u) {
+#pragma unroll
+            for (int e = 0; e < PX; ++e)
+                v[u][e] &= e < live[u] ? ~0u : 0u;
+            uint4 q;
+            if constexpr (PX == 4)
+                q = make_uint4(v[u][0], v[u][1], v[u][2], v[u][3]);
+            else
+                q = make_uint4(v[u][0] | (v[u][1] << 16), v[u][2] | (v[u][3] << 16),
+                               v[u][PX - 4] | (v[u][PX - 3] << 16),
+                               v[u][PX - 2] | (v[u][PX - 1] << 16));
+            if (i0 + u * kAThreads < N)
+                *reinterpret_cast<uint4 *>(wl + at[u]) = q;
+        }
     }
 }
 
 // HS: 32-byte halves of a chunk that are contracted (1 where every source
 // channel fits the first)
-template <typename E, int K, int NT, int MG, int U, int HS>
+template <typename E, int K, int NT, int MG, int U, int HS, bool MIS>
 __global__ __launch_bounds__(kAThreads) void conv_any_k(const E *x, // not restrict: the loads ahead stay where they are
                                                         const E *__restrict__ w,
                                                         const E *__restrict__ bias,
@@ -152,30 +180,29 @@ __global__ __launch_bounds__(kAThreads) void conv_any_k(const E *x, // not restr
         for (int q = 0; q < Q; ++q)
             stage_weights<E, T, NB>(smem + q * T * WT, w, a, d0, (q % a.nch) * CK, q / a.nch);
 
-    // Position: tile, chunk.  Chunks whose source plane lies outside are
-    // passed over; the centre plane never does.
+    // Position: tile, window plane, chunk of channels.  Planes outside the
+    // volume are passed over; the centre plane never is.
     struct Pos {
-        int tb, q;         // tile, chunk
-        int n, l, i0;      // image, destination plane, first row
-        int zs;            // source plane of the chunk
-        int first;         // first chunk of its tile
+        int tb, zi, cc; // tile, window plane, channel chunk
+        int n, l, i0;   // image, destination plane, first row
+        int first;      // first chunk of its tile
     };
     auto place = [&](Pos &p) {
-        const int per = a.Dd * a.tiles;
-        p.n = p.tb / per;
-        const int r = p.tb - p.n * per;
-        p.l = r / a.tiles;
+        const uint32_t per = static_cast<uint32_t>(a.Dd) * a.tiles;
+        p.n = static_cast<int>(fdiv(static_cast<uint32_t>(p.tb), a.fper));
+        const uint32_t r = p.tb - p.n * per;
+        p.l = static_cast<int>(fdiv(r, a.ftiles));
         p.i0 = (r - p.l * a.tiles) * a.TR;
     };
-    auto settle = [&](Pos &p) { // first chunk from p.q on with its plane inside
-        for (; p.q < Q; ++p.q) {
-            p.zs = a.sz * p.l + p.q / a.nch - a.kz;
-            if (p.zs >= 0 && p.zs < a.Ds)
+    auto settle = [&](Pos &p) { // first plane from p.zi on that exists
+        for (; p.zi < a.Z; ++p.zi) {
+            const int zs = a.sz * p.l + p.zi - a.kz;
+            if (zs >= 0 && zs < a.Ds)
                 return true;
         }
         return false;
     };
-    AnyItem<E> it[U];
+    AnyItem<E, MIS> it[U];
     auto span = [&](const Pos &p, int &lo, int &run) { // existing rows of the window
         const int r_lo = a.s * p.i0 - K;
         lo = max(0, -r_lo);
@@ -183,28 +210,36 @@ __global__ __launch_bounds__(kAThreads) void conv_any_k(const E *x, // not restr
         run = (hi - lo) * a.Ws;
         return hi;
     };
+    auto source = [&](const Pos &p, int lo) { // first pixel of the window's rows
+        const int c0 = p.cc * CK;
+        return x + (static_cast<size_t>(p.n) * a.Cs + c0) * cs_src +
+                       static_cast<size_t>(a.sz * p.l + p.zi - a.kz) * HWs +
+                       static_cast<size_t>(a.s * p.i0 - K + lo) * a.Ws;
+    };
     auto load = [&](const Pos &p) {
         int lo, run;
         span(p, lo, run);
-        const int c0 = (p.q % a.nch) * CK;
-        const E *src = x + (static_cast<size_t>(p.n) * a.Cs + c0) * cs_src +
-                       static_cast<size_t>(p.zs) * HWs +
-                       static_cast<size_t>(a.s * p.i0 - K + lo) * a.Ws;
+        const E *src = source(p, lo);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = threadIdx.x + u * kAThreads;
             const int f = min((i >> 2) * PX, run - PX);
-            it[u].load(src, cs_src, (i & 3) * PX, a.Cs - c0, f);
+            it[u].load(src, cs_src, (i & 3) * PX, a.Cs - p.cc * CK, f);
         }
     };
     auto commit = [&](const Pos &p) {
         int lo, run;
         const int hi = span(p, lo, run);
+        const int left = a.Cs - p.cc * CK; // source channels from this chunk on
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = threadIdx.x + u * kAThreads;
+            const int f = min((i >> 2) * PX, run - PX);
+            it[u].align(source(p, lo), cs_src, (i & 3) * PX, left, f);
+            if (left < CK)
+                it[u].drop((i & 3) * PX, left);
             if ((i >> 2) * PX < run)
-                it[u].template commit<kSB>(win, wg, lo, min((i >> 2) * PX, run - PX), i & 3);
+                it[u].template commit<kSB>(win, wg, lo, f, i & 3);
         }
         if (p.first)
             zero_border<kSB, 4, kAThreads>(win, wg, lo, hi);
@@ -221,12 +256,15 @@ __global__ __launch_bounds__(kAThreads) void conv_any_k(const E *x, // not restr
         // the chunk after this one, in this tile or the block's next
         Pos nxt = cur;
         nxt.first = 0;
-        ++nxt.q;
         bool more = true, last = false;
-        if (!settle(nxt)) {
-            last = true;
+        if (++nxt.cc == a.nch) {
+            nxt.cc = 0;
+            ++nxt.zi;
+            last = !settle(nxt);
+        }
+        if (last) {
             nxt.tb += tstep;
-            nxt.q = 0;
+            nxt.zi = 0;
             nxt.first = 1;
             more = nxt.tb < a.ntot;
             if (more) {
@@ -244,7 +282,7 @@ __global__ __launch_bounds__(kAThreads) void conv_any_k(const E *x, // not restr
         __syncthreads(); // the previous chunk's (or tile's) readers are done
         commit(cur);
         if (!a.resident)
-            stage_weights<E, T, NB>(smem, w, a, d0, (cur.q % a.nch) * CK, cur.q / a.nch);
+            stage_weights<E, T, NB>(smem, w, a, d0, cur.cc * CK, cur.zi);
         __syncthreads();
         if (more)
             load(nxt);
@@ -252,7 +290,7 @@ __global__ __launch_bounds__(kAThreads) void conv_any_k(const E *x, // not restr
         const int rows = min(a.TR, a.Hd - cur.i0);
         const int M = rows * a.Wd;
         if (wave * 32 < M) {
-            const unsigned char *wq = smem + (a.resident ? cur.q * T * WT : 0);
+            const unsigned char *wq = smem + (a.resident ? (cur.zi * a.nch + cur.cc) * T * WT : 0);
             F fa[2][MG], fb[2][NT];
             auto read = [&](int i, F(&ra)[MG], F(&rb)[NT]) {
                 const int t = i / HS, h = i % HS;
@@ -268,8 +306,11 @@ __global__ __launch_bounds__(kAThreads) void conv_any_k(const E *x, // not restr
             read(0, fa[0], fb[0]);
 #pragma unroll
             for (int i = 0; i < HS * T; ++i) {
+                // the next step's operands are requested before this step's
+                // products (left alone, the scheduler sinks them to their use)
                 if (i + 1 < HS * T)
                     read(i + 1, fa[(i + 1) & 1], fb[(i + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -284,6 +325,7 @@ __global__ __launch_bounds__(kAThreads) void conv_any_k(const E *x, // not restr
                                 fa[i & 1][m], fb[i & 1][j], acc[m][j], 0, 0, 0);
                         }
                     }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
 
@@ -362,6 +404,246 @@ __global__ __launch_bounds__(kAThreads) void conv_any_k(const E *x, // not restr
     }
 }
 
+// ------------------------------------------- data gradient at strides above 1
+// dx pixel p = (r, c) of axial class (a, b) = (c mod s, (r - floor(c/2)) mod s)
+// receives from the taps with dq = a, ds = b (mod s), and tap (dq, ds) reads
+// the output at the axial offset ((a - dq) / s, (b - ds) / s) from the pixel's
+// lattice cell: within a class a dense convolution of dy with a few taps.  A
+// block takes s TR rows of dx; each class holds TR pixels of every column
+// c = a (mod s), so the pixels of a class are the TR x ceil(W / s) elements
+// (u, Q) whatever the class.  The dy rows of the tile are staged once, every
+// channel of them (nch windows), and the classes take turns on them; weights
+// as in the forward (all taps for the block's life where they fit, else a
+// class's taps chunk by chunk).  Results leave straight from the accumulators
+// (32 pixels s apart per channel; the classes that fill the gaps follow within
+// the block, so the lines meet in its L2).  64 x 64 -> 64 channels, 128 x 128,
+// k = 1, stride 2, bfloat16, 134 MB of dx: 161 us with the pixels sorted
+// through LDS, 1020 us on the generic kernel (rows of odd length).
+constexpr int kMaxCls = 64; // strides up to 8
+
+struct DgsArgs {
+    int Cs, Cd;         // dy and dx channels
+    int Hs, Ws, Hd, Wd; // dy and dx planes
+    int s;
+    int sD, sS;         // weight elements between dx / dy channels
+    int TR, tiles;      // rows of each class per tile, tiles per image
+    int Qn;             // columns of a class
+    int rows, RP;       // window
+    int rlo, coff;      // first row offset of a tap, window column of dy column 0
+    int nch, nblk, ntot, resident;
+    int win_off, win_bytes; // first window, bytes per window
+    FastDiv ftiles;
+    int cstart[kMaxCls + 1];
+    int toff[kMaxTaps]; // by class: byte offset, odd column, tap
+    int todd[kMaxTaps];
+    int tap[kMaxTaps];
+};
+
+template <typename E, int K, int NT, int MG, bool MIS>
+__global__ __launch_bounds__(kAThreads) void conv_any_dgs_k(const E *dy, const E *__restrict__ w,
+                                                            E *__restrict__ dx, DgsArgs a)
+{
+    constexpr bool F32 = sizeof(E) == 4;
+    constexpr int PX = AnyE<E>::PX;
+    constexpr int CK = 64 / sizeof(E);
+    constexpr int T = num_taps(K);
+    constexpr int NB = 32 * NT;
+    constexpr int WT = NB * 64 + 16;
+    constexpr int U = 2;
+    using F = typename Frag<E>::T;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int tlist[kMaxTaps];
+
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n32 = lane & 31, kh = lane >> 5;
+    const int db = blockIdx.x % a.nblk, tstep = gridDim.x / a.nblk;
+    const int d0 = db * NB;
+    const int s = a.s;
+    const uint32_t HWs = static_cast<uint32_t>(a.Hs) * a.Ws;
+    const size_t HWd = static_cast<size_t>(a.Hd) * a.Wd;
+    const WinGeom wg{a.rows, a.RP, a.RP, 1, a.coff, a.Ws};
+    const int wb0 = n32 * 64 + (((0 + kh) ^ ((n32 >> 1) & 3)) << 4);
+    const int wb1 = n32 * 64 + (((2 + kh) ^ ((n32 >> 1) & 3)) << 4);
+    if (threadIdx.x < T)
+        tlist[threadIdx.x] = a.tap[threadIdx.x];
+    __syncthreads();
+
+    // weights of the taps k0 .. k0 + nt - 1 (in class order) and chunk q
+    auto stage_w = [&](unsigned char *wl, int k0, int nt, int q) {
+        using I = std::conditional_t<F32, uint32_t, uint16_t>;
+        const I *wi = reinterpret_cast<const I *>(w);
+        constexpr int UW = 2;
+        const int n_items = nt * NB * 4;
+        for (int i0 = threadIdx.x; i0 < n_items; i0 += UW * kAThreads) {
+            uint32_t v[UW][PX];
+            int at[UW], live[UW];
+#pragma unroll
+            for (int u = 0; u < UW; ++u) {
+                const int i = min(i0 + u * kAThreads, n_items - 1);
+                const int t = i % nt, r = i / nt;
+                const int o = r & 3, n = r >> 2;
+                const int c = q * CK + o * PX, d = d0 + n;
+                const I *p = wi + static_cast<size_t>(min(d, a.Cd - 1)) * a.sD + tlist[k0 + t];
+                live[u] = d < a.Cd ? a.Cs - c : 0;
+                at[u] = t * WT + n * 64 + ((o ^ ((n >> 1) & 3)) << 4);
+#pragma unroll
+                for (int e = 0; e < PX; ++e)
+                    v[u][e] = p[static_cast<size_t>(min(c + e, a.Cs - 1)) * a.sS];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < UW; ++u) {
+#pragma unroll
+                for (int e = 0; e < PX; ++e)
+                    v[u][e] &= e < live[u] ? ~0u : 0u;
+                uint4 q4;
+                if constexpr (PX == 4)
+                    q4 = make_uint4(v[u][0], v[u][1], v[u][2], v[u][3]);
+                else
+                    q4 = make_uint4(v[u][0] | (v[u][1] << 16), v[u][2] | (v[u][3] << 16),
+                                    v[u][PX - 4] | (v[u][PX - 3] << 16),
+                                    v[u][PX - 2] | (v[u][PX - 1] << 16));
+                if (i0 + u * kAThreads < n_items)
+                    *reinterpret_cast<uint4 *>(wl + at[u]) = q4;
+            }
+        }
+    };
+    if (a.resident)
+        for (int q = 0; q < a.nch; ++q)
+            stage_w(smem + q * T * WT, 0, T, q);
+
+    for (int tb = blockIdx.x / a.nblk; tb < a.ntot; tb += tstep) {
+        const int n = static_cast<int>(fdiv(static_cast<uint32_t>(tb), a.ftiles));
+        const int i0 = (tb - n * a.tiles) * a.TR; // r0 = s i0
+        // window row 0 is dy row i0 - 1 + rlo
+        const int r_lo = i0 - 1 + a.rlo;
+        const int lo = min(a.rows, max(0, -r_lo));
+        const int hi = max(lo, min(a.rows, a.Hs - r_lo));
+        const int run = (hi - lo) * a.Ws;
+        __syncthreads(); // the previous tile's readers are done
+        for (int q = 0; q < a.nch; ++q) {
+            unsigned char *win = smem + a.win_off + q * a.win_bytes;
+            if (run > 0) {
+                const int left = a.Cs - q * CK;
+                const E *src = dy + (static_cast<size_t>(n) * a.Cs + q * CK) * HWs +
+                               static_cast<size_t>(r_lo + lo) * a.Ws;
+                AnyItem<E, MIS> it[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = threadIdx.x + u * kAThreads;
+                    it[u].load(src, HWs, (i & 3) * PX, left, min((i >> 2) * PX, run - PX));
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = threadIdx.x + u * kAThreads;
+                    const int f = min((i >> 2) * PX, run - PX);
+                    it[u].align(src, HWs, (i & 3) * PX, left, f);
+                    if (left < CK)
+                        it[u].drop((i & 3) * PX, left);
+                    if ((i >> 2) * PX < run)
+                        it[u].template commit<kSB>(win, wg, lo, f, i & 3);
+                }
+            }
+            zero_border<kSB, 4, kAThreads>(win, wg, lo, hi);
+        }
+        __syncthreads();
+
+        const int M = a.TR * a.Qn;
+        for (int cl = 0; cl < s * s; ++cl) {
+            const int ca = cl / s, cb = cl - ca * s;
+            const int k0 = a.cstart[cl], nt = a.cstart[cl + 1] - k0;
+            int be[MG], bo[MG], at[MG];
+#pragma unroll
+            for (int m = 0; m < MG; ++m) {
+                const int e = min((wave + kAWaves * m) * 32 + n32, M - 1);
+                const int u = e / a.Qn, Q = e - u * a.Qn;
+                const int c = ca + s * Q, h = c >> 1;
+                const int rr = (cb + h) % s + s * u;             // row of the tile
+                const int i = (rr - cb - (h - s * (Q >> 1))) / s; // exact; its cell's row - i0
+                be[m] = ((i + 1 - a.rlo) * a.RP + Q + a.coff) * kSB + 16 * kh;
+                bo[m] = be[m] + ((Q & 1) ? a.RP * kSB : 0);
+                const int r = s * i0 + rr;
+                at[m] = (wave + kAWaves * m) * 32 + n32 < M && r < a.Hd && c < a.Wd
+                            ? r * a.Wd + c
+                            : -1;
+            }
+            floatx16 acc[MG][NT];
+#pragma unroll
+            for (int m = 0; m < MG; ++m)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    acc[m][j] = floatx16{};
+            for (int q = 0; q < a.nch; ++q) {
+                if (!a.resident) {
+                    __syncthreads();
+                    stage_w(smem, k0, nt, q);
+                    __syncthreads();
+                }
+                const unsigned char *wq = smem + (a.resident ? (q * T + k0) * WT : 0);
+                const unsigned char *win = smem + a.win_off + q * a.win_bytes;
+                if (wave * 32 >= M)
+                    continue;
+                F fa[2][MG], fb[2][NT];
+                auto read = [&](int t, int h) {
+#pragma unroll
+                    for (int m = 0; m < MG; ++m)
+                        fa[h][m] = *reinterpret_cast<const F *>(
+                            win + (a.todd[k0 + t] ? bo[m] : be[m]) + a.toff[k0 + t] + 32 * h);
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+                        fb[h][j] = *reinterpret_cast<const F *>(wq + (h ? wb1 : wb0) + t * WT +
+                                                                j * 32 * 64);
+                };
+                auto mul = [&](int h) {
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+#pragma unroll
+                        for (int m = 0; m < MG; ++m) {
+                            if constexpr (F32) {
+#pragma unroll
+                                for (int e = 0; e < 4; ++e)
+                                    acc[m][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                                        fb[h][j][e], fa[h][m][e], acc[m][j], 0, 0, 0);
+                            } else {
+                                acc[m][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                    fb[h][j], fa[h][m], acc[m][j], 0, 0, 0);
+                            }
+                        }
+                };
+                if (nt > 0)
+                    read(0, 0);
+                for (int t = 0; t < nt; ++t) {
+                    read(t, 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mul(0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (t + 1 < nt)
+                        read(t + 1, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mul(1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            // row r of D: channel 8 (r / 4) + 4 kh + r % 4; column: pixel
+            const int nd = min(NB, a.Cd - d0);
+            E *xb = dx + (static_cast<size_t>(n) * a.Cd + d0) * HWd;
+#pragma unroll
+            for (int m = 0; m < MG; ++m) {
+                if (at[m] < 0)
+                    continue;
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int d = j * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
+                        if (d < nd)
+                            xb[d * HWd + at[m]] = from_f<E>(acc[m][j][r]);
+                    }
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------------- host
 
 constexpr size_t kAnyLds = 160 * 1024;
@@ -405,42 +687,49 @@ bool plan_tile(const ConvShape &sh, Dtype d, bool dgrad, int NT, int MG, AnyPlan
     const int maxM = 32 * kAWaves * MG;
     if (a.Wd > maxM)
         return false;
-    a.TR = std::min(maxM / a.Wd, a.Hd);
-    a.tiles = (a.Hd + a.TR - 1) / a.TR;
-    a.TR = (a.Hd + a.tiles - 1) / a.tiles;
     a.nch = (a.Cs + CK - 1) / CK;
     a.nblk = (a.Cd + NB - 1) / NB;
+    const int cols = a.Ws + 2 * K;
+    const int Q = a.Z * a.nch;
+    const size_t wchunk = static_cast<size_t>(T) * WT;
+    int items = 0, M = 0;
+    bool ok = false;
+    for (int TR = std::min(maxM / a.Wd, a.Hd); TR >= 1 && !ok; --TR) {
+        a.tiles = (a.Hd + TR - 1) / TR;
+        a.TR = (a.Hd + a.tiles - 1) / a.tiles;
+        M = a.TR * a.Wd;
+        a.OP = ((M + 31) & ~31) + 4;
+        a.rows = a.s * (a.TR - 1) + (a.Wd > 1 ? a.s / 2 : 0) + 2 * K + 1;
+        items = 4 * ((std::min(a.rows, a.Hs) * a.Ws + PX - 1) / PX);
+        pl.U = (items + kAThreads - 1) / kAThreads;
+        // three tiles of channels leave no registers for two items of two groups
+        if (pl.U > (NT == 3 && MG == 2 ? 1 : 2))
+            continue;
+        const size_t outb = d == F32 ? 0 : static_cast<size_t>(32) * a.OP * 2;
+        // weights resident, else streamed; window rows of a multiple of 8
+        // slots per class of columns (odd tap columns at odd centres then
+        // keep the banks' phase), else unpadded
+        for (int pass = 0; pass < 4 && !ok; ++pass) {
+            a.resident = pass < 2;
+            const int per = (cols + a.s - 1) / a.s;
+            a.WCs = (pass & 1) ? per : (per + 7) & ~7;
+            a.RP = a.s * a.WCs;
+            const size_t winb = static_cast<size_t>(a.rows) * a.RP * kSB;
+            size_t wts = a.resident ? wchunk * Q : wchunk;
+            wts = (wts + 255) & ~static_cast<size_t>(255);
+            pl.lds = wts + std::max(winb, outb);
+            a.win_off = static_cast<int>(wts);
+            ok = pl.lds <= kAnyLds;
+        }
+    }
+    if (!ok)
+        return false;
     const long ntot = static_cast<long>(sh.N) * a.Dd * a.tiles;
     if (ntot > (1L << 30))
         return false;
     a.ntot = static_cast<int>(ntot);
-    const int M = a.TR * a.Wd;
-    a.OP = ((M + 31) & ~31) + 4;
-    a.rows = a.s * (a.TR - 1) + (a.Wd > 1 ? a.s / 2 : 0) + 2 * K + 1;
-    const int cols = a.Ws + 2 * K; // one class of columns: rows of a multiple of 8 slots where it fits
-    const int items = 4 * ((std::min(a.rows, a.Hs) * a.Ws + PX - 1) / PX);
-    pl.U = (items + kAThreads - 1) / kAThreads;
-    if (pl.U > 2)
-        return false;
-    const int Q = a.Z * a.nch;
-    const size_t wchunk = static_cast<size_t>(T) * WT;
-    const size_t outb = d == F32 ? 0 : static_cast<size_t>(32) * a.OP * 2;
-    bool ok = false;
-    for (int pass = 0; pass < 4 && !ok; ++pass) { // resident padded, unpadded, then streamed
-        a.resident = pass < 2;
-        const int per = (cols + a.s - 1) / a.s;
-        a.WCs = (pass & 1) ? per : (per + 7) & ~7;
-        a.RP = a.s * a.WCs;
-        // the padded columns of the last slots are reached by no tap, only staged as zeros
-        const size_t winb = (static_cast<size_t>(a.rows) * a.RP * kSB + 15) & ~static_cast<size_t>(15);
-        size_t wts = a.resident ? wchunk * Q : wchunk;
-        wts = (wts + 255) & ~static_cast<size_t>(255);
-        pl.lds = wts + std::max(winb, outb);
-        a.win_off = static_cast<int>(wts);
-        ok = pl.lds <= kAnyLds;
-    }
-    if (!ok)
-        return false;
+    a.fper = make_fastdiv(static_cast<uint32_t>(a.Dd) * a.tiles);
+    a.ftiles = make_fastdiv(static_cast<uint32_t>(a.tiles));
     int t = 0;
     for (int dq = -K; dq <= K; ++dq)
         for (int i = 0; i < col_len(K, dq); ++i, ++t) {
@@ -474,7 +763,7 @@ bool plan_any(const ConvShape &sh, Dtype d, bool dgrad, AnyPlan &best)
     if (dgrad && (sh.s != 1 || sh.sz != 1))
         return false;
     // a run of rows has to hold one whole item
-    if (sh.W < 8 || sh.Wo < 8 || sh.Ho < 1)
+    if (sh.W < (d == F32 ? 4 : 8) || sh.Ho < 1)
         return false;
     bool found = false;
     for (int NT = 1; NT <= 3; ++NT)
@@ -492,11 +781,11 @@ bool plan_any(const ConvShape &sh, Dtype d, bool dgrad, AnyPlan &best)
     return found;
 }
 
-template <typename E, int K, int NT, int MG, int U, int HS>
+template <typename E, int K, int NT, int MG, int U, int HS, bool MIS>
 hipError_t launch_h(const AnyPlan &pl, const void *x, const void *w, const void *b, void *y,
                   hipStream_t st)
 {
-    HEX_LAUNCH((conv_any_k<E, K, NT, MG, U, HS>), dim3(pl.grid), dim3(kAThreads), pl.lds, st,
+    HEX_LAUNCH((conv_any_k<E, K, NT, MG, U, HS, MIS>), dim3(pl.grid), dim3(kAThreads), pl.lds, st,
                static_cast<const E *>(x), static_cast<const E *>(w), static_cast<const E *>(b),
                static_cast<E *>(y), pl.a);
     return hipGetLastError();
@@ -506,8 +795,12 @@ template <typename E, int K, int NT, int MG, int U>
 hipError_t launch(const AnyPlan &pl, const void *x, const void *w, const void *b, void *y,
                   hipStream_t st)
 {
-    return pl.HS == 1 ? launch_h<E, K, NT, MG, U, 1>(pl, x, w, b, y, st)
-                      : launch_h<E, K, NT, MG, U, 2>(pl, x, w, b, y, st);
+    if constexpr (sizeof(E) == 2)
+        if (pl.a.Ws & 1) // some runs start at an odd element
+            return pl.HS == 1 ? launch_h<E, K, NT, MG, U, 1, true>(pl, x, w, b, y, st)
+                              : launch_h<E, K, NT, MG, U, 2, true>(pl, x, w, b, y, st);
+    return pl.HS == 1 ? launch_h<E, K, NT, MG, U, 1, false>(pl, x, w, b, y, st)
+                      : launch_h<E, K, NT, MG, U, 2, false>(pl, x, w, b, y, st);
 }
 
 template <typename E, int K, int NT>
@@ -517,7 +810,9 @@ hipError_t dispatch_m(const AnyPlan &pl, const void *x, const void *w, const voi
     if (pl.MG == 1 || (sizeof(E) == 4 && NT == 3))
         return pl.U == 1 ? launch<E, K, NT, 1, 1>(pl, x, w, b, y, st)
                          : launch<E, K, NT, 1, 2>(pl, x, w, b, y, st);
-    if constexpr (sizeof(E) == 2 || NT < 3)
+    if constexpr (sizeof(E) == 2 && NT == 3)
+        return launch<E, K, NT, 2, 1>(pl, x, w, b, y, st);
+    else if constexpr (NT < 3)
         return pl.U == 1 ? launch<E, K, NT, 2, 1>(pl, x, w, b, y, st)
                          : launch<E, K, NT, 2, 2>(pl, x, w, b, y, st);
     return hipErrorInvalidValue;
@@ -551,6 +846,142 @@ hipError_t dispatch_k(const AnyPlan &pl, int k, const void *x, const void *w, co
     }
 }
 
+struct DgsPlan {
+    DgsArgs a;
+    int NT, MG, grid;
+    size_t lds;
+};
+
+bool plan_dgs(const ConvShape &sh, Dtype d, DgsPlan &best)
+{
+    if (sh.k < 1 || sh.k > 3 || sh.s < 2 || sh.s * sh.s > kMaxCls || sh.Z != 1 || sh.D != 1 ||
+        sh.Wo < (d == F32 ? 4 : 8) || sh.Ho < 1)
+        return false;
+    const int es = d == F32 ? 4 : 2, PX = 16 / es, CK = 64 / es;
+    const int K = sh.k, T = sh.T, s = sh.s;
+    DgsArgs a{};
+    a.Cs = sh.Co;
+    a.Cd = sh.Ci;
+    a.Hs = sh.Ho;
+    a.Ws = sh.Wo;
+    a.Hd = sh.H;
+    a.Wd = sh.W;
+    a.s = s;
+    a.sD = T;
+    a.sS = sh.Ci * T;
+    a.nch = (a.Cs + CK - 1) / CK;
+    a.Qn = (sh.W + s - 1) / s;
+    if (static_cast<long>(sh.Ho) * sh.Wo * CK * es >= kAnyMaxSpan ||
+        static_cast<long>(sh.H) * sh.W >= (1L << 30))
+        return false;
+    // taps by class, with their offsets on the output lattice
+    int oq[kMaxTaps], os[kMaxTaps], rlo = 0, rhi = 0, clo = 0, chi = 0, n = 0, most = 0;
+    for (int cl = 0; cl < s * s; ++cl) {
+        a.cstart[cl] = n;
+        for (int t = 0; t < T; ++t) {
+            int dq = 0, ds = 0;
+            tap_axial(K, t, dq, ds);
+            const int ra = ((dq % s) + s) % s, rb = ((ds % s) + s) % s;
+            if (ra * s + rb != cl)
+                continue;
+            oq[n] = (ra - dq) / s;
+            os[n] = (rb - ds) / s;
+            a.tap[n] = t;
+            a.todd[n] = oq[n] & 1;
+            for (int par = 0; par < 2; ++par) {
+                const int row = tap_drow(oq[n], os[n], par);
+                rlo = std::min(rlo, row);
+                rhi = std::max(rhi, row);
+            }
+            clo = std::min(clo, oq[n]);
+            chi = std::max(chi, oq[n]);
+            ++n;
+        }
+        most = std::max(most, n - a.cstart[cl]);
+    }
+    a.cstart[s * s] = n;
+    a.rlo = rlo;
+    a.coff = -clo;
+    // columns of the window: cells reach column Qn - 1, taps chi beyond
+    const int cols = a.coff + std::max(a.Ws, a.Qn + chi);
+    const int cus = device_cus();
+    double cost = 0;
+    bool found = false;
+    for (int NT = 1; NT <= 2; ++NT)
+        for (int MG = 1; MG <= 2; ++MG)
+            for (int resident = 1; resident >= 0; --resident) {
+                DgsArgs c = a;
+                const int NB = 32 * NT, WT = NB * 64 + 16;
+                const int maxM = 32 * kAWaves * MG;
+                if (c.Qn > maxM)
+                    continue;
+                const int all = (sh.H + s - 1) / s; // rows of each class in a plane
+                c.resident = resident;
+                c.nblk = (c.Cd + NB - 1) / NB;
+                const size_t wts = (static_cast<size_t>(resident ? T * c.nch : most) * WT + 255) &
+                                   ~static_cast<size_t>(255);
+                size_t lds = 0;
+                bool ok = false;
+                for (int TR = std::min(maxM / c.Qn, all); TR >= 1 && !ok; --TR) {
+                    c.tiles = (all + TR - 1) / TR;
+                    c.TR = (all + c.tiles - 1) / c.tiles;
+                    c.rows = c.TR + 1 + rhi - rlo;
+                    c.RP = (cols + 7) & ~7;
+                    c.win_bytes = c.rows * c.RP * kSB;
+                    lds = wts + static_cast<size_t>(c.win_bytes) * c.nch;
+                    const int items = 4 * ((std::min(c.rows, c.Hs) * c.Ws + PX - 1) / PX);
+                    ok = lds <= kAnyLds - 256 && items <= 2 * kAThreads;
+                }
+                const long ntot = static_cast<long>(sh.N) * c.tiles;
+                if (!ok || ntot > (1L << 30))
+                    continue;
+                c.win_off = static_cast<int>(wts);
+                c.ntot = static_cast<int>(ntot);
+                c.ftiles = make_fastdiv(static_cast<uint32_t>(c.tiles));
+                const int blocks = std::min(c.ntot, std::max(1, cus / c.nblk));
+                const int rounds = (c.ntot + blocks - 1) / blocks;
+                const double M = static_cast<double>(c.TR) * c.Qn;
+                const double mf = c.nch * 2.0 * T * 2 * MG * NT * (d == F32 ? 256 : 32);
+                const double st = c.nch * 1600.0 + s * s * M * NB / 64 * 12 +
+                                  (resident ? 0 : c.nch * (s * s * 2500.0 + T * NB * 8.0));
+                const double v =
+                    rounds * (mf + st) + (resident ? c.nch * T * NB * 8.0 : 0.0);
+                if (!found || v < cost) {
+                    for (int i = 0; i < T; ++i)
+                        c.toff[i] = ((os[i] + floor_half(oq[i])) * c.RP + oq[i]) * kSB;
+                    best = DgsPlan{c, NT, MG, blocks * c.nblk, lds};
+                    cost = v;
+                    found = true;
+                }
+            }
+    return found;
+}
+
+template <typename E, int K, int NT, int MG>
+hipError_t launch_dgs(const DgsPlan &pl, const void *dy, const void *w, void *dx, hipStream_t st)
+{
+    const E *g = static_cast<const E *>(dy), *we = static_cast<const E *>(w);
+    if constexpr (sizeof(E) == 2)
+        if (pl.a.Ws & 1) {
+            HEX_LAUNCH((conv_any_dgs_k<E, K, NT, MG, true>), dim3(pl.grid), dim3(kAThreads),
+                       pl.lds, st, g, we, static_cast<E *>(dx), pl.a);
+            return hipGetLastError();
+        }
+    HEX_LAUNCH((conv_any_dgs_k<E, K, NT, MG, false>), dim3(pl.grid), dim3(kAThreads), pl.lds, st, g,
+               we, static_cast<E *>(dx), pl.a);
+    return hipGetLastError();
+}
+
+template <typename E, int K>
+hipError_t dispatch_dgs(const DgsPlan &pl, const void *dy, const void *w, void *dx, hipStream_t st)
+{
+    if (pl.NT == 1)
+        return pl.MG == 1 ? launch_dgs<E, K, 1, 1>(pl, dy, w, dx, st)
+                          : launch_dgs<E, K, 1, 2>(pl, dy, w, dx, st);
+    return pl.MG == 1 ? launch_dgs<E, K, 2, 1>(pl, dy, w, dx, st)
+                      : launch_dgs<E, K, 2, 2>(pl, dy, w, dx, st);
+}
+
 } // namespace
 
 bool conv_any_ok(const ConvShape &sh, Dtype d, bool dgrad)
@@ -564,6 +995,10 @@ bool conv_any_ok(const ConvShape &sh, Dtype d, bool dgrad)
     const int Cs = dgrad ? sh.Co : sh.Ci;
     if (Cs < (d == F32 ? 3 : 2))
         return false;
+    if (dgrad && sh.s > 1) {
+        DgsPlan pl;
+        return plan_dgs(sh, d, pl);
+    }
     AnyPlan pl;
     return plan_any(sh, d, dgrad, pl);
 }
@@ -571,6 +1006,18 @@ bool conv_any_ok(const ConvShape &sh, Dtype d, bool dgrad)
 hipError_t conv_any(const void *in, const void *w, const void *bias, void *out,
                     const ConvShape &sh, Dtype d, bool dgrad, bool relu, hipStream_t st)
 {
+    if (dgrad && sh.s > 1) {
+        DgsPlan dp;
+        if (!plan_dgs(sh, d, dp))
+            return hipErrorInvalidValue;
+        auto go = [&](auto *p) {
+            using E = std::remove_pointer_t<decltype(p)>;
+            return sh.k == 1   ? dispatch_dgs<E, 1>(dp, in, w, out, st)
+                   : sh.k == 2 ? dispatch_dgs<E, 2>(dp, in, w, out, st)
+                               : dispatch_dgs<E, 3>(dp, in, w, out, st);
+        };
+        return d == F32 ? go(static_cast<float *>(nullptr)) : go(static_cast<bf16raw *>(nullptr));
+    }
     AnyPlan pl;
     if (!plan_any(sh, d, dgrad, pl))
         return hipErrorInvalidValue;

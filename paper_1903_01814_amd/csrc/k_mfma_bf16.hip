@@ -1413,6 +1413,29 @@ bool bf16_wide_ok(const ConvShape &sh, int IC, int OC)
     return plan_wide(sh, IC, OC).ok;
 }
 
+// Whether these kernels go before the one for any shape (k_conv_any.hip).
+// Pipelined rows do (64 -> 64 channels, 128 x 128, N = 64: 67 / 77 us forward /
+// data gradient; 128 x 127 there 122). The 32x32 kernel does on small planes,
+// whose tiles of whole rows leave a block there idle (us here against there:
+// 32 -> 64 channels, 24 x 24, k = 2, N = 512 43 / 53 against 53 / 57; 64 ->
+// 128, 12 x 12, k = 1 31 / 32 against 38 / 42), and in the forward of up to 64
+// channels out (64 x 64 planes, 64 -> 64, N = 32: 20.4 against 20.7; but 64 ->
+// 96, 45 x 48, N = 96 51 against 42); not in the data gradient of larger planes
+// (30 against 23; 77 against 44). The 16x16 kernel does nowhere (96 -> 96,
+// 64 x 64, N = 24: 55 against 34).
+bool bf16_wide_first(const ConvShape &sh, int IC, int OC, bool reflect)
+{
+    PipeArgs pa{};
+    size_t lds = 0;
+    int grid = 0;
+    if (pipe_plan(sh, IC, OC, pa, lds, grid))
+        return true;
+    const WidePlan pl = plan_wide(sh, IC, OC);
+    if (!pl.ok || !pl.cfg.E32)
+        return false;
+    return sh.H * sh.W < 1024 || (!reflect && OC <= 64);
+}
+
 hipError_t bf16_wide_conv(const void *in, const void *w, const void *bias, void *out,
                           const ConvShape &sh, bool reflect, bool relu, hipStream_t st)
 {

@@ -86,7 +86,7 @@ __device__ __forceinline__ bf16x8 tr_read(unsigned char *a0, unsigned char *a1)
 // NCO: 32-channel tiles of output channels (1 or 2); A: of input channels
 // U: items of x and of dy per thread.  PF: the next tile's items are loaded
 // during the products (where the registers hold them beside the sums).
-template <typename E, int K, int NCO, int A, int U, bool PF>
+template <typename E, int K, int NCO, int A, int U, bool PF, bool MIS>
 __global__ __launch_bounds__(kWThreads) void wgrad_any_k(const E *x, const E *dy,
                                                          float *__restrict__ part, WAnyArgs a)
 {
@@ -145,27 +145,30 @@ __global__ __launch_bounds__(kWThreads) void wgrad_any_k(const E *x, const E *dy
         run = (hi - lo) * a.W;
         return hi;
     };
-    AnyItem<E> ix[U], id[U];
+    AnyItem<E, MIS> ix[U], id[U];
+    auto x_src = [&](const Pos &p, int lo) { // first pixel of the window's rows
+        return x + (static_cast<size_t>(p.n) * a.Ci + ci0) * csx + static_cast<size_t>(p.zs) * HWx +
+               static_cast<size_t>(a.s * p.i0 - K + lo) * a.W;
+    };
+    auto dy_src = [&](const Pos &p) {
+        return dy + (static_cast<size_t>(p.n) * a.Co + co0) * csy +
+               static_cast<size_t>(p.l) * HWy + static_cast<size_t>(p.i0) * a.Wo;
+    };
     auto load_x = [&](const Pos &p) {
         int lo, run;
         span(p, lo, run);
-        const E *xs = x + (static_cast<size_t>(p.n) * a.Ci + ci0) * csx +
-                      static_cast<size_t>(p.zs) * HWx +
-                      static_cast<size_t>(a.s * p.i0 - K + lo) * a.W;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = threadIdx.x + u * kWThreads;
-            ix[u].load(xs, csx, (i % XG) * PX, a.Ci - ci0, min((i / XG) * PX, run - PX));
+            ix[u].load(x_src(p, lo), csx, (i % XG) * PX, a.Ci - ci0, min((i / XG) * PX, run - PX));
         }
     };
     auto load_dy = [&](const Pos &p) {
-        const E *ds = dy + (static_cast<size_t>(p.n) * a.Co + co0) * csy +
-                      static_cast<size_t>(p.l) * HWy + static_cast<size_t>(p.i0) * a.Wo;
         const int M = min(a.TR, a.Ho - p.i0) * a.Wo;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = threadIdx.x + u * kWThreads;
-            id[u].load(ds, csy, (i % DG) * PX, a.Co - co0, min((i / DG) * PX, M - PX));
+            id[u].load(dy_src(p), csy, (i % DG) * PX, a.Co - co0, min((i / DG) * PX, M - PX));
         }
     };
     auto commit_x = [&](const Pos &p) {
@@ -174,8 +177,12 @@ __global__ __launch_bounds__(kWThreads) void wgrad_any_k(const E *x, const E *dy
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = threadIdx.x + u * kWThreads;
+            const int f = min((i / XG) * PX, run - PX);
+            ix[u].align(x_src(p, lo), csx, (i % XG) * PX, a.Ci - ci0, f);
+            if (a.Ci - ci0 < 32 * A)
+                ix[u].drop((i % XG) * PX, a.Ci - ci0);
             if ((i / XG) * PX < run)
-                ix[u].template commit<XB>(win, wg, lo, min((i / XG) * PX, run - PX), i % XG);
+                ix[u].template commit<XB>(win, wg, lo, f, i % XG);
         }
         zero_border<XB, XG, kWThreads>(win, wg, lo, hi);
     };
@@ -184,8 +191,12 @@ __global__ __launch_bounds__(kWThreads) void wgrad_any_k(const E *x, const E *dy
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = threadIdx.x + u * kWThreads;
+            const int f = min((i / DG) * PX, M - PX);
+            id[u].align(dy_src(p), csy, (i % DG) * PX, a.Co - co0, f);
+            if (a.Co - co0 < 32 * NCO)
+                id[u].drop((i % DG) * PX, a.Co - co0);
             if ((i / DG) * PX < M)
-                id[u].template commit_flat<DB>(dyl, min((i / DG) * PX, M - PX), i % DG);
+                id[u].template commit_flat<DB>(dyl, f, i % DG);
         }
         // the slots past the last pixel, up to a whole step
         const int Mp = (M + 15) & ~15;
@@ -500,7 +511,7 @@ bool plan_tile(const ConvShape &sh, Dtype d, int A, int U, WAnyPlan &pl)
 
 bool plan_wgrad(const ConvShape &sh, Dtype d, WAnyPlan &pl)
 {
-    if (sh.k < 1 || sh.k > 3 || sh.W < 8 || sh.Wo < 8 || sh.Ho < 1)
+    if (sh.k < 1 || sh.k > 3 || sh.Wo < (d == F32 ? 4 : 8) || sh.Ho < 1)
         return false;
     // two input-channel tiles share the dy tile (at k = 3 the taps take
     // every wave); bfloat16 with one item per thread where that holds a tile
@@ -536,17 +547,25 @@ hipError_t launch_u(const WAnyPlan &pl, const void *x, const void *dy, float *pa
     // the next tile's items fit beside the sums except at 160 sums per lane
     // (k > 1, two tiles of output channels) and at 128 registers of items
     constexpr bool sums = K == 1 || NCO == 1;
+#define HEX_WA(UV, PFV, MISV)                                                                \
+    HEX_LAUNCH((wgrad_any_k<E, K, NCO, A, UV, PFV, MISV>), grid, block, pl.lds, st, xe, de,  \
+               part, pl.a)
     if constexpr (sizeof(E) == 4) {
-        HEX_LAUNCH((wgrad_any_k<E, K, NCO, A, 2, sums>), grid, block, pl.lds, st, xe, de, part,
-                   pl.a);
+        HEX_WA(2, sums, false);
     } else {
-        if (pl.U == 1)
-            HEX_LAUNCH((wgrad_any_k<E, K, NCO, A, 1, sums>), grid, block, pl.lds, st, xe, de,
-                       part, pl.a);
-        else
-            HEX_LAUNCH((wgrad_any_k<E, K, NCO, A, 2, false>), grid, block, pl.lds, st, xe, de,
-                       part, pl.a);
+        const bool mis = ((pl.a.W | pl.a.Wo) & 1) != 0; // some runs start at an odd element
+        if (pl.U == 1) {
+            if (mis)
+                HEX_WA(1, NCO == 1, true);
+            else
+                HEX_WA(1, sums, false);
+        } else if (mis) {
+            HEX_WA(2, false, true);
+        } else {
+            HEX_WA(2, false, false);
+        }
     }
+#undef HEX_WA
     return hipGetLastError();
 }
 

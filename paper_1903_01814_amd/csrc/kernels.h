@@ -151,6 +151,8 @@ hipError_t smallc_bwd_fused(const void *x, const void *dy, const void *w, void *
 // forward (reflect = false: IC = C_in, OC = C_out) or stride-1 data
 // gradient (reflect = true: IC = C_out, OC = C_in)
 bool bf16_wide_ok(const ConvShape &sh, int IC, int OC);
+// (bf16_wide_ok shapes) before the kernel for any shape?
+bool bf16_wide_first(const ConvShape &sh, int IC, int OC, bool reflect);
 hipError_t bf16_wide_conv(const void *in, const void *w, const void *bias, void *out,
                           const ConvShape &sh, bool reflect, bool relu, hipStream_t st);
 
@@ -180,7 +182,7 @@ hipError_t bf16_wgrad(const void *x, const void *dy, float *dw, float *db, void 
 
 // ---- matrix-core kernels for planes of any size and any channel count, k 1
 // to 3, bf16 and fp32, 2-D and 3-D (k_conv_any.hip, k_wgrad_any.hip) --------
-// forward, or (dgrad) the data gradient at in-plane and plane stride 1
+// forward, or (dgrad) the data gradient: 2-D at any stride, 3-D at stride 1
 bool conv_any_ok(const ConvShape &sh, Dtype d, bool dgrad);
 hipError_t conv_any(const void *in, const void *w, const void *bias, void *out,
                     const ConvShape &sh, Dtype d, bool dgrad, bool relu, hipStream_t st);

@@ -26,6 +26,12 @@ CASES = [
     (40, 12, 12, 20, 21, 1, 1),    # more tiles than a block's run
     (2, 48, 32, 29, 31, 1, 2),     # strides: split columns, odd centres
     (2, 40, 33, 31, 45, 2, 3),
+    # data gradient at strides: classes cut at the border, streamed weights
+    # (100 output channels at k = 2), one class row, strides up to 8
+    (1, 5, 100, 33, 35, 2, 2), (1, 33, 16, 48, 47, 3, 2), (3, 16, 16, 16, 40, 1, 4),
+    (1, 12, 8, 33, 64, 2, 8), (1, 3, 8, 2, 17, 1, 2), (1, 64, 64, 32, 32, 1, 2),
+    # whole 16-byte rows that the tuned bf16 kernels leave to this one
+    (2, 64, 96, 40, 48, 1, 1), (1, 96, 96, 33, 40, 1, 1), (2, 32, 32, 64, 64, 2, 1),
 ]
 
 
