@@ -371,7 +371,9 @@ int hexconv_fwd(const void *x, const void *w, const void *bias, void *y, int N, 
         const bool wide = d == hexk::BF16 && hexk::bf16_wide_ok(sh, sh.Ci, sh.Co);
         if (wide && hexk::bf16_wide_first(sh, sh.Ci, sh.Co, false))
             return launched(hexk::bf16_wide_conv(x, w, bias, y, sh, false, relu, st));
-        if (hexk::conv_any_ok(sh, d, false))
+        if (d == hexk::F32 && hexk::conv_f32_fwd_ok(sh))
+            return launched(hexk::conv_f32_fwd(x, w, bias, y, sh, relu, st));
+        if (d == hexk::BF16 && hexk::conv_any_ok(sh, d, false))
             return launched(hexk::conv_any(x, w, bias, y, sh, d, false, relu, st));
         if (wide)
             return launched(hexk::bf16_wide_conv(x, w, bias, y, sh, false, relu, st));
@@ -631,7 +633,10 @@ int hexconv3d_fwd(const void *x, const void *w, const void *bias, void *y, int N
         return launched(hexk::smallc_fwd(x, w, bias, y, sh, static_cast<Dtype>(dt),
                                          (flags & HEX_FLAG_RELU) != 0,
                                          static_cast<hipStream_t>(stream)));
-    if (!force_generic() && hexk::conv_any_ok(sh, static_cast<Dtype>(dt), false))
+    if (!force_generic() && dt == HEX_F32 && hexk::conv_f32_fwd_ok(sh))
+        return launched(hexk::conv_f32_fwd(x, w, bias, y, sh, (flags & HEX_FLAG_RELU) != 0,
+                                       static_cast<hipStream_t>(stream)));
+    if (!force_generic() && dt == HEX_BF16 && hexk::conv_any_ok(sh, static_cast<Dtype>(dt), false))
         return launched(hexk::conv_any(x, w, bias, y, sh, static_cast<Dtype>(dt), false,
                                        (flags & HEX_FLAG_RELU) != 0,
                                        static_cast<hipStream_t>(stream)));

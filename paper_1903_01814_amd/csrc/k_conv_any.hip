@@ -1,10 +1,10 @@
 // k_conv_any.hip -- convolution on the matrix cores for planes of any size
-// and any channel count: forward at any stride and, at stride 1, the data
-// gradient (the same sum with the reflected kernel), in bfloat16 and in
-// float32, two- and three-dimensional.  The tuned bfloat16 kernels
-// (k_mfma_bf16.hip, k_mfma_gen.hip) need rows of whole 16-byte vectors and
-// whole 32-channel blocks; this one takes what they do not: odd rows, other
-// channel counts, float32 layers with more than a few channels, 3-D layers.
+// and any channel count: the bfloat16 forward at any stride and the data
+// gradient (at stride 1 the same sum with the reflected kernel) in bfloat16
+// and float32, two- and three-dimensional.  (The float32 forward keeps the
+// order of its sums: k_conv_f32.hip.)  The tuned bfloat16 kernels of
+// k_mfma_bf16.hip need rows of whole 16-byte vectors and whole 32-channel
+// blocks; this one takes what they do not, and what it does faster.
 //
 // Implicit GEMM on 32x32 tiles.  A block (8 waves) computes a tile of whole
 // output rows of one plane (up to 256 MG pixels, groups of 32, MG per wave)
@@ -988,10 +988,9 @@ bool conv_any_ok(const ConvShape &sh, Dtype d, bool dgrad)
 {
     // Few source channels leave most of a chunk empty; then the generic
     // kernel is the faster one.  64 images of 41 x 43, k = 1, us here against
-    // generic: fp32 3 -> 16 channels 13.4 / 18.0, 2 -> 16 18.5 / 15.4; bf16
-    // 3 -> 16 8.6 / 17.7, 1 -> 16 9.9 / 10.8; 8 volumes of 12 planes of
-    // 37 x 41, kz = 1: fp32 4 -> 16 38 / 54, 3 -> 16 38 / 43; bf16 2 -> 16
-    // 25 / 32, 1 -> 16 25 / 20.
+    // generic: bf16 3 -> 16 channels 8.6 / 17.7, 1 -> 16 9.9 / 10.8; 8 volumes
+    // of 12 planes of 37 x 41, kz = 1: bf16 2 -> 16 25 / 32, 1 -> 16 25 / 20;
+    // fp32 (the data gradient only) 8 source channels 36 / 33, 16 57 / 71.
     const int Cs = dgrad ? sh.Co : sh.Ci;
     if (Cs < (d == F32 ? 3 : 2))
         return false;

@@ -287,7 +287,10 @@ __global__ __launch_bounds__(kThreads) void fwd_smallc_k(
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 a[s] = xs[ca + off[s]];
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+            // cut rows start from the bias, as the generic kernel does, whose
+            // sums (the same order of products) they then equal bit for bit
+            const float b0 = RAG ? bco : 0.f;
+            floatx4 acc = {b0, b0, b0, b0};
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kval[s] ? a[s] : 0.f, bw[s], acc, 0,
@@ -299,7 +302,7 @@ __global__ __launch_bounds__(kThreads) void fwd_smallc_k(
             float v[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                v[j] = acc[j] + bco;
+                v[j] = RAG ? acc[j] : acc[j] + bco;
                 if (relu)
                     v[j] = fmaxf(v[j], 0.f);
             }

@@ -186,6 +186,11 @@ hipError_t bf16_wgrad(const void *x, const void *dy, float *dw, float *db, void 
 bool conv_any_ok(const ConvShape &sh, Dtype d, bool dgrad);
 hipError_t conv_any(const void *in, const void *w, const void *bias, void *out,
                     const ConvShape &sh, Dtype d, bool dgrad, bool relu, hipStream_t st);
+// float32 forward in the generic kernel's order of sums, bit for bit
+// (k_conv_f32.hip); 2-D and 3-D, k 1 to 3
+bool conv_f32_fwd_ok(const ConvShape &sh);
+hipError_t conv_f32_fwd(const void *x, const void *w, const void *bias, void *y,
+                        const ConvShape &sh, bool relu, hipStream_t st);
 bool wgrad_any_ok(const ConvShape &sh, Dtype d);
 size_t wgrad_any_workspace(const ConvShape &sh, Dtype d);
 hipError_t wgrad_any(const void *x, const void *dy, float *dw, float *db, void *ws,

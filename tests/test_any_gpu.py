@@ -165,6 +165,44 @@ def test_pool3d_any_shape(case, mode, dt):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("case", [
+    # N, C_in, C_out, D (None: 2-D), H, W, k, kz, stride, stride_z
+    (2, 33, 70, None, 17, 29, 1, 0, 2, 1), (1, 40, 20, None, 12, 13, 2, 0, 1, 1),
+    (1, 24, 24, None, 1, 9, 1, 0, 1, 1), (1, 16, 7, None, 9, 250, 1, 0, 1, 1),
+    (2, 16, 33, None, 9, 8, 3, 0, 1, 1), (1, 1, 16, None, 20, 21, 2, 0, 1, 1),
+    (1, 130, 40, None, 11, 24, 1, 0, 3, 1), (30, 16, 24, None, 20, 21, 1, 0, 1, 1),
+    (2, 9, 32, 4, 12, 13, 1, 1, 1, 1), (1, 8, 12, 5, 9, 11, 1, 2, 1, 2),
+    (1, 5, 40, 3, 12, 13, 2, 1, 2, 1)])
+def test_f32_forward_order(case):
+    """The float32 forward of rows that the generic kernel used to take equals
+    that kernel bit for bit: the same products in the same order from the
+    bias on, so what a ReLU or a maximum decides does not change."""
+    import os
+    from paper_1903_01814_amd import hexconv as hx
+    torch = torch_mod()
+    N, Ci, Co, D, H, W, k, kz, s, sz = case
+    g = torch.Generator().manual_seed(N + Ci + H)
+    T = hx.hex_num_taps(k)
+    vol = D is not None
+    x = torch.randn((N, Ci) + ((D,) if vol else ()) + (H, W), generator=g).cuda()
+    w = torch.randn((Co, Ci) + ((2 * kz + 1,) if vol else ()) + (T,), generator=g).cuda()
+    b = torch.randn(Co, generator=g).cuda()
+    o = hx.hex_out_shape3d(D, H, W, k, kz, s, sz) if vol else hx.hex_out_shape(H, W, k, s)
+    got = []
+    try:
+        for path in ("", "generic"):
+            os.environ["HEXCONV_PATH"] = path
+            y = torch.full((N, Co) + tuple(o), float("nan"), device="cuda")
+            if vol:
+                hx.hexconv3d_fwd(x, w, b, y, k, kz, s, sz)
+            else:
+                hx.hexconv_fwd(x, w, b, y, k, s)
+            got.append(y)
+    finally:
+        os.environ.pop("HEXCONV_PATH", None)
+    assert torch.equal(*got)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_weight_gradient_keeps_infinities(dt):
     """An infinity in x next to a tile's end reaches the sums of its own taps
