@@ -256,14 +256,29 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
     const int p0 = Gm::colbase(c0w) + K + 4 * (dwv & 1) + kq;
     constexpr int PSTEP = 2 * P - 1; // two columns further
     const int nsteps = (W - c0w + 1) / 2;
-    floatx4 acc[2][MT][NT];
+    // A tile's products are summed by themselves (HC chains) and then added
+    // to the run's sums: one chain over the whole run is less precise
+    // (db of 2 -> 16 channels, 45 x 43, N = 192, relative error against 64
+    // bits 3e-7, now 1.7e-7; the generic kernel 1.2e-7; 1 -> 16, 40 x 40, k =
+    // 2, N = 256, all outputs 3.4e-7, now 1.9e-7) and no faster (37.6 us the
+    // pass, now 37.3).  One chain a tile where four or more products are
+    // independent keeps the registers as few as two chains over the run.
+    constexpr int HC = MT * NT <= 2 ? 2 : 1;
+    floatx4 acc[HC][MT][NT], tot[MT][NT];
+    auto clear = [&]() {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < HC; ++h)
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+            for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int j = 0; j < NT; ++j)
-                acc[h][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+                for (int j = 0; j < NT; ++j)
+                    acc[h][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    };
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+            tot[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     auto kstep = [&](int i, int h) {
         const int pa = p0 + i * PSTEP;
         float a[MT], b[NT];
@@ -371,13 +386,23 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
                         dxp[((g * CI + ci) * kTR + r) * W + c] = gacc[ci][r];
             }
         } else {
+            clear();
             int i = 0;
             for (; i + 1 < nsteps; i += 2) {
                 kstep(i, 0);
-                kstep(i + 1, 1);
+                kstep(i + 1, HC - 1);
             }
             if (i < nsteps)
                 kstep(i, 0);
+#pragma unroll
+            for (int ii = 0; ii < MT; ++ii)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    floatx4 t = acc[0][ii][j];
+                    if constexpr (HC == 2)
+                        t += acc[1][ii][j];
+                    tot[ii][j] += t;
+                }
         }
         __syncthreads(); // partials written; every read of the window done
         // dx: the groups' partials added in a fixed order, 16-byte stores.
@@ -424,8 +449,7 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
     if (tile < t_end)
         tile_step(sa, tile);
 
-    // sum the accumulator sets and the weight-gradient waves in a fixed
-    // order; one partial per output element (chunked layout)
+    // sum the weight-gradient waves in a fixed order; one partial per output element (chunked layout)
     __syncthreads();
     float *red = lds; // [kDwWaves][MT * 16][NT * 16]
     if (!dxrole) {
@@ -436,7 +460,7 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     red[((dwv * MT + i) * 16 + 4 * kq + q) * (NT * 16) + j * 16 + m] =
-                        acc[0][i][j][q] + acc[1][i][j][q];
+                        tot[i][j][q];
     }
     __syncthreads();
     constexpr int Jt = J + 1;
