@@ -34,6 +34,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "../../include/hexconv.h"
 #include "chanlast.h"
 #include "kernels.h"
 
@@ -533,9 +534,16 @@ bool plan_wgrad(const ConvShape &sh, Dtype d, WAnyPlan &pl)
     a.ntot = static_cast<int>(ntot);
     pl.types = a.Z * a.nci * a.nco;
     // one block per compute unit in all; every slot costs a write and a read
-    // of its partial sums
-    a.nslots = std::max(1, std::min(a.ntot, device_cus() / pl.types));
-    pl.ws = static_cast<size_t>(pl.types) * a.nslots * pl.G * pl.A * we * 4;
+    // of its partial sums.  No more slots than the scratch array of
+    // hexconv_bwd_noalloc holds (at k > 1 256 slots would take 80 MB of its
+    // 64), and no shape of which it holds not even one, so that this call
+    // takes every shape that the other kernels' workspaces allow.
+    const size_t slot = static_cast<size_t>(pl.types) * pl.G * pl.A * we * 4;
+    if (slot > HEX_NOALLOC_SCRATCH_BYTES)
+        return false;
+    a.nslots = std::max(1, std::min({a.ntot, device_cus() / pl.types,
+                                     static_cast<int>(HEX_NOALLOC_SCRATCH_BYTES / slot)}));
+    pl.ws = slot * a.nslots;
     return true;
 }
 

@@ -185,6 +185,15 @@ def test_pool_rejects_invalid():
     assert bw(mode=3) == hx.HEX_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("dt", [hx.HEX_F32, hx.HEX_BF16])
+@pytest.mark.parametrize("shape", [(256, 131, 184, 139, 11, 3, 1), (1, 159, 182, 82, 127, 2, 1),
+                                   (256, 101, 61, 66, 122, 2, 3)])
+def test_noalloc_holds_every_slot_count(shape, dt):
+    """k > 1 layers of many tiles: 256 slots of partial sums would pass the
+    scratch array, so there are fewer."""
+    assert 0 < hx.hexconv_bwd_workspace(*shape, dt) <= hx.HEX_NOALLOC_SCRATCH_BYTES
+
+
 def test_noalloc_rejects_oversized_workspace():
     """hexconv_bwd_noalloc: a shape whose workspace exceeds the static
     scratch array is HEX_ERR_UNSUPPORTED, decided on the host before any
