@@ -529,6 +529,12 @@ hipError_t dispatch(const F32Plan &pl, const float *x, const float *w, const flo
 
 bool conv_f32_fwd_ok(const ConvShape &sh)
 {
+    // One input plane (at a stride; the few-channel kernel has the others) is
+    // too short a contraction to pay for staging and weights: stride 2, us
+    // here against generic, 2 x 1 -> 15 channels, 33 x 48, k = 2 7.3 / 6.1;
+    // 4 x 1 -> 4, 24 x 30, k = 1 5.3 / 4.6; from two planes on it is not slower.
+    if (sh.Ci * sh.Z == 1)
+        return false;
     F32Plan pl;
     return plan_f32(sh, pl);
 }
