@@ -34,6 +34,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "../../include/hexconv.h"
 #include "hexdev.h"
 #include "kernels.h"
 #include "shear.h"
@@ -791,11 +792,24 @@ hipError_t smallc_bwd_data(const void *dy, const void *w, void *dx, const ConvSh
 }
 
 namespace {
+// one slot of partial sums (bytes)
+size_t wgrad_slot(const ConvShape &sh)
+{
+    return sizeof(float) * static_cast<size_t>(sh.Co) * (sh.Ci * sh.Z * sh.T + 1);
+}
+
+// Slots of partial sums, a block each (times blocks of 16 output channels).
+// No more of them than the scratch array of hexconv_bwd_noalloc holds: 1024
+// slots pass it from about 260 output channels of 63 columns on (8 -> 454
+// channels, 64 images of 116 x 37: 103 KB a slot, 79.5 MB of slots, now 64
+// MB), where the blocks of output channels fill the chip many times over.
 int wgrad_grid(const ConvShape &sh, const Tiling &tg)
 {
     const int per_cu = std::max(
         1, std::min(kWgradPerCu, static_cast<int>(kLdsPerCu / std::max<size_t>(1, wgrad_lds(sh, tg)))));
-    return std::min(tg.ntiles, device_cus() * per_cu);
+    const size_t fit = std::max<size_t>(1, HEX_NOALLOC_SCRATCH_BYTES / wgrad_slot(sh));
+    return std::min({tg.ntiles, device_cus() * per_cu,
+                     static_cast<int>(std::min<size_t>(fit, 1 << 20))});
 }
 } // namespace
 
@@ -816,8 +830,7 @@ size_t smallc_wgrad_workspace(const ConvShape &sh0)
 {
     const ConvShape sh = fwd_view(sh0);
     const Tiling tg = make_tiling(sh, kWgradTarget);
-    return sizeof(float) * static_cast<size_t>(wgrad_grid(sh, tg)) * sh.Co *
-           (sh.Ci * sh.Z * sh.T + 1);
+    return wgrad_slot(sh) * wgrad_grid(sh, tg);
 }
 
 namespace {

@@ -194,6 +194,16 @@ def test_noalloc_holds_every_slot_count(shape, dt):
     assert 0 < hx.hexconv_bwd_workspace(*shape, dt) <= hx.HEX_NOALLOC_SCRATCH_BYTES
 
 
+@pytest.mark.parametrize("shape", [
+    (64, 8, 454, 116, 37, 1, 1), (1000, 3, 769, 45, 43, 1, 1), (800, 1, 1500, 30, 29, 3, 1),
+    (200, 2, 900, 41, 127, 2, 1), (20, 8, 65535, 9, 13, 1, 1)])
+@pytest.mark.parametrize("dt", [hx.HEX_F32, hx.HEX_BF16])
+def test_noalloc_holds_few_input_channels(shape, dt):
+    """Few channels in and many out: a slot of partial sums is large, and
+    1024 of them would pass the scratch array."""
+    assert 0 < hx.hexconv_bwd_workspace(*shape, dt) <= hx.HEX_NOALLOC_SCRATCH_BYTES
+
+
 def test_noalloc_rejects_oversized_workspace():
     """hexconv_bwd_noalloc: a shape whose workspace exceeds the static
     scratch array is HEX_ERR_UNSUPPORTED, decided on the host before any
