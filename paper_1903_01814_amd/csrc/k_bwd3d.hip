@@ -147,6 +147,21 @@ __global__ __launch_bounds__(kMaxThreads3) void bwd_data3d_smallc_k(
         load_group(p, last ? d + 1 : d, last ? 0 : g + 1);
         const int c0 = g * CC, cn = min(CC, Co - c0);
         if (active) {
+            // float32: summed by themselves, then added to the ring, so that
+            // a chain has a third of the additions (dx of 1 -> 12 channels,
+            // 15 volumes of 25 x 31 x 35, off the sum in 64 bits: generic
+            // kernel 2.6e-7, one chain 3.0e-7, now 1.7e-7).  bfloat16 results
+            // do not show it, and there it costs (39 volumes, 2 -> 16
+            // channels, 23 x 41 x 31: 86, 101 us).
+            constexpr bool SPLIT = sizeof(TT) == sizeof(float);
+            float part[Z][CI][R];
+#pragma unroll
+            for (int s = 0; s < Z; ++s)
+#pragma unroll
+                for (int ci = 0; ci < CI; ++ci)
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        part[s][ci][r] = SPLIT ? 0.f : acc[s][ci][r];
             // products of staged channel cl with its weights: wt(ci, m) is
             // value m of the Z T weights of (this output channel, ci)
             auto channel = [&](int cl, auto wt) __attribute__((always_inline)) {
@@ -173,7 +188,7 @@ __global__ __launch_bounds__(kMaxThreads3) void bwd_data3d_smallc_k(
                                     const float wv = wt(ci, s * T + (T - 1 - tr));
 #pragma unroll
                                     for (int r = 0; r < R; ++r)
-                                        acc[s][ci][r] += wv * v[r + u];
+                                        part[s][ci][r] += wv * v[r + u];
                                 }
                             }
                         }
@@ -203,6 +218,13 @@ __global__ __launch_bounds__(kMaxThreads3) void bwd_data3d_smallc_k(
                     channel(cl, [&](int ci, int m) { return we(ci * Z * T + m); });
                 }
             }
+#pragma unroll
+            for (int s = 0; s < Z; ++s)
+#pragma unroll
+                for (int ci = 0; ci < CI; ++ci)
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        acc[s][ci][r] = (SPLIT ? acc[s][ci][r] : 0.f) + part[s][ci][r];
         }
         if (last) {
             store_slot0(d - KZ);

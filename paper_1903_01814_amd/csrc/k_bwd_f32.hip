@@ -256,15 +256,20 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
     const int p0 = Gm::colbase(c0w) + K + 4 * (dwv & 1) + kq;
     constexpr int PSTEP = 2 * P - 1; // two columns further
     const int nsteps = (W - c0w + 1) / 2;
-    // A tile's products are summed by themselves (HC chains) and then added
-    // to the run's sums: one chain over the whole run is less precise
-    // (db of 2 -> 16 channels, 45 x 43, N = 192, relative error against 64
-    // bits 3e-7, now 1.7e-7; the generic kernel 1.2e-7; 1 -> 16, 40 x 40, k =
-    // 2, N = 256, all outputs 3.4e-7, now 1.9e-7) and no faster (37.6 us the
-    // pass, now 37.3).  One chain a tile where four or more products are
-    // independent keeps the registers as few as two chains over the run.
-    constexpr int HC = MT * NT <= 2 ? 2 : 1;
-    floatx4 acc[HC][MT][NT], tot[MT][NT];
+    // The matrix cores add four K-steps (16 pixels) from zero, these sums are
+    // added over the tile, and the tiles' sums over the run: one chain over
+    // the run is further off the sum in 64 bits (db of 2 -> 12 channels, k = 2,
+    // 30 images of 37 x 41: generic kernel 1.1e-7, a chain a tile 2.0e-7, now
+    // 1.0e-7; 1 -> 16, 38 x 30, N = 106, k = 1, dw 1.05e-7, 1.24e-7, 0.9e-7).
+    // 1 -> 16 channels, 40 x 40, k = 2, N = 256: 21.3 us a chain a tile, 21.9.
+    constexpr bool BY_TILE = MT * NT <= 4; // the registers hold the tile's sums too
+    constexpr int HC = MT * NT <= 2 ? 2 : 1; // chains at a time
+    floatx4 acc[HC][MT][NT], sum[MT][NT], tot[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+            tot[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     auto clear = [&]() {
 #pragma unroll
         for (int h = 0; h < HC; ++h)
@@ -274,11 +279,17 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
                 for (int j = 0; j < NT; ++j)
                     acc[h][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     };
+    auto flush = [&]() {
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
-            tot[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < NT; ++j) {
+                floatx4 v = acc[0][i][j];
+                if constexpr (HC == 2)
+                    v += acc[1][i][j];
+                (BY_TILE ? sum : tot)[i][j] += v;
+            }
+    };
     auto kstep = [&](int i, int h) {
         const int pa = p0 + i * PSTEP;
         float a[MT], b[NT];
@@ -386,23 +397,36 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
                         dxp[((g * CI + ci) * kTR + r) * W + c] = gacc[ci][r];
             }
         } else {
-            clear();
-            int i = 0;
-            for (; i + 1 < nsteps; i += 2) {
-                kstep(i, 0);
-                kstep(i + 1, HC - 1);
-            }
-            if (i < nsteps)
-                kstep(i, 0);
 #pragma unroll
             for (int ii = 0; ii < MT; ++ii)
 #pragma unroll
-                for (int j = 0; j < NT; ++j) {
-                    floatx4 t = acc[0][ii][j];
-                    if constexpr (HC == 2)
-                        t += acc[1][ii][j];
-                    tot[ii][j] += t;
-                }
+                for (int j = 0; j < NT; ++j)
+                    sum[ii][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+            int i = 0;
+            auto group = [&](auto n) {
+                clear();
+#pragma unroll
+                for (int u = 0; u < decltype(n)::value; ++u)
+                    kstep(i + u, u % HC);
+                flush();
+                i += decltype(n)::value;
+            };
+            while (i + 4 * HC <= nsteps)
+                group(std::integral_constant<int, 4 * HC>{});
+            if (HC == 2 && i + 4 <= nsteps)
+                group(std::integral_constant<int, 4>{});
+            if (i < nsteps) {
+                clear();
+                for (; i < nsteps; ++i)
+                    kstep(i, 0);
+                flush();
+            }
+            if constexpr (BY_TILE)
+#pragma unroll
+                for (int ii = 0; ii < MT; ++ii)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+                        tot[ii][j] += sum[ii][j];
         }
         __syncthreads(); // partials written; every read of the window done
         // dx: the groups' partials added in a fixed order, 16-byte stores.

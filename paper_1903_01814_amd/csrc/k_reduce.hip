@@ -8,7 +8,10 @@
 //    elements, each slot's 64 values contiguous, so a block writing its
 //    partials and the reduction reading them both touch whole lines.
 // Either way the slots are summed in a fixed order (strided per thread,
-// then a fixed tree), so results do not depend on timing.
+// then a fixed tree), so results do not depend on timing.  Up to 1024 slots
+// added in float32 chains were a good part of the error of dw and db:
+// reduce_partials adds them in 64 bits (its loads bound it), reduce_chunked,
+// where that costs 2 us of 4, in a tree.
 #include "hexdev.h"
 #include "kernels.h"
 
@@ -24,7 +27,7 @@ __global__ __launch_bounds__(64) void reduce_partials_k(const float *__restrict_
     const int e = blockIdx.x;
     const int lane = threadIdx.x;
     const float *src = part + static_cast<size_t>(e) * nparts;
-    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
     int p = lane;
     for (; p + 192 < nparts; p += 256) {
 #pragma unroll
@@ -33,11 +36,12 @@ __global__ __launch_bounds__(64) void reduce_partials_k(const float *__restrict_
     }
     for (; p < nparts; p += 64)
         s[0] += src[p];
-    float v = (s[0] + s[1]) + (s[2] + s[3]);
+    double sum = (s[0] + s[1]) + (s[2] + s[3]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1)
-        v += __shfl_xor(v, off, 64);
+        sum += __shfl_xor(sum, off, 64);
     if (lane == 0) {
+        const float v = static_cast<float>(sum);
         const int Jt = J + 1;
         const int co = e / Jt, col = e % Jt;
         if (col < J)
@@ -72,8 +76,11 @@ __global__ __launch_bounds__(kPartChunk * kRedSlices) void reduce_chunked_k(
             v[u] = p < nparts ? src[static_cast<size_t>(p) * kPartChunk] : 0.f;
         }
 #pragma unroll
-        for (int u = 0; u < kRedBatch; ++u)
-            acc += v[u];
+        for (int half = kRedBatch / 2; half > 0; half >>= 1)
+#pragma unroll
+            for (int u = 0; u < half; ++u)
+                v[u] += v[u + half];
+        acc += v[0];
     }
     red[sl][el] = acc;
     for (int half = kRedSlices / 2; half > 0; half >>= 1) {

@@ -29,6 +29,18 @@
 // block's sums go to a slot of the workspace and reduce_any_k adds the slots
 // in order (deterministic).
 //
+// float32 sums: a chain of n additions of independent terms is off by about
+// 2.5e-8 sqrt(n / 2) of the sum, and a block's run of tiles is long.  So the
+// matrix cores add 16 pixels at a time, from zero, eight of these sums are
+// added up, and those are added over the run: three short chains.  Off the
+// sum in 64 bits (generic kernel, one chain, now): 4 -> 8 channels, k = 2, 227
+// images of 41 x 39, dw 1.1e-7, 1.8e-7, 0.85e-7, db 1.8e-7, 4.4e-7, 1.4e-7; 64
+// -> 96, 28 x 29 x 33, dw 1.4e-7, 2.1e-7, 1.0e-7; 22 volumes of 12 -> 32, dw
+// 1.1e-7, 2.7e-7, 1.1e-7.  The two sums kept of a tap take 32 registers, so a block holds one 32 x 32
+// tile of channels (at k = 1 two of output channels, a tap a wave), which
+// costs little, the products being the slow part (64 clocks each).  (64-bit sums of the 16 pixels: the conversions made k = 2
+// 1.3 times as slow.)
+//
 // Pixels past a tile's end: both operands are zeroed (by masks), so that no
 // product of a stray infinity reaches a sum.
 #include <algorithm>
@@ -62,16 +74,9 @@ struct WAnyArgs {
 };
 
 // Taps per wave and tap groups: T + 1 columns (the taps and the bias)
-template <int K> struct WRole;
-template <> struct WRole<1> {
-    static constexpr int TPW = 4, G = 2;
-};
-template <> struct WRole<2> {
-    static constexpr int TPW = 5, G = 4;
-};
-template <> struct WRole<3> {
-    static constexpr int TPW = 5, G = 8;
-};
+constexpr int role_tpw(bool f32, int k, int nco) { return k > 1 ? 5 : f32 ? 2 / nco : 4; }
+constexpr int role_g(bool f32, int k, int nco) { return k == 3 ? 8 : k == 2 ? 4 : f32 ? 4 * nco : 2; }
+constexpr int kRunSteps = 8; // float32: steps of 16 pixels per chain of step sums
 
 // Four pixels of a channel from a0 and four from a1, transposed (see above)
 __device__ __forceinline__ bf16x8 tr_read(unsigned char *a0, unsigned char *a1)
@@ -95,7 +100,7 @@ __global__ __launch_bounds__(kWThreads) void wgrad_any_k(const E *x, const E *dy
     constexpr int PX = AnyE<E>::PX;
     constexpr int T = num_taps(K);
     constexpr TapTable<K> tab{};
-    constexpr int TPW = WRole<K>::TPW, G = WRole<K>::G;
+    constexpr int TPW = role_tpw(F32, K, NCO), G = role_g(F32, K, NCO);
     constexpr int KS = 8 / (G * A);
     constexpr int CB = 32 * sizeof(E);      // bytes of 32 channels
     constexpr int XB = A * CB, DB = NCO * CB; // bytes per slot
@@ -212,6 +217,25 @@ __global__ __launch_bounds__(kWThreads) void wgrad_any_k(const E *x, const E *dy
 #pragma unroll
         for (int t = 0; t < TPW; ++t)
             acc[c][t] = floatx16{};
+    // float32: sums of up to kRunSteps steps, not yet in acc
+    constexpr int RC = F32 ? NCO : 1, RT = F32 ? TPW : 1;
+    floatx16 run[RC][RT];
+    int nrun = 0;
+#pragma unroll
+    for (int c = 0; c < RC; ++c)
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+            run[c][t] = floatx16{};
+    auto end_run = [&]() {
+        if constexpr (F32)
+#pragma unroll
+            for (int c = 0; c < NCO; ++c)
+#pragma unroll
+                for (int t = 0; t < TPW; ++t) {
+                    acc[c][t] += run[c][t];
+                    run[c][t] = floatx16{};
+                }
+    };
 
     unsigned char *xb = win + ai * CB;
     const int prow = a.RP * XB;
@@ -237,30 +261,64 @@ __global__ __launch_bounds__(kWThreads) void wgrad_any_k(const E *x, const E *dy
     auto step = [&](auto tail, int p0, int left) {
         constexpr bool TAIL = decltype(tail)::value;
         if constexpr (F32) {
+            float av[NCO][8];
+            int b0[8], b1[8]; // window bytes of the centre, and where the tap's column is odd
 #pragma unroll
             for (int h = 0; h < 8; ++h) {
                 const int p = p0 + 2 * h + (lane >> 5);
                 const int e = ptab[p];
-                const unsigned char *b0 = xb + (e & ~1) + 4 * (lane & 31);
-                const unsigned char *b1 = b0 + ((e & 1) ? prow : 0);
-                const bool live = 2 * h + (lane >> 5) < left;
-                float av[NCO];
+                b0[h] = (e & ~1) + 4 * (lane & 31);
+                b1[h] = b0[h] + ((e & 1) ? prow : 0);
 #pragma unroll
                 for (int c = 0; c < NCO; ++c)
-                    av[c] = *reinterpret_cast<const float *>(dyl + p * DB + c * CB +
-                                                             4 * (lane & 31));
+                    av[c][h] = *reinterpret_cast<const float *>(dyl + p * DB + c * CB +
+                                                                4 * (lane & 31));
+            }
+            // a tap's operands are read during the products of the tap before
+            // (left alone, each product waits for its own read), whose sums
+            // are added in turn between this tap's products
+            float bv[2][8];
+            auto read = [&](int t) {
 #pragma unroll
-                for (int t = 0; t < TPW; ++t) {
-                    float bv = *reinterpret_cast<const float *>((todd[t] ? b1 : b0) + toff[t]);
+                for (int h = 0; h < 8; ++h) {
+                    float v = *reinterpret_cast<const float *>(xb + (todd[t] ? b1[h] : b0[h]) +
+                                                               toff[t]);
                     if (t == T % TPW && has_bias)
-                        bv = 1.f;
+                        v = 1.f;
                     if (TAIL)
-                        bv = live ? bv : 0.f;
-#pragma unroll
-                    for (int c = 0; c < NCO; ++c)
-                        acc[c][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[c], bv, acc[c][t], 0,
-                                                                         0, 0);
+                        v = 2 * h + (lane >> 5) < left ? v : 0.f;
+                    bv[t & 1][h] = v;
                 }
+            };
+            floatx16 s[2][NCO];
+            read(0);
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) {
+                if (t + 1 < TPW)
+                    read(t + 1);
+#pragma unroll
+                for (int c = 0; c < NCO; ++c)
+                    s[t & 1][c] = floatx16{};
+#pragma unroll
+                for (int h = 0; h < 8; ++h) {
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int c = 0; c < NCO; ++c) {
+                        s[t & 1][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                            av[c][h], bv[t & 1][h], s[t & 1][c], 0, 0, 0);
+                        if (t > 0)
+#pragma unroll
+                            for (int r = 2 * h; r < 2 * h + 2; ++r)
+                                run[c][t - 1][r] += s[(t - 1) & 1][c][r];
+                    }
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < NCO; ++c)
+                run[c][TPW - 1] += s[(TPW - 1) & 1][c];
+            if (++nrun == kRunSteps) {
+                nrun = 0;
+                end_run();
             }
         } else {
             // pixels 8 (lane / 32) + (lane % 16) / 4 and 4 further on;
@@ -331,6 +389,7 @@ __global__ __launch_bounds__(kWThreads) void wgrad_any_k(const E *x, const E *dy
         cur = nxt;
     }
 
+    end_run();
     // add the pixel splits, then one slot of partial sums:
     // part[type][slot][wave role][tap][co tile][r][lane]
     constexpr int WE = NCO * TPW * 16 * 64; // floats per wave
@@ -371,9 +430,10 @@ __global__ __launch_bounds__(kWThreads) void wgrad_any_k(const E *x, const E *dy
     }
 }
 
-// dw and db from the slots, in a fixed order: a block owns 64 consecutive
-// partial elements (one wave's width) and its waves every kRedWaves-th slot,
-// eight loads in flight each; the waves' sums are added through LDS.  One
+// dw and db from the slots, in a fixed order and in 64 bits (the loads bound
+// it): a block owns 64 consecutive partial elements (one wave's width) and its
+// waves every kRedWaves-th slot, eight loads in flight each; the waves' sums
+// are added through LDS.  One
 // thread per element over all slots was bound by its chain of loads (256
 // slots of 64 KB: 18.7 us).
 struct RedArgs {
@@ -386,7 +446,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void reduce_any_k(const float *__re
                                                                float *__restrict__ dw,
                                                                float *__restrict__ db, RedArgs a)
 {
-    __shared__ float sums[kRedWaves][64];
+    __shared__ double sums[kRedWaves][64];
     const int type = blockIdx.y;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -406,7 +466,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void reduce_any_k(const float *__re
         (bias && (db == nullptr || ci0 != 0 || dz != a.kz)))
         return; // the same for the whole block
     const float *p = part + static_cast<size_t>(type) * a.nslots * a.per + blockIdx.x * 64 + lane;
-    float s[8] = {};
+    double s[8] = {};
     int i = wave;
     for (; i + 7 * kRedWaves < a.nslots; i += 8 * kRedWaves)
 #pragma unroll
@@ -418,10 +478,11 @@ __global__ __launch_bounds__(64 * kRedWaves) void reduce_any_k(const float *__re
     __syncthreads();
     if (wave != 0)
         return;
-    float v = 0.f;
+    double sum = 0.0;
 #pragma unroll
     for (int k = 0; k < kRedWaves; ++k)
-        v += sums[k][lane];
+        sum += sums[k][lane];
+    const float v = static_cast<float>(sum);
     const int co = co0 + 4 * (lane >> 5), ci = ci0 + (lane & 31);
     if (co >= a.Co || ci >= a.Ci || (bias && ci != 0))
         return;
@@ -440,15 +501,32 @@ struct WAnyPlan {
     int NCO, A, U, G, TPW;
     size_t lds, ws;
     int types;
+    double cost;
 };
 
-// The largest tile for A input-channel tiles and U items per thread.
-bool plan_tile(const ConvShape &sh, Dtype d, int A, int U, WAnyPlan &pl)
+// Clocks of a compute unit for `slots` blocks of every type at the tile of
+// `pl`: rounds of tiles (products of two waves a SIMD, and staging), and the
+// partial sums of all slots, written and read again at about 3 TB/s.
+double tile_cost(const WAnyPlan &pl, Dtype d, long ntot, int slots, int items, int types,
+                 size_t slot)
+{
+    const WAnyArgs &a = pl.a;
+    const int KS = 8 / (pl.G * pl.A);
+    const int steps = (a.npix / 16 + KS - 1) / KS;
+    const double mf = steps * 2.0 * pl.TPW * pl.NCO * (d == F32 ? 8 * 64 : 32);
+    const double waves = std::max(1.0, types * slots / static_cast<double>(device_cus()));
+    const double rounds = static_cast<double>((ntot + slots - 1) / slots);
+    return waves * rounds * (mf + 4000 + items * 4.0) + slot * slots * 0.0008;
+}
+
+// The tile (rows of it) and the number of slots for A input-channel tiles
+// and U items per thread, the cheapest that fits.
+bool plan_tile(const ConvShape &sh, Dtype d, int A, int U, WAnyPlan &best)
 {
     const int es = d == F32 ? 4 : 2, PX = 16 / es;
     const int K = sh.k;
+    WAnyPlan pl{};
     WAnyArgs &a = pl.a;
-    a = WAnyArgs{};
     a.N = sh.N;
     a.Ci = sh.Ci;
     a.Co = sh.Co;
@@ -462,26 +540,41 @@ bool plan_tile(const ConvShape &sh, Dtype d, int A, int U, WAnyPlan &pl)
     a.sz = sh.sz;
     a.kz = sh.kz;
     a.Z = sh.Z;
-    pl.TPW = K == 1 ? 4 : 5;
-    pl.G = K == 1 ? 2 : K == 2 ? 4 : 8;
-    pl.NCO = sh.Co > 32 ? 2 : 1;
+    pl.NCO = (d != F32 || K == 1) && sh.Co > 32 ? 2 : 1;
+    pl.TPW = role_tpw(d == F32, K, pl.NCO);
+    pl.G = role_g(d == F32, K, pl.NCO);
     pl.A = A;
     pl.U = U;
     a.nco = (sh.Co + 32 * pl.NCO - 1) / (32 * pl.NCO);
     a.nci = (sh.Ci + 32 * A - 1) / (32 * A);
+    pl.types = a.Z * a.nci * a.nco;
     const int XB = A * 32 * es, DB = pl.NCO * 32 * es;
     if (static_cast<long>(sh.D) * sh.H * sh.W * XB >= kAnyMaxSpan ||
         static_cast<long>(sh.Do) * sh.Ho * sh.Wo * DB >= kAnyMaxSpan)
         return false;
+    const int we = pl.NCO * pl.TPW * 16 * 64;
+    const int KS = 8 / (pl.G * A);
+    // one block per compute unit in all; every slot costs a write and a read
+    // of its partial sums.  No more slots than the scratch array of
+    // hexconv_bwd_noalloc holds (at k > 1 256 slots would take 80 MB of its
+    // 64), and no shape of which it holds not even one, so that this call
+    // takes every shape that the other kernels' workspaces allow.
+    const size_t slot = static_cast<size_t>(pl.types) * pl.G * A * we * 4;
+    if (slot > HEX_NOALLOC_SCRATCH_BYTES)
+        return false;
+    const int most = std::max(1, std::min(device_cus() / pl.types,
+                                          static_cast<int>(HEX_NOALLOC_SCRATCH_BYTES / slot)));
     const int cols = sh.W + 2 * K;
     a.WCs = (cols + a.s - 1) / a.s;
     // slots of 64 bytes: rows of a multiple of 4 keep the 256-byte phase of
     // consecutive columns when odd columns read one row further down
     a.WCs = (a.WCs + 3) & ~3;
     a.RP = a.s * a.WCs;
-    bool ok = false;
-    for (int TR = std::min(sh.Ho, std::max(1, 512 / sh.Wo)); TR >= 1 && !ok; --TR) {
+    bool found = false;
+    for (int TR = std::min(sh.Ho, std::max(1, 512 / sh.Wo)); TR >= 1; --TR) {
         const int tiles = (sh.Ho + TR - 1) / TR;
+        if (found && tiles == a.tiles)
+            continue; // the same rows per tile
         a.TR = (sh.Ho + tiles - 1) / tiles;
         a.tiles = tiles;
         a.rows = a.s * (a.TR - 1) + (sh.Wo > 1 ? a.s / 2 : 0) + 2 * K + 1;
@@ -494,18 +587,34 @@ bool plan_tile(const ConvShape &sh, Dtype d, int A, int U, WAnyPlan &pl)
         pl.lds = dyb + xb + static_cast<size_t>(a.npix) * 4;
         if (pl.lds > kAnyLds || ix > U * kWThreads || id > U * kWThreads)
             continue;
+        const long ntot = static_cast<long>(sh.N) * sh.Do * tiles;
+        if (ntot > (1L << 30))
+            break;
+        const int slots = static_cast<int>(std::min<long>(ntot, most));
+        const double cost = tile_cost(pl, d, ntot, slots, ix + id, pl.types, slot);
+        if (found && cost >= best.cost)
+            continue;
+        found = true;
         a.x_off = static_cast<int>(dyb);
         a.tab_off = static_cast<int>(dyb + xb);
-        ok = true;
+        a.ntot = static_cast<int>(ntot);
+        a.nslots = slots;
+        pl.ws = slot * slots;
+        pl.cost = cost;
+        best = pl;
+        // the pixel splits are added through LDS
+        if (KS > 1)
+            best.lds = std::max(best.lds, static_cast<size_t>(pl.G) * A * we * 4);
     }
-    if (!ok)
+    if (!found)
         return false;
+    WAnyArgs &b = best.a;
     int t = 0;
     for (int dq = -K; dq <= K; ++dq)
         for (int i = 0; i < col_len(K, dq); ++i, ++t) {
             const int c = K + dq;
-            a.toff[t] = ((col_ds_lo(K, dq) + i + floor_half(dq)) * a.RP + (c % a.s) * a.WCs +
-                         c / a.s) * XB;
+            b.toff[t] = ((col_ds_lo(K, dq) + i + floor_half(dq)) * b.RP + (c % b.s) * b.WCs +
+                         c / b.s) * XB;
         }
     return true;
 }
@@ -514,37 +623,14 @@ bool plan_wgrad(const ConvShape &sh, Dtype d, WAnyPlan &pl)
 {
     if (sh.k < 1 || sh.k > 3 || sh.Wo < (d == F32 ? 4 : 8) || sh.Ho < 1)
         return false;
-    // two input-channel tiles share the dy tile (at k = 3 the taps take
-    // every wave); bfloat16 with one item per thread where that holds a tile
-    const int A = (sh.Ci > 32 && sh.k < 3) ? 2 : 1;
+    // bfloat16: two input-channel tiles share the dy tile (at k = 3 the taps
+    // take every wave), and one item per thread where that holds a tile
+    const int A = (d != F32 && sh.Ci > 32 && sh.k < 3) ? 2 : 1;
     bool ok = false;
     for (int aa = A; aa >= 1 && !ok; --aa)
         for (int u = d == F32 ? 2 : 1; u <= 2 && !ok; ++u)
             ok = plan_tile(sh, d, aa, u, pl);
-    if (!ok)
-        return false;
-    WAnyArgs &a = pl.a;
-    const int KS = 8 / (pl.G * pl.A);
-    const int we = pl.NCO * pl.TPW * 16 * 64;
-    if (KS > 1)
-        pl.lds = std::max(pl.lds, static_cast<size_t>(pl.G) * pl.A * we * 4);
-    const long ntot = static_cast<long>(sh.N) * sh.Do * a.tiles;
-    if (ntot > (1L << 30))
-        return false;
-    a.ntot = static_cast<int>(ntot);
-    pl.types = a.Z * a.nci * a.nco;
-    // one block per compute unit in all; every slot costs a write and a read
-    // of its partial sums.  No more slots than the scratch array of
-    // hexconv_bwd_noalloc holds (at k > 1 256 slots would take 80 MB of its
-    // 64), and no shape of which it holds not even one, so that this call
-    // takes every shape that the other kernels' workspaces allow.
-    const size_t slot = static_cast<size_t>(pl.types) * pl.G * pl.A * we * 4;
-    if (slot > HEX_NOALLOC_SCRATCH_BYTES)
-        return false;
-    a.nslots = std::max(1, std::min({a.ntot, device_cus() / pl.types,
-                                     static_cast<int>(HEX_NOALLOC_SCRATCH_BYTES / slot)}));
-    pl.ws = slot * a.nslots;
-    return true;
+    return ok;
 }
 
 template <typename E, int K, int NCO, int A>
@@ -552,9 +638,10 @@ hipError_t launch_u(const WAnyPlan &pl, const void *x, const void *dy, float *pa
 {
     const dim3 grid(pl.types * pl.a.nslots), block(kWThreads);
     const E *xe = static_cast<const E *>(x), *de = static_cast<const E *>(dy);
-    // the next tile's items fit beside the sums except at 160 sums per lane
-    // (k > 1, two tiles of output channels) and at 128 registers of items
-    constexpr bool sums = K == 1 || NCO == 1;
+    // the next tile's items fit beside the sums except at 160 registers of
+    // sums (k > 1: bfloat16 with two tiles of output channels, float32) and at
+    // 128 registers of items
+    constexpr bool sums = K == 1 || (sizeof(E) == 2 && NCO == 1);
 #define HEX_WA(UV, PFV, MISV)                                                                \
     HEX_LAUNCH((wgrad_any_k<E, K, NCO, A, UV, PFV, MISV>), grid, block, pl.lds, st, xe, de,  \
                part, pl.a)
@@ -580,12 +667,19 @@ hipError_t launch_u(const WAnyPlan &pl, const void *x, const void *dy, float *pa
 template <typename E, int K>
 hipError_t launch_k(const WAnyPlan &pl, const void *x, const void *dy, float *part, hipStream_t st)
 {
-    if constexpr (K < 3)
-        if (pl.A == 2)
-            return pl.NCO == 2 ? launch_u<E, K, 2, 2>(pl, x, dy, part, st)
-                               : launch_u<E, K, 1, 2>(pl, x, dy, part, st);
-    return pl.NCO == 2 ? launch_u<E, K, 2, 1>(pl, x, dy, part, st)
-                       : launch_u<E, K, 1, 1>(pl, x, dy, part, st);
+    if constexpr (sizeof(E) == 4) {
+        if constexpr (K == 1)
+            if (pl.NCO == 2)
+                return launch_u<E, K, 2, 1>(pl, x, dy, part, st);
+        return launch_u<E, K, 1, 1>(pl, x, dy, part, st);
+    } else {
+        if constexpr (K < 3)
+            if (pl.A == 2)
+                return pl.NCO == 2 ? launch_u<E, K, 2, 2>(pl, x, dy, part, st)
+                                   : launch_u<E, K, 1, 2>(pl, x, dy, part, st);
+        return pl.NCO == 2 ? launch_u<E, K, 2, 1>(pl, x, dy, part, st)
+                           : launch_u<E, K, 1, 1>(pl, x, dy, part, st);
+    }
 }
 
 template <typename E>

@@ -7,10 +7,11 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_helpers import check, torch_mod
+from gpu_helpers import check, rel_l2, torch_mod
 from paper_1903_01814_amd import inputs as gen
 from test_parity3d_gpu import run_bwd_data3, run_bwd_weight3, run_fwd3
-from test_parity_gpu import check_bwd_full, check_fwd_full, run_pool_bwd, test_pool_sweep
+from test_parity_gpu import (check_bwd_full, check_fwd_full, run_bwd_weight, run_pool_bwd,
+                             test_pool_sweep)
 
 pytestmark = pytest.mark.gpu
 
@@ -75,6 +76,51 @@ def test_conv3d_any_shape(case, dt):
     mw, mb = oracle.conv3d_bwd_weight(a(x), a(dy), k, kz, s, sz)
     check(dt, dw, rw, mw, "dw")
     check(dt, db, rb, mb, "db")
+
+
+# Relative error of float32 sums whose terms are independent: a chain of n
+# additions is off by about 2.5e-8 sqrt(n / 2) (half an ulp at most each, of a
+# partial sum that grows as a random walk).  The weight gradients add chains of
+# 16 pixels, of 8 of these and of the run's (20 at most here): 1.3e-7 with the
+# slots' sums, and over the 40 and more values of db of all `runs` together a
+# fifth to either side (24 values alone: 0.8e-7 to 1.9e-7).  One chain over a block's run of tiles has hundreds
+# (1.8e-7 to 5.1e-7 in these cases).  A plane's part of the 3-D data gradient:
+# 84 terms here, 1.7e-7 with the three planes' sum (3.0e-7 in one chain).
+SUM_REL, PLANE_REL = 1.6e-7, 2.1e-7
+
+
+@pytest.mark.parametrize("case", [
+    # N, C_in, C_out, H, W, k, runs: the any-shape kernel, few channels, fused
+    (227, 4, 8, 41, 39, 2, 5), (60, 12, 64, 37, 41, 1, 1), (119, 3, 24, 37, 30, 1, 2),
+    (60, 2, 12, 37, 41, 2, 6)], ids=lambda c: "N%d_ci%d_co%d_%dx%d_k%d_runs%d" % c)
+def test_f32_weight_gradient_sums(case):
+    N, Ci, Co, H, W, k, runs = case
+    rng = np.random.default_rng(500 + sum(case[:6]))
+    got, ref = [], []
+    for _ in range(runs):
+        x = gen.round_to(np.exp(rng.normal(size=(N, Ci, H, W))) *
+                         (rng.uniform(size=(N, Ci, H, W)) < 0.1), "f32")
+        dy = gen.round_to(rng.normal(size=(N, Co, H, W)), "f32")
+        got.append(run_bwd_weight(x, dy, k, 1, "f32"))
+        ref.append(oracle.conv_bwd_weight(x, dy, k, 1))
+    err = [rel_l2(np.stack([g[i] for g in got]), np.stack([r[i] for r in ref])) for i in (0, 1)]
+    assert max(err) <= SUM_REL, err
+
+
+def test_f32_volume_sums():
+    rng = np.random.default_rng(600)
+    got, ref = [], []
+    for _ in range(5):
+        x = gen.round_to(rng.normal(size=(6, 8, 10, 33, 35)), "f32")
+        dy = gen.round_to(rng.normal(size=(6, 24, 10, 33, 35)), "f32")
+        got.append(run_bwd_weight3(x, dy, 1, 1, 1, 1, "f32"))
+        ref.append(oracle.conv3d_bwd_weight(x, dy, 1, 1, 1, 1))
+    err = [rel_l2(np.stack([g[i] for g in got]), np.stack([r[i] for r in ref])) for i in (0, 1)]
+    assert max(err) <= SUM_REL, err
+    w = gen.round_to(rng.normal(size=(12, 1, 3, 7)), "f32")
+    dx = run_bwd_data3(dy[:, :12], w, 1, 1, 1, 1, 10, 33, 35, "f32")
+    rx = oracle.conv3d_bwd_data(dy[:, :12], w, 1, 1, 1, 1, 10, 33, 35)
+    assert rel_l2(dx, rx) <= PLANE_REL, rel_l2(dx, rx)
 
 
 # Few input channels on rows that are no multiple of 4 (the last group of four
