@@ -62,6 +62,15 @@ __global__ __launch_bounds__(kMaxThreads3) void bwd_data3d_smallc_k(
     constexpr int T = num_taps(K);
     constexpr int Z = 2 * KZ + 1;
     constexpr int R = kR3;
+    // float32: a plane's part is summed by itself and then added to the ring,
+    // so that a chain has a third of the additions (dx of 1 -> 12 channels, 15
+    // volumes of 25 x 31 x 35, off the sum in 64 bits: generic kernel 2.6e-7,
+    // one chain 3.0e-7, now 1.7e-7).  bfloat16 results do not show it, and
+    // there it costs (39 volumes, 2 -> 16 channels, 23 x 41 x 31: 86, 101 us);
+    // nor where the weights of a channel are more than the scalar registers,
+    // whose spills it makes three times as many (31 volumes of 7 x 23 x 45,
+    // 2 -> 33 channels, k = 2, kz = 2: 405, 1911 us).
+    constexpr bool SPLIT = sizeof(TT) == sizeof(float) && CI * Z * T <= 100;
     static_assert(CI == 1 || CI == 2, "one or two input channels");
     extern __shared__ float ds3[];
     const int W = sh.W, H = sh.H, D = sh.D, Co = sh.Co;
@@ -147,21 +156,7 @@ __global__ __launch_bounds__(kMaxThreads3) void bwd_data3d_smallc_k(
         load_group(p, last ? d + 1 : d, last ? 0 : g + 1);
         const int c0 = g * CC, cn = min(CC, Co - c0);
         if (active) {
-            // float32: summed by themselves, then added to the ring, so that
-            // a chain has a third of the additions (dx of 1 -> 12 channels,
-            // 15 volumes of 25 x 31 x 35, off the sum in 64 bits: generic
-            // kernel 2.6e-7, one chain 3.0e-7, now 1.7e-7).  bfloat16 results
-            // do not show it, and there it costs (39 volumes, 2 -> 16
-            // channels, 23 x 41 x 31: 86, 101 us).
-            constexpr bool SPLIT = sizeof(TT) == sizeof(float);
-            float part[Z][CI][R];
-#pragma unroll
-            for (int s = 0; s < Z; ++s)
-#pragma unroll
-                for (int ci = 0; ci < CI; ++ci)
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-                        part[s][ci][r] = SPLIT ? 0.f : acc[s][ci][r];
+            float part[Z][CI][R] = {};
             // products of staged channel cl with its weights: wt(ci, m) is
             // value m of the Z T weights of (this output channel, ci)
             auto channel = [&](int cl, auto wt) __attribute__((always_inline)) {
@@ -188,7 +183,7 @@ __global__ __launch_bounds__(kMaxThreads3) void bwd_data3d_smallc_k(
                                     const float wv = wt(ci, s * T + (T - 1 - tr));
 #pragma unroll
                                     for (int r = 0; r < R; ++r)
-                                        part[s][ci][r] += wv * v[r + u];
+                                        (SPLIT ? part : acc)[s][ci][r] += wv * v[r + u];
                                 }
                             }
                         }
@@ -206,25 +201,32 @@ __global__ __launch_bounds__(kMaxThreads3) void bwd_data3d_smallc_k(
             } else {
                 // bfloat16: output channels in pairs from an even one (c0 is
                 // even), so that every weight is at a compile-time offset
-                // from an even element and needs no select
+                // from an even element and needs no select.  The two channels
+                // read from addresses of their own: joined, their weights
+                // outnumber the scalar registers (7 volumes of 10 x 26 x 32, 2
+                // -> 34 channels, k = 2, kz = 2: 541 us, spilling; now 410).
                 int cl = 0;
                 for (; cl + 1 < cn; cl += 2) {
                     const WEven<TT> we(w, static_cast<uint32_t>((c0 + cl) * L));
                     channel(cl, [&](int ci, int m) { return we(ci * Z * T + m); });
-                    channel(cl + 1, [&](int ci, int m) { return we(L + ci * Z * T + m); });
+                    __builtin_amdgcn_sched_barrier(0);
+                    const WEven<TT> wo(w, static_cast<uint32_t>((c0 + cl) * L));
+                    channel(cl + 1, [&](int ci, int m) { return wo(L + ci * Z * T + m); });
                 }
                 if (cl < cn) {
                     const WEven<TT> we(w, static_cast<uint32_t>((c0 + cl) * L));
                     channel(cl, [&](int ci, int m) { return we(ci * Z * T + m); });
                 }
             }
+            if constexpr (SPLIT) {
 #pragma unroll
-            for (int s = 0; s < Z; ++s)
+                for (int s = 0; s < Z; ++s)
 #pragma unroll
-                for (int ci = 0; ci < CI; ++ci)
+                    for (int ci = 0; ci < CI; ++ci)
 #pragma unroll
-                    for (int r = 0; r < R; ++r)
-                        acc[s][ci][r] = (SPLIT ? acc[s][ci][r] : 0.f) + part[s][ci][r];
+                        for (int r = 0; r < R; ++r)
+                            acc[s][ci][r] += part[s][ci][r];
+            }
         }
         if (last) {
             store_slot0(d - KZ);
