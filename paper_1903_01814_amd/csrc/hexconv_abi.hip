@@ -2,6 +2,7 @@
 // argument validation (host only, before anything is enqueued), choice of
 // kernel per shape regime, and launch-status mapping.
 #include <atomic>
+#include <math.h>
 #include <mutex>
 #include <stdint.h>
 #include <string>
@@ -92,6 +93,7 @@ namespace {
 
 using hexk::ConvShape;
 using hexk::Dtype;
+using hexk::Tried;
 
 constexpr long kMaxElems = (1L << 31) - 1; // per tensor, int32-indexable planes
 
@@ -186,11 +188,18 @@ bool force_generic()
     return v != nullptr && strcmp(v, "generic") == 0;
 }
 
-// Weight-gradient kernel family for a shape; the workspace query and the
-// call must agree, so both go through this choice.
+// Weight-gradient kernel family for a shape, its workspace and, for the
+// kernel for any shape, its plan; the workspace query and the call must
+// agree, so both go through this choice.
 enum class WgradPath { Generic, Fused, Small, Bf16Mfma32, Bf16Mfma, Any };
 
-WgradPath wgrad_path(const ConvShape &sh, Dtype d)
+struct WgradPick {
+    WgradPath path = WgradPath::Generic;
+    size_t ws = 0;
+    hexk::WAnyPlan any;
+};
+
+WgradPath wgrad_path(const ConvShape &sh, Dtype d, hexk::WAnyPlan &any)
 {
     if (force_generic())
         return WgradPath::Generic;
@@ -201,63 +210,139 @@ WgradPath wgrad_path(const ConvShape &sh, Dtype d)
     if (hexk::smallc_bwd_fused_ok(sh, d))
         return WgradPath::Fused;
     const bool small = hexk::smallc_wgrad_ok(sh);
-    const WgradPath rest = small                        ? WgradPath::Small
-                           : hexk::wgrad_any_ok(sh, d) ? WgradPath::Any
-                                                        : WgradPath::Generic;
-    if (d == hexk::F32)
-        return rest;
-    // bf16 with few input channels: the small-channel kernel stages x once
-    // per 16 output channels, so it wins only for one such block at k <= 2
-    // (1 -> 16 channels, 40x40, N = 256: 27 -> 18 us at k = 1, 26 -> 23 us
-    // at k = 2; 32 or 64 output channels and k = 3 favour the bf16 kernels)
-    if (small && sh.Co <= 16 && sh.k <= 2)
+    // few channels on rows of whole 4-column groups: float32 (43 shapes, all
+    // faster than generic); bf16, for which the small-channel kernel stages x
+    // once per 16 output channels, with one such block at k <= 2 (1 -> 16
+    // channels, 40x40, N = 256: 27 -> 18 us at k = 1, 26 -> 23 us at k = 2; 32
+    // or 64 output channels and k = 3 favour the bf16 kernels)
+    if (small && sh.W % 4 == 0 && (d == hexk::F32 || (sh.Co <= 16 && sh.k <= 2)))
         return WgradPath::Small;
-    // one pass of the tuned kernel (64 -> 64 channels, 128 x 128, N = 64: 98 us
-    // against 149 on the kernel for any shape); several passes re-read x, and
-    // the kernel for any shape wins (64 -> 128 channels, 12 x 12, N = 512: 59 ->
-    // 35 us; 64 -> 96, 45 x 48, N = 96: 114 -> 56), as it does at strides above
-    // 1 and k = 3 (64 -> 64, 128 x 128: stride 2 171 -> 84, k = 3 223 -> 125)
-    const int passes = hexk::bf16_wgrad32_passes(sh);
-    if (passes == 1)
+    int passes = 0;
+    if (d == hexk::BF16) {
+        // one pass of the tuned kernel (64 -> 64 channels, 128 x 128, N = 64:
+        // 98 us against 149 on the kernel for any shape); several passes
+        // re-read x, and the kernel for any shape wins (64 -> 128 channels, 12
+        // x 12, N = 512: 59 -> 35 us; 64 -> 96, 45 x 48, N = 96: 114 -> 56)
+        passes = hexk::bf16_wgrad32_passes(sh);
+        if (passes == 1)
+            return WgradPath::Bf16Mfma32;
+    }
+    // else the bf16 kernel for whole 16-byte rows, the small-channel kernel on
+    // rows of whole 4-column groups or the generic one, unless the estimates
+    // put another kernel clearly below it
+    const bool mfma = d == hexk::BF16 && hexk::bf16_wgrad_ok(sh);
+    WgradPath best = WgradPath::Generic;
+    double us = hexk::wgrad_generic_us(sh, d);
+    const auto offer = [&](WgradPath path, double t) {
+        if (t < us) {
+            us = t;
+            best = path;
+        }
+    };
+    if (mfma) {
+        const double t = hexk::bf16_wgrad_us(sh) * hexk::kClearly;
+        offer(WgradPath::Bf16Mfma, t);
+    } else if (small && sh.W % 4 == 0) {
+        best = WgradPath::Small;
+        us = hexk::smallc_wgrad_us(sh, d) * hexk::kClearly;
+    } else {
+        us *= hexk::kClearly;
+        if (small)
+            offer(WgradPath::Small, hexk::smallc_wgrad_us(sh, d));
+    }
+    if (hexk::wgrad_any_plan(sh, d, any))
+        offer(WgradPath::Any, any.us);
+    else if (passes > 1 && !mfma)
         return WgradPath::Bf16Mfma32;
-    if (hexk::wgrad_any_ok(sh, d))
-        return WgradPath::Any;
-    if (passes > 1 && !hexk::bf16_wgrad_ok(sh))
-        return WgradPath::Bf16Mfma32;
-    if (hexk::bf16_wgrad_ok(sh))
-        return WgradPath::Bf16Mfma;
-    return rest;
+    return best;
 }
 
-// Fused data + weight gradient (hexconv_bwd) for this shape?
-bool bwd_fused(const ConvShape &sh, Dtype d)
+WgradPick wgrad_pick(const ConvShape &sh, Dtype d)
 {
-    return !force_generic() && hexk::smallc_bwd_fused_ok(sh, d);
-}
-
-size_t wgrad_workspace(const ConvShape &sh, Dtype d)
-{
-    switch (wgrad_path(sh, d)) {
+    WgradPick p;
+    p.path = wgrad_path(sh, d, p.any);
+    switch (p.path) {
     case WgradPath::Fused:
-        return hexk::smallc_bwd_fused_workspace(sh);
+        p.ws = hexk::smallc_bwd_fused_workspace(sh);
+        break;
     case WgradPath::Small:
-        return hexk::smallc_wgrad_workspace(sh);
+        p.ws = hexk::smallc_wgrad_workspace(sh);
+        break;
     case WgradPath::Bf16Mfma32:
-        return hexk::bf16_wgrad32_workspace(sh);
+        p.ws = hexk::bf16_wgrad32_workspace(sh);
+        break;
     case WgradPath::Bf16Mfma:
-        return hexk::bf16_wgrad_workspace(sh);
+        p.ws = hexk::bf16_wgrad_workspace(sh);
+        break;
     case WgradPath::Any:
-        return hexk::wgrad_any_workspace(sh, d);
+        p.ws = p.any.ws;
+        break;
     default:
-        return hexk::wgrad_generic_workspace(sh);
+        p.ws = hexk::wgrad_generic_workspace(sh);
+    }
+    return p;
+}
+
+// 3-D weight gradient: the small-channel kernel with the planes around each
+// output plane staged as channels (on rows of whole 4-column groups always),
+// the matrix-core kernel for any size or the generic one, by their estimates
+WgradPick wgrad3d_pick(const ConvShape &sh, Dtype d)
+{
+    WgradPick p;
+    p.ws = hexk::wgrad_generic_workspace(sh);
+    if (force_generic())
+        return p;
+    const double us = hexk::wgrad_generic_us(sh, d) * hexk::kClearly;
+    if (hexk::smallc_wgrad_ok(sh)) {
+        if (sh.W % 4 == 0 || hexk::smallc_wgrad_us(sh, d) < us) {
+            p.path = WgradPath::Small;
+            p.ws = hexk::smallc_wgrad_workspace(sh);
+        }
+        return p;
+    }
+    if (hexk::wgrad_any_plan(sh, d, p.any) && p.any.us < us) {
+        p.path = WgradPath::Any;
+        p.ws = p.any.ws;
+    }
+    return p;
+}
+
+hipError_t wgrad_run(const WgradPick &p, const void *x, const void *dy, float *dw, float *db,
+                     void *ws, const ConvShape &sh, Dtype d, hipStream_t st)
+{
+    switch (p.path) {
+    case WgradPath::Fused: // no data gradient: w is not read
+        return hexk::smallc_bwd_fused(x, dy, nullptr, nullptr, dw, db, ws, sh, d, st);
+    case WgradPath::Small:
+        return hexk::smallc_wgrad(x, dy, dw, db, ws, sh, d, st);
+    case WgradPath::Bf16Mfma32:
+        return hexk::bf16_wgrad32(x, dy, dw, db, ws, sh, st);
+    case WgradPath::Bf16Mfma:
+        return hexk::bf16_wgrad(x, dy, dw, db, ws, sh, st);
+    case WgradPath::Any:
+        return hexk::wgrad_any(x, dy, dw, db, ws, sh, d, p.any, st);
+    default:
+        return hexk::wgrad_generic(x, dy, dw, db, ws, sh, d, st);
     }
 }
 
+// Estimated time of the generic forward / data gradient, where it runs at all.
+double fwd_generic_us(const ConvShape &sh, Dtype d)
+{
+    return hexk::conv_fwd_generic_ok(sh) ? hexk::conv_fwd_generic_us(sh, d) : HUGE_VAL;
+}
+
+double bwd_data_generic_us(const ConvShape &sh, Dtype d)
+{
+    return hexk::conv_bwd_data_generic_ok(sh) ? hexk::conv_bwd_data_generic_us(sh, d) : HUGE_VAL;
+}
+
 // Every check of hexconv_bwd's arguments but the workspace, so that a bad
-// argument enqueues nothing; `need` receives the workspace bytes.
+// argument enqueues nothing; `pick` receives the weight-gradient kernel and
+// its workspace (none for an empty batch).
 int bwd_check(const void *x, const void *dy, const void *w, const void *dx, const float *dw,
               const float *db, int N, int Ci, int Co, int H, int W, int k, int stride, int dt,
-              ConvShape &sh, size_t &need)
+              ConvShape &sh, WgradPick &pick)
 {
     int rc = check_shape(N, Ci, Co, H, W, k, stride, dt, sh);
     if (rc != HEX_OK)
@@ -269,9 +354,8 @@ int bwd_check(const void *x, const void *dy, const void *w, const void *dx, cons
         return HEX_ERR_INVALID_ARG;
     if (dx != nullptr && w == nullptr)
         return HEX_ERR_INVALID_ARG;
-    const Dtype d = static_cast<Dtype>(dt);
-    need = empty ? 0
-                 : (bwd_fused(sh, d) ? hexk::smallc_bwd_fused_workspace(sh) : wgrad_workspace(sh, d));
+    if (!empty)
+        pick = wgrad_pick(sh, static_cast<Dtype>(dt));
     return HEX_OK;
 }
 
@@ -366,18 +450,23 @@ int hexconv_fwd(const void *x, const void *w, const void *bias, void *y, int N, 
     if (!force_generic()) {
         if (hexk::smallc_fwd_ok(sh))
             return launched(hexk::smallc_fwd(x, w, bias, y, sh, d, relu, st));
-        // bf16: the tuned stride-1 kernels where they win, then the kernel for
-        // any shape; the others only where that one's window does not fit
+        // the tuned bf16 stride-1 kernels where they win, then the kernels
+        // for any shape or, where the work is little, the generic one; the
+        // other bf16 kernels only where the any-shape window does not fit
         const bool wide = d == hexk::BF16 && hexk::bf16_wide_ok(sh, sh.Ci, sh.Co);
         if (wide && hexk::bf16_wide_first(sh, sh.Ci, sh.Co, false))
             return launched(hexk::bf16_wide_conv(x, w, bias, y, sh, false, relu, st));
-        if (d == hexk::F32 && hexk::conv_f32_fwd_ok(sh))
-            return launched(hexk::conv_f32_fwd(x, w, bias, y, sh, relu, st));
-        if (d == hexk::BF16 && hexk::conv_any_ok(sh, d, false))
-            return launched(hexk::conv_any(x, w, bias, y, sh, d, false, relu, st));
-        if (wide)
+        hipError_t e = hipSuccess;
+        const bool strided = d == hexk::BF16 && hexk::bf16_gen_fwd_ok(sh);
+        const double other = wide || strided ? HUGE_VAL : fwd_generic_us(sh, d);
+        const Tried t = d == hexk::F32
+                            ? hexk::conv_f32_fwd(x, w, bias, y, sh, relu, st, other, e)
+                            : hexk::conv_any(x, w, bias, y, sh, d, false, relu, st, other, e);
+        if (t == Tried::Ran)
+            return launched(e);
+        if (wide && t == Tried::No)
             return launched(hexk::bf16_wide_conv(x, w, bias, y, sh, false, relu, st));
-        if (d == hexk::BF16 && hexk::bf16_gen_fwd_ok(sh))
+        if (strided)
             return launched(hexk::bf16_gen_fwd(x, w, bias, y, sh, relu, st));
     }
     if (!hexk::conv_fwd_generic_ok(sh))
@@ -401,23 +490,35 @@ int hexconv_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in, i
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Dtype d = static_cast<Dtype>(dt);
     if (!force_generic() && sh.Ho > 0) {
-        // bf16 on the matrix cores first (64 images of 41 x 43, 4 -> 32
-        // channels, k = 1: 52 us on the small-channel kernel, whose fp32
-        // arithmetic runs on the vector units, 10 us here; 1 -> 8: 9.2 and
-        // 8.0), by the tuned kernels where they win
+        // bf16 on the matrix cores, by the tuned kernels where they win, unless
+        // the work is little (64 images of 41 x 43, 4 -> 32 channels, k = 1:
+        // 52 us on the small-channel kernel, whose fp32 arithmetic runs on
+        // the vector units, 10 us here; 170 of 46 x 18, 5 -> 2: 8.6 on the
+        // generic one, 13.4); fp32 of few channels on the vector units first
         const bool wide = d == hexk::BF16 && hexk::bf16_wide_ok(sh, sh.Co, sh.Ci);
         if (wide && hexk::bf16_wide_first(sh, sh.Co, sh.Ci, true))
             return launched(hexk::bf16_wide_conv(dy, w, nullptr, dx, sh, true, false, st));
-        const bool any = hexk::conv_any_ok(sh, d, true);
-        if (d == hexk::BF16 && any)
-            return launched(hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st));
-        if (wide)
-            return launched(hexk::bf16_wide_conv(dy, w, nullptr, dx, sh, true, false, st));
-        if (hexk::smallc_bwd_data_ok(sh))
+        const bool small = hexk::smallc_bwd_data_ok(sh);
+        if (small && d == hexk::F32)
             return launched(hexk::smallc_bwd_data(dy, w, dx, sh, d, st));
-        if (any)
-            return launched(hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st));
-        if (d == hexk::BF16 && hexk::bf16_gen_dgrad_ok(sh))
+        hipError_t e = hipSuccess;
+        // bf16 on rows of whole 16-byte vectors: one walk over dy for all
+        // classes of pixels is the faster one for many output channels (3 ->
+        // 192 channels, 112 x 96, N = 2, k = 1, stride 2: 23 us, 50 here; 128
+        // -> 96, 64 x 80, N = 9, k = 2: 112, 56)
+        const bool strided = d == hexk::BF16 && !small && hexk::bf16_gen_dgrad_ok(sh);
+        const double other = wide      ? HUGE_VAL
+                             : small   ? hexk::smallc_bwd_data_us(sh)
+                             : strided ? hexk::bf16_gen_dgrad_us(sh)
+                                       : bwd_data_generic_us(sh, d);
+        const Tried t = hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st, other, e);
+        if (t == Tried::Ran)
+            return launched(e);
+        if (wide && t == Tried::No)
+            return launched(hexk::bf16_wide_conv(dy, w, nullptr, dx, sh, true, false, st));
+        if (small)
+            return launched(hexk::smallc_bwd_data(dy, w, dx, sh, d, st));
+        if (strided)
             return launched(hexk::bf16_gen_dgrad(dy, w, dx, sh, st));
     }
     if (!hexk::conv_bwd_data_generic_ok(sh))
@@ -433,7 +534,7 @@ size_t hexconv_bwd_weight_workspace(int N, int C_in, int C_out, int H, int W, in
         return 0;
     if (N == 0 || sh.Ho == 0)
         return 0;
-    return wgrad_workspace(sh, static_cast<Dtype>(dt));
+    return wgrad_pick(sh, static_cast<Dtype>(dt)).ws;
 }
 
 int hexconv_bwd_weight(const void *x, const void *dy, float *dw, float *db, void *ws,
@@ -450,26 +551,15 @@ int hexconv_bwd_weight(const void *x, const void *dy, float *dw, float *db, void
     if (!empty && (x == nullptr || dy == nullptr))
         return HEX_ERR_INVALID_ARG;
     const Dtype d = static_cast<Dtype>(dt);
-    const size_t need = empty ? 0 : wgrad_workspace(sh, d);
-    if (need > 0 && (ws == nullptr || ws_bytes < need))
+    WgradPick pick;
+    if (!empty)
+        pick = wgrad_pick(sh, d);
+    if (pick.ws > 0 && (ws == nullptr || ws_bytes < pick.ws))
         return HEX_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (empty)
         return launched(hexk::fill_zero_f32(dw, db, sh, st));
-    switch (wgrad_path(sh, d)) {
-    case WgradPath::Fused: // no data gradient: w is not read
-        return launched(hexk::smallc_bwd_fused(x, dy, nullptr, nullptr, dw, db, ws, sh, d, st));
-    case WgradPath::Small:
-        return launched(hexk::smallc_wgrad(x, dy, dw, db, ws, sh, d, st));
-    case WgradPath::Bf16Mfma32:
-        return launched(hexk::bf16_wgrad32(x, dy, dw, db, ws, sh, st));
-    case WgradPath::Bf16Mfma:
-        return launched(hexk::bf16_wgrad(x, dy, dw, db, ws, sh, st));
-    case WgradPath::Any:
-        return launched(hexk::wgrad_any(x, dy, dw, db, ws, sh, d, st));
-    default:
-        return launched(hexk::wgrad_generic(x, dy, dw, db, ws, sh, d, st));
-    }
+    return launched(wgrad_run(pick, x, dy, dw, db, ws, sh, d, st));
 }
 
 size_t hexconv_bwd_workspace(int N, int C_in, int C_out, int H, int W, int k, int stride,
@@ -480,19 +570,17 @@ size_t hexconv_bwd_workspace(int N, int C_in, int C_out, int H, int W, int k, in
         return 0;
     if (N == 0 || sh.Ho == 0)
         return 0;
-    const Dtype d = static_cast<Dtype>(dt);
-    return bwd_fused(sh, d) ? hexk::smallc_bwd_fused_workspace(sh) : wgrad_workspace(sh, d);
+    return wgrad_pick(sh, static_cast<Dtype>(dt)).ws;
 }
 
-// hexconv_bwd after its checks: ws holds at least the workspace the shape
-// needs (ws_bytes of it).
-static int bwd_run(const void *x, const void *dy, const void *w, void *dx, float *dw, float *db,
-                   void *ws, size_t ws_bytes, const ConvShape &sh, hex_dtype dt, void *stream)
+// hexconv_bwd after its checks: ws holds at least pick.ws bytes.
+static int bwd_run(const WgradPick &pick, const void *x, const void *dy, const void *w, void *dx,
+                   float *dw, float *db, void *ws, const ConvShape &sh, hex_dtype dt, void *stream)
 {
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Dtype d = static_cast<Dtype>(dt);
     const bool empty = (sh.N == 0 || sh.Ho == 0);
-    if (!empty && bwd_fused(sh, d))
+    if (!empty && pick.path == WgradPath::Fused)
         return launched(hexk::smallc_bwd_fused(x, dy, w, dx, dw, db, ws, sh, d, st));
     if (dx != nullptr && sh.N > 0) {
         const int rc = hexconv_bwd_data(dy, w, dx, sh.N, sh.Ci, sh.Co, sh.H, sh.W, sh.k, sh.s, dt,
@@ -500,8 +588,9 @@ static int bwd_run(const void *x, const void *dy, const void *w, void *dx, float
         if (rc != HEX_OK)
             return rc;
     }
-    return hexconv_bwd_weight(x, dy, dw, db, ws, ws_bytes, sh.N, sh.Ci, sh.Co, sh.H, sh.W, sh.k,
-                              sh.s, dt, stream);
+    if (empty)
+        return launched(hexk::fill_zero_f32(dw, db, sh, st));
+    return launched(wgrad_run(pick, x, dy, dw, db, ws, sh, d, st));
 }
 
 int hexconv_bwd(const void *x, const void *dy, const void *w, void *dx, float *dw, float *db,
@@ -509,15 +598,15 @@ int hexconv_bwd(const void *x, const void *dy, const void *w, void *dx, float *d
                 int stride, hex_dtype dt, void *stream)
 {
     ConvShape sh;
-    size_t need = 0;
-    int rc = bwd_check(x, dy, w, dx, dw, db, N, C_in, C_out, H, W, k, stride, dt, sh, need);
+    WgradPick pick;
+    int rc = bwd_check(x, dy, w, dx, dw, db, N, C_in, C_out, H, W, k, stride, dt, sh, pick);
     if (rc != HEX_OK)
         return rc;
     if ((rc = ptrs_ok({}, {ws})) != HEX_OK)
         return rc;
-    if (need > 0 && (ws == nullptr || ws_bytes < need))
+    if (pick.ws > 0 && (ws == nullptr || ws_bytes < pick.ws))
         return HEX_ERR_INVALID_ARG;
-    return bwd_run(x, dy, w, dx, dw, db, ws, ws_bytes, sh, dt, stream);
+    return bwd_run(pick, x, dy, w, dx, dw, db, ws, sh, dt, stream);
 }
 
 int hexconv_bwd_noalloc(const void *x, const void *dy, const void *w, void *dx, float *dw,
@@ -525,17 +614,16 @@ int hexconv_bwd_noalloc(const void *x, const void *dy, const void *w, void *dx, 
                         hex_dtype dt, void *stream)
 {
     ConvShape sh;
-    size_t need = 0;
-    int rc = bwd_check(x, dy, w, dx, dw, db, N, C_in, C_out, H, W, k, stride, dt, sh, need);
+    WgradPick pick;
+    int rc = bwd_check(x, dy, w, dx, dw, db, N, C_in, C_out, H, W, k, stride, dt, sh, pick);
     if (rc != HEX_OK)
         return rc;
-    if (need > HEX_NOALLOC_SCRATCH_BYTES)
+    if (pick.ws > HEX_NOALLOC_SCRATCH_BYTES)
         return HEX_ERR_UNSUPPORTED;
     void *ws = nullptr;
-    if (need > 0 && (ws = scratch_ptr()) == nullptr)
+    if (pick.ws > 0 && (ws = scratch_ptr()) == nullptr)
         return HEX_ERR_LAUNCH;
-    return bwd_run(x, dy, w, dx, dw, db, ws, need > 0 ? HEX_NOALLOC_SCRATCH_BYTES : 0, sh, dt,
-                   stream);
+    return bwd_run(pick, x, dy, w, dx, dw, db, ws, sh, dt, stream);
 }
 
 int hexpool_fwd(const void *x, void *y, uint8_t *argmax_tap, int N, int C, int H, int W, int k,
@@ -582,11 +670,17 @@ int hexpool_bwd(const void *dy, const uint8_t *argmax_tap, const void *relu_y, v
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Dtype d = static_cast<Dtype>(dt);
     // The mean's gradient at stride 1 gathers (512 x 32 planes of 48 x 48,
-    // bf16, k = 1: 228 -> 113 us, k = 2: 1306 -> 218; 64 x 64 of 40 x 40: 25 ->
-    // 27 and 70 -> 49), and so does the one-tap pool; every other shape of
-    // whole rows is at least as fast by phases (stride 2, max, 256 x 64 of
-    // 40 x 40: 21 us against 28).
-    if (!force_generic() && sh.Ho > 0 && mode == HEX_POOL_AVG && sh.s == 1 &&
+    // bf16, k = 2: 1306 -> 218 us), and so does the one-tap pool.  At k = 1 by
+    // phases it is the faster where a block holds a few outputs per thread
+    // (160 shapes, with a mask: planes of up to 1024 pixels 0.73 to 1.06 times
+    // the gather's time, larger ones 0.82 to 1.08), but for small calls of
+    // more than 1024 pixels a plane (1.0 to 1.38) and past 2048 (1.3 to 1.95;
+    // 512 x 32 of 48 x 48 228 -> 113 us).  Every other shape of whole rows is
+    // at least as fast by phases (stride 2, max, 256 x 64 of 40 x 40: 21 us
+    // against 28).
+    const long hw = static_cast<long>(sh.H) * sh.W;
+    const bool gather = sh.k != 1 || hw > 2048 || (hw > 1024 && hw * sh.N * sh.Ci <= 3L << 20);
+    if (!force_generic() && sh.Ho > 0 && mode == HEX_POOL_AVG && sh.s == 1 && gather &&
         hexk::pool_any_ok(sh, d, false, true, mode))
         return launched(hexk::pool_any_bwd(dy, argmax_tap, relu_y, dx, sh, mode, d, false, st));
     if (!force_generic() && sh.Ho > 0 && hexk::pool_fast_ok(sh, d))
@@ -627,24 +721,25 @@ int hexconv3d_fwd(const void *x, const void *w, const void *bias, void *y, int N
         return rc;
     if (sh.Ho == 0)
         return HEX_OK;
-    // few input channels: the small-channel forward with the 2kz + 1 planes
-    // around each output plane staged as extra input channels
-    if (!force_generic() && hexk::smallc_fwd_ok(sh))
-        return launched(hexk::smallc_fwd(x, w, bias, y, sh, static_cast<Dtype>(dt),
-                                         (flags & HEX_FLAG_RELU) != 0,
-                                         static_cast<hipStream_t>(stream)));
-    if (!force_generic() && dt == HEX_F32 && hexk::conv_f32_fwd_ok(sh))
-        return launched(hexk::conv_f32_fwd(x, w, bias, y, sh, (flags & HEX_FLAG_RELU) != 0,
-                                       static_cast<hipStream_t>(stream)));
-    if (!force_generic() && dt == HEX_BF16 && hexk::conv_any_ok(sh, static_cast<Dtype>(dt), false))
-        return launched(hexk::conv_any(x, w, bias, y, sh, static_cast<Dtype>(dt), false,
-                                       (flags & HEX_FLAG_RELU) != 0,
-                                       static_cast<hipStream_t>(stream)));
+    const Dtype d = static_cast<Dtype>(dt);
+    const bool relu = (flags & HEX_FLAG_RELU) != 0;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (!force_generic()) {
+        // few input channels: the small-channel forward with the 2kz + 1
+        // planes around each output plane staged as extra input channels
+        if (hexk::smallc_fwd_ok(sh))
+            return launched(hexk::smallc_fwd(x, w, bias, y, sh, d, relu, st));
+        hipError_t e = hipSuccess;
+        const double gen = fwd_generic_us(sh, d);
+        const Tried t = d == hexk::F32
+                            ? hexk::conv_f32_fwd(x, w, bias, y, sh, relu, st, gen, e)
+                            : hexk::conv_any(x, w, bias, y, sh, d, false, relu, st, gen, e);
+        if (t == Tried::Ran)
+            return launched(e);
+    }
     if (!hexk::conv_fwd_generic_ok(sh))
         return HEX_ERR_UNSUPPORTED;
-    return launched(hexk::conv_fwd_generic(x, w, bias, y, sh, static_cast<Dtype>(dt),
-                                           (flags & HEX_FLAG_RELU) != 0,
-                                           static_cast<hipStream_t>(stream)));
+    return launched(hexk::conv_fwd_generic(x, w, bias, y, sh, d, relu, st));
 }
 
 int hexconv3d_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in, int C_out, int D,
@@ -661,43 +756,20 @@ int hexconv3d_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in,
         return rc;
     if (dy == nullptr && sh.Ho > 0)
         return HEX_ERR_INVALID_ARG;
-    if (!force_generic() && sh.Ho > 0 && hexk::smallc3d_bwd_data_ok(sh))
-        return launched(hexk::smallc3d_bwd_data(dy, w, dx, sh, static_cast<Dtype>(dt),
-                                                static_cast<hipStream_t>(stream)));
-    if (!force_generic() && hexk::conv_any_ok(sh, static_cast<Dtype>(dt), true))
-        return launched(hexk::conv_any(dy, w, nullptr, dx, sh, static_cast<Dtype>(dt), true,
-                                       false, static_cast<hipStream_t>(stream)));
+    const Dtype d = static_cast<Dtype>(dt);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (!force_generic() && sh.Ho > 0) {
+        if (hexk::smallc3d_bwd_data_ok(sh))
+            return launched(hexk::smallc3d_bwd_data(dy, w, dx, sh, d, st));
+        hipError_t e = hipSuccess;
+        if (hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st, bwd_data_generic_us(sh, d),
+                           e) == Tried::Ran)
+            return launched(e);
+    }
     if (!hexk::conv_bwd_data_generic_ok(sh))
         return HEX_ERR_UNSUPPORTED;
-    return launched(hexk::conv_bwd_data_generic(dy, w, dx, sh, static_cast<Dtype>(dt),
-                                                static_cast<hipStream_t>(stream)));
+    return launched(hexk::conv_bwd_data_generic(dy, w, dx, sh, d, st));
 }
-
-namespace {
-// 3-D weight gradient: the small-channel kernel with the planes around each
-// output plane staged as channels where it applies, then the matrix-core
-// kernel for any size, else the generic one
-WgradPath wgrad3d_path(const ConvShape &sh, Dtype d)
-{
-    if (force_generic())
-        return WgradPath::Generic;
-    if (hexk::smallc_wgrad_ok(sh))
-        return WgradPath::Small;
-    return hexk::wgrad_any_ok(sh, d) ? WgradPath::Any : WgradPath::Generic;
-}
-
-size_t wgrad3d_workspace(const ConvShape &sh, Dtype d)
-{
-    switch (wgrad3d_path(sh, d)) {
-    case WgradPath::Small:
-        return hexk::smallc_wgrad_workspace(sh);
-    case WgradPath::Any:
-        return hexk::wgrad_any_workspace(sh, d);
-    default:
-        return hexk::wgrad_generic_workspace(sh);
-    }
-}
-} // namespace
 
 size_t hexconv3d_bwd_weight_workspace(int N, int C_in, int C_out, int D, int H, int W, int k,
                                       int kz, int stride, int stride_z, hex_dtype dt)
@@ -707,7 +779,7 @@ size_t hexconv3d_bwd_weight_workspace(int N, int C_in, int C_out, int D, int H, 
         return 0;
     if (N == 0 || sh.Ho == 0)
         return 0;
-    return wgrad3d_workspace(sh, static_cast<Dtype>(dt));
+    return wgrad3d_pick(sh, static_cast<Dtype>(dt)).ws;
 }
 
 int hexconv3d_bwd_weight(const void *x, const void *dy, float *dw, float *db, void *ws,
@@ -723,21 +795,16 @@ int hexconv3d_bwd_weight(const void *x, const void *dy, float *dw, float *db, vo
     const bool empty = (N == 0 || sh.Ho == 0);
     if (!empty && (x == nullptr || dy == nullptr))
         return HEX_ERR_INVALID_ARG;
-    const size_t need = empty ? 0 : wgrad3d_workspace(sh, static_cast<Dtype>(dt));
-    if (need > 0 && (ws == nullptr || ws_bytes < need))
+    const Dtype d = static_cast<Dtype>(dt);
+    WgradPick pick;
+    if (!empty)
+        pick = wgrad3d_pick(sh, d);
+    if (pick.ws > 0 && (ws == nullptr || ws_bytes < pick.ws))
         return HEX_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (empty)
         return launched(hexk::fill_zero_f32(dw, db, sh, st));
-    const Dtype d = static_cast<Dtype>(dt);
-    switch (wgrad3d_path(sh, d)) {
-    case WgradPath::Small:
-        return launched(hexk::smallc_wgrad(x, dy, dw, db, ws, sh, d, st));
-    case WgradPath::Any:
-        return launched(hexk::wgrad_any(x, dy, dw, db, ws, sh, d, st));
-    default:
-        return launched(hexk::wgrad_generic(x, dy, dw, db, ws, sh, d, st));
-    }
+    return launched(wgrad_run(pick, x, dy, dw, db, ws, sh, d, st));
 }
 
 int hexpool3d_fwd(const void *x, void *y, uint16_t *argmax, int N, int C, int D, int H, int W,

@@ -31,6 +31,7 @@
 // channel and instruction; bfloat16 results go through LDS, one 32-channel
 // tile at a time, and leave as 16-byte vectors.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "chanlast.h"
@@ -655,55 +656,44 @@ struct AnyPlan {
     double cost;
 };
 
-// Tile of TR rows at NT x MG; false if it does not fit.  The cost counts, in
-// clocks of a compute unit, the rounds of tiles times products (or the LDS
-// reads that feed them, about 6.5 clocks per 16-byte wave read), staging and
-// results.
-bool plan_tile(const ConvShape &sh, Dtype d, bool dgrad, int NT, int MG, AnyPlan &pl)
+// Tile of TR rows at NT x MG (of plan_any's `pl`, which holds the rest); false
+// if it does not fit.  The cost counts, in clocks of a compute unit, the
+// rounds of tiles times products (or the LDS reads that feed them, about 6.5
+// clocks per 16-byte wave read), staging and results.
+bool plan_tile(const ConvShape &sh, Dtype d, int cus, AnyPlan &pl)
 {
-    const int es = d == F32 ? 4 : 2, PX = 16 / es, CK = 64 / es;
-    const int K = sh.k, T = sh.T;
+    const int es = d == F32 ? 4 : 2, PX = 16 / es;
+    const int K = sh.k, T = sh.T, NT = pl.NT, MG = pl.MG;
     AnyArgs &a = pl.a;
-    a = AnyArgs{};
-    a.Cs = dgrad ? sh.Co : sh.Ci;
-    a.Cd = dgrad ? sh.Ci : sh.Co;
-    a.Ds = dgrad ? sh.Do : sh.D;
-    a.Hs = dgrad ? sh.Ho : sh.H;
-    a.Ws = dgrad ? sh.Wo : sh.W;
-    a.Dd = dgrad ? sh.D : sh.Do;
-    a.Hd = dgrad ? sh.H : sh.Ho;
-    a.Wd = dgrad ? sh.W : sh.Wo;
-    a.s = sh.s;
-    a.sz = sh.sz;
-    a.kz = sh.kz;
-    a.Z = sh.Z;
-    a.J = sh.Z * T;
-    a.sD = dgrad ? a.J : sh.Ci * a.J;
-    a.sS = dgrad ? sh.Ci * a.J : a.J;
-    a.reflect = dgrad;
-    if (static_cast<long>(a.Ds) * a.Hs * a.Ws * CK * es >= kAnyMaxSpan)
-        return false;
     const int NB = 32 * NT, WT = NB * 64 + 16;
     const int maxM = 32 * kAWaves * MG;
     if (a.Wd > maxM)
         return false;
-    a.nch = (a.Cs + CK - 1) / CK;
     a.nblk = (a.Cd + NB - 1) / NB;
-    const int cols = a.Ws + 2 * K;
+    const int per = (a.Ws + 2 * K + a.s - 1) / a.s; // slots per class of columns
     const int Q = a.Z * a.nch;
     const size_t wchunk = static_cast<size_t>(T) * WT;
+    // three tiles of channels leave no registers for two items of two groups
+    const int most = NT == 3 && MG == 2 ? 1 : 2;
+    // the rows that the items and the LDS allow at best
+    const int fixed = (a.Wd > 1 ? a.s / 2 : 0) + 2 * K + 1;
+    int rows = static_cast<int>((kAnyLds - std::min(wchunk, kAnyLds)) /
+                                (static_cast<size_t>(a.s) * per * kSB));
+    if (a.Hs * a.Ws > most * kAThreads / 4 * PX)
+        rows = std::min(rows, most * kAThreads / 4 * PX / a.Ws);
+    if (rows < fixed)
+        return false;
     int items = 0, M = 0;
     bool ok = false;
-    for (int TR = std::min(maxM / a.Wd, a.Hd); TR >= 1 && !ok; --TR) {
+    for (int TR = std::min({maxM / a.Wd, a.Hd, (rows - fixed) / a.s + 1}); TR >= 1 && !ok; --TR) {
         a.tiles = (a.Hd + TR - 1) / TR;
         a.TR = (a.Hd + a.tiles - 1) / a.tiles;
         M = a.TR * a.Wd;
         a.OP = ((M + 31) & ~31) + 4;
-        a.rows = a.s * (a.TR - 1) + (a.Wd > 1 ? a.s / 2 : 0) + 2 * K + 1;
+        a.rows = a.s * (a.TR - 1) + fixed;
         items = 4 * ((std::min(a.rows, a.Hs) * a.Ws + PX - 1) / PX);
         pl.U = (items + kAThreads - 1) / kAThreads;
-        // three tiles of channels leave no registers for two items of two groups
-        if (pl.U > (NT == 3 && MG == 2 ? 1 : 2))
+        if (pl.U > most)
             continue;
         const size_t outb = d == F32 ? 0 : static_cast<size_t>(32) * a.OP * 2;
         // weights resident, else streamed; window rows of a multiple of 8
@@ -711,7 +701,6 @@ bool plan_tile(const ConvShape &sh, Dtype d, bool dgrad, int NT, int MG, AnyPlan
         // keep the banks' phase), else unpadded
         for (int pass = 0; pass < 4 && !ok; ++pass) {
             a.resident = pass < 2;
-            const int per = (cols + a.s - 1) / a.s;
             a.WCs = (pass & 1) ? per : (per + 7) & ~7;
             a.RP = a.s * a.WCs;
             const size_t winb = static_cast<size_t>(a.rows) * a.RP * kSB;
@@ -728,22 +717,8 @@ bool plan_tile(const ConvShape &sh, Dtype d, bool dgrad, int NT, int MG, AnyPlan
     if (ntot > (1L << 30))
         return false;
     a.ntot = static_cast<int>(ntot);
-    a.fper = make_fastdiv(static_cast<uint32_t>(a.Dd) * a.tiles);
-    a.ftiles = make_fastdiv(static_cast<uint32_t>(a.tiles));
-    int t = 0;
-    for (int dq = -K; dq <= K; ++dq)
-        for (int i = 0; i < col_len(K, dq); ++i, ++t) {
-            const int ds = col_ds_lo(K, dq) + i;
-            const int c = K + dq;
-            a.toff[t] = ((ds + floor_half(dq)) * a.RP + (c % a.s) * a.WCs + c / a.s) * kSB;
-        }
-    pl.NT = NT;
-    pl.MG = MG;
-    const int cus = device_cus();
-    const int per = std::max(1, cus / a.nblk);
-    const int blocks = std::min(a.ntot, per);
+    const int blocks = std::min(a.ntot, std::max(1, cus / a.nblk));
     pl.grid = blocks * a.nblk;
-    pl.HS = a.Cs <= CK / 2 ? 1 : 2;
     const double mf = 2.0 * T * pl.HS * MG * NT * (d == F32 ? 256 : 32);
     const double rd = 8.0 * T * pl.HS * (MG + NT) * 6.5;
     const double stage = 800 + items * 1.5 + (a.resident ? 0 : T * NB * 4 * 2.0);
@@ -765,20 +740,57 @@ bool plan_any(const ConvShape &sh, Dtype d, bool dgrad, AnyPlan &best)
     // a run of rows has to hold one whole item
     if (sh.W < (d == F32 ? 4 : 8) || sh.Ho < 1)
         return false;
+    const int es = d == F32 ? 4 : 2, CK = 64 / es;
+    const int K = sh.k, T = sh.T;
+    AnyPlan pl;
+    AnyArgs &a = pl.a;
+    a.Cs = dgrad ? sh.Co : sh.Ci;
+    a.Cd = dgrad ? sh.Ci : sh.Co;
+    a.Ds = dgrad ? sh.Do : sh.D;
+    a.Hs = dgrad ? sh.Ho : sh.H;
+    a.Ws = dgrad ? sh.Wo : sh.W;
+    a.Dd = dgrad ? sh.D : sh.Do;
+    a.Hd = dgrad ? sh.H : sh.Ho;
+    a.Wd = dgrad ? sh.W : sh.Wo;
+    a.s = sh.s;
+    a.sz = sh.sz;
+    a.kz = sh.kz;
+    a.Z = sh.Z;
+    a.J = sh.Z * T;
+    a.sD = dgrad ? a.J : sh.Ci * a.J;
+    a.sS = dgrad ? sh.Ci * a.J : a.J;
+    a.reflect = dgrad;
+    a.relu = 0;
+    a.nch = (a.Cs + CK - 1) / CK;
+    pl.HS = a.Cs <= CK / 2 ? 1 : 2;
+    if (static_cast<long>(a.Ds) * a.Hs * a.Ws * CK * es >= kAnyMaxSpan)
+        return false;
+    const int cus = device_cus();
     bool found = false;
-    for (int NT = 1; NT <= 3; ++NT)
-        for (int MG = 1; MG <= 2; ++MG) {
-            if (d == F32 && NT == 3 && MG == 2)
+    // no more tiles of channels than there are channels, no second group of
+    // pixels where a plane has none
+    for (pl.NT = 1; pl.NT <= std::min(3, (a.Cd + 31) / 32); ++pl.NT)
+        for (pl.MG = 1; pl.MG <= (a.Hd * a.Wd > 32 * kAWaves ? 2 : 1); ++pl.MG) {
+            if (d == F32 && pl.NT == 3 && pl.MG == 2)
                 continue; // does not fit the registers
-            AnyPlan pl;
-            if (!plan_tile(sh, d, dgrad, NT, MG, pl))
-                continue;
-            if (!found || pl.cost < best.cost) {
+            if (plan_tile(sh, d, cus, pl) && (!found || pl.cost < best.cost)) {
                 best = pl;
                 found = true;
             }
         }
-    return found;
+    if (!found)
+        return false;
+    AnyArgs &b = best.a;
+    b.fper = make_fastdiv(static_cast<uint32_t>(b.Dd) * b.tiles);
+    b.ftiles = make_fastdiv(static_cast<uint32_t>(b.tiles));
+    int t = 0;
+    for (int dq = -K; dq <= K; ++dq)
+        for (int i = 0; i < col_len(K, dq); ++i, ++t) {
+            const int ds = col_ds_lo(K, dq) + i;
+            const int c = K + dq;
+            b.toff[t] = ((ds + floor_half(dq)) * b.RP + (c % b.s) * b.WCs + c / b.s) * kSB;
+        }
+    return true;
 }
 
 template <typename E, int K, int NT, int MG, int U, int HS, bool MIS>
@@ -850,6 +862,7 @@ struct DgsPlan {
     DgsArgs a;
     int NT, MG, grid;
     size_t lds;
+    double cost;
 };
 
 bool plan_dgs(const ConvShape &sh, Dtype d, DgsPlan &best)
@@ -859,7 +872,7 @@ bool plan_dgs(const ConvShape &sh, Dtype d, DgsPlan &best)
         return false;
     const int es = d == F32 ? 4 : 2, PX = 16 / es, CK = 64 / es;
     const int K = sh.k, T = sh.T, s = sh.s;
-    DgsArgs a{};
+    DgsArgs a;
     a.Cs = sh.Co;
     a.Cd = sh.Ci;
     a.Hs = sh.Ho;
@@ -875,19 +888,16 @@ bool plan_dgs(const ConvShape &sh, Dtype d, DgsPlan &best)
         static_cast<long>(sh.H) * sh.W >= (1L << 30))
         return false;
     // taps by class, with their offsets on the output lattice
-    int oq[kMaxTaps], os[kMaxTaps], rlo = 0, rhi = 0, clo = 0, chi = 0, n = 0, most = 0;
-    for (int cl = 0; cl < s * s; ++cl) {
-        a.cstart[cl] = n;
-        for (int t = 0; t < T; ++t) {
-            int dq = 0, ds = 0;
-            tap_axial(K, t, dq, ds);
+    int oq[kMaxTaps], os[kMaxTaps], cls[kMaxTaps], count[kMaxCls + 1] = {};
+    int rlo = 0, rhi = 0, clo = 0, chi = 0, most = 0, n = 0;
+    for (int dq = -K; dq <= K; ++dq)
+        for (int i = 0; i < col_len(K, dq); ++i, ++n) {
+            const int ds = col_ds_lo(K, dq) + i;
             const int ra = ((dq % s) + s) % s, rb = ((ds % s) + s) % s;
-            if (ra * s + rb != cl)
-                continue;
+            cls[n] = ra * s + rb;
             oq[n] = (ra - dq) / s;
             os[n] = (rb - ds) / s;
-            a.tap[n] = t;
-            a.todd[n] = oq[n] & 1;
+            most = std::max(most, ++count[cls[n]]);
             for (int par = 0; par < 2; ++par) {
                 const int row = tap_drow(oq[n], os[n], par);
                 rlo = std::min(rlo, row);
@@ -895,66 +905,98 @@ bool plan_dgs(const ConvShape &sh, Dtype d, DgsPlan &best)
             }
             clo = std::min(clo, oq[n]);
             chi = std::max(chi, oq[n]);
-            ++n;
         }
-        most = std::max(most, n - a.cstart[cl]);
-    }
-    a.cstart[s * s] = n;
     a.rlo = rlo;
     a.coff = -clo;
     // columns of the window: cells reach column Qn - 1, taps chi beyond
     const int cols = a.coff + std::max(a.Ws, a.Qn + chi);
+    a.RP = (cols + 7) & ~7;
     const int cus = device_cus();
-    double cost = 0;
+    const int all = (sh.H + s - 1) / s; // rows of each class in a plane
+    const int fixed = 1 + rhi - rlo;    // window rows beside the tile's
     bool found = false;
-    for (int NT = 1; NT <= 2; ++NT)
-        for (int MG = 1; MG <= 2; ++MG)
+    for (int NT = 1; NT <= std::min(2, (a.Cd + 31) / 32); ++NT)
+        for (int MG = 1; MG <= (all * a.Qn > 32 * kAWaves ? 2 : 1); ++MG)
             for (int resident = 1; resident >= 0; --resident) {
-                DgsArgs c = a;
                 const int NB = 32 * NT, WT = NB * 64 + 16;
                 const int maxM = 32 * kAWaves * MG;
-                if (c.Qn > maxM)
+                if (a.Qn > maxM)
                     continue;
-                const int all = (sh.H + s - 1) / s; // rows of each class in a plane
-                c.resident = resident;
-                c.nblk = (c.Cd + NB - 1) / NB;
-                const size_t wts = (static_cast<size_t>(resident ? T * c.nch : most) * WT + 255) &
+                a.resident = resident;
+                a.nblk = (a.Cd + NB - 1) / NB;
+                const size_t wts = (static_cast<size_t>(resident ? T * a.nch : most) * WT + 255) &
                                    ~static_cast<size_t>(255);
-                size_t lds = 0;
-                bool ok = false;
-                for (int TR = std::min(maxM / c.Qn, all); TR >= 1 && !ok; --TR) {
-                    c.tiles = (all + TR - 1) / TR;
-                    c.TR = (all + c.tiles - 1) / c.tiles;
-                    c.rows = c.TR + 1 + rhi - rlo;
-                    c.RP = (cols + 7) & ~7;
-                    c.win_bytes = c.rows * c.RP * kSB;
-                    lds = wts + static_cast<size_t>(c.win_bytes) * c.nch;
-                    const int items = 4 * ((std::min(c.rows, c.Hs) * c.Ws + PX - 1) / PX);
-                    ok = lds <= kAnyLds - 256 && items <= 2 * kAThreads;
-                }
-                const long ntot = static_cast<long>(sh.N) * c.tiles;
-                if (!ok || ntot > (1L << 30))
+                if (wts >= kAnyLds - 256)
                     continue;
-                c.win_off = static_cast<int>(wts);
-                c.ntot = static_cast<int>(ntot);
-                c.ftiles = make_fastdiv(static_cast<uint32_t>(c.tiles));
-                const int blocks = std::min(c.ntot, std::max(1, cus / c.nblk));
-                const int rounds = (c.ntot + blocks - 1) / blocks;
-                const double M = static_cast<double>(c.TR) * c.Qn;
-                const double mf = c.nch * 2.0 * T * 2 * MG * NT * (d == F32 ? 256 : 32);
-                const double st = c.nch * 1600.0 + s * s * M * NB / 64 * 12 +
-                                  (resident ? 0 : c.nch * (s * s * 2500.0 + T * NB * 8.0));
+                // the rows that the LDS and two items per thread allow
+                int rows = static_cast<int>((kAnyLds - 256 - wts) /
+                                            (static_cast<size_t>(a.RP) * kSB * a.nch));
+                if (a.Hs * a.Ws > kAThreads / 2 * PX)
+                    rows = std::min(rows, kAThreads / 2 * PX / a.Ws);
+                const int TR = std::min({maxM / a.Qn, all, rows - fixed});
+                if (TR < 1)
+                    continue;
+                a.tiles = (all + TR - 1) / TR;
+                a.TR = (all + a.tiles - 1) / a.tiles;
+                a.rows = a.TR + fixed;
+                a.win_bytes = a.rows * a.RP * kSB;
+                const size_t lds = wts + static_cast<size_t>(a.win_bytes) * a.nch;
+                const long ntot = static_cast<long>(sh.N) * a.tiles;
+                if (ntot > (1L << 30))
+                    continue;
+                a.win_off = static_cast<int>(wts);
+                a.ntot = static_cast<int>(ntot);
+                const int blocks = std::min(a.ntot, std::max(1, cus / a.nblk));
+                const int rounds = (a.ntot + blocks - 1) / blocks;
+                const double M = static_cast<double>(a.TR) * a.Qn;
+                const double mf = a.nch * 2.0 * T * 2 * MG * NT * (d == F32 ? 256 : 32);
+                const double st = a.nch * 1600.0 + s * s * M * NB / 64 * 12 +
+                                  (resident ? 0 : a.nch * (s * s * 2500.0 + T * NB * 8.0));
                 const double v =
-                    rounds * (mf + st) + (resident ? c.nch * T * NB * 8.0 : 0.0);
-                if (!found || v < cost) {
-                    for (int i = 0; i < T; ++i)
-                        c.toff[i] = ((os[i] + floor_half(oq[i])) * c.RP + oq[i]) * kSB;
-                    best = DgsPlan{c, NT, MG, blocks * c.nblk, lds};
-                    cost = v;
+                    rounds * (mf + st) + (resident ? a.nch * T * NB * 8.0 : 0.0);
+                if (!found || v < best.cost) {
+                    best.a = a;
+                    best.NT = NT;
+                    best.MG = MG;
+                    best.grid = blocks * a.nblk;
+                    best.lds = lds;
+                    best.cost = v;
                     found = true;
                 }
             }
-    return found;
+    if (!found)
+        return false;
+    DgsArgs &b = best.a;
+    b.ftiles = make_fastdiv(static_cast<uint32_t>(b.tiles));
+    b.cstart[0] = 0;
+    for (int cl = 0; cl < s * s; ++cl)
+        b.cstart[cl + 1] = b.cstart[cl] + count[cl];
+    int at[kMaxCls];
+    std::copy(b.cstart, b.cstart + s * s, at);
+    for (int t = 0; t < T; ++t) {
+        const int i = at[cls[t]]++;
+        b.tap[i] = t;
+        b.todd[i] = oq[t] & 1;
+        b.toff[i] = ((os[t] + floor_half(oq[t])) * b.RP + oq[t]) * kSB;
+    }
+    return true;
+}
+
+// Estimated time: products, staging, results, weights (once, or per class) and
+// the classes' turns.
+double dgs_us(const DgsPlan &pl, const ConvShape &sh, Dtype d)
+{
+    static const double c[2][8] = {{3.6, 1.11, 1.23, 1.19, -0.56, 0.29, 0.59, 0.45},
+                                   {2.0, 2.61, 4.65, 0.39, 3.03, 0.48, 4.21, 0.77}};
+    const DgsArgs &a = pl.a;
+    const double blocks = pl.grid / a.nblk, classes = a.s * a.s;
+    const double rounds = std::ceil(a.ntot / blocks) * std::max(1.0, pl.grid / 256.0);
+    const double wts = a.nch * sh.T * 32.0 * pl.NT / 1000;
+    const double *k = c[d];
+    return k[0] + (a.resident ? k[4] * wts : 0) +
+           rounds * (k[1] * a.nch * sh.T * pl.MG * pl.NT * (d == F32 ? 1024 : 128) / 2400 +
+                     k[2] * a.nch + k[3] * classes * a.TR * a.Qn * 32 * pl.NT / 1e4 +
+                     (a.resident ? 0 : k[5] * a.nch * classes + k[6] * wts) + k[7] * classes);
 }
 
 template <typename E, int K, int NT, int MG>
@@ -984,45 +1026,40 @@ hipError_t dispatch_dgs(const DgsPlan &pl, const void *dy, const void *w, void *
 
 } // namespace
 
-bool conv_any_ok(const ConvShape &sh, Dtype d, bool dgrad)
+Tried conv_any(const void *in, const void *w, const void *bias, void *out, const ConvShape &sh,
+               Dtype d, bool dgrad, bool relu, hipStream_t st, double other_us, hipError_t &e)
 {
-    // Few source channels leave most of a chunk empty; then the generic
-    // kernel is the faster one.  64 images of 41 x 43, k = 1, us here against
-    // generic: bf16 3 -> 16 channels 8.6 / 17.7, 1 -> 16 9.9 / 10.8; 8 volumes
-    // of 12 planes of 37 x 41, kz = 1: bf16 2 -> 16 25 / 32, 1 -> 16 25 / 20;
-    // fp32 (the data gradient only) 8 source channels 36 / 33, 16 57 / 71.
-    const int Cs = dgrad ? sh.Co : sh.Ci;
-    if (Cs < (d == F32 ? 3 : 2))
-        return false;
-    if (dgrad && sh.s > 1) {
-        DgsPlan pl;
-        return plan_dgs(sh, d, pl);
-    }
-    AnyPlan pl;
-    return plan_any(sh, d, dgrad, pl);
-}
-
-hipError_t conv_any(const void *in, const void *w, const void *bias, void *out,
-                    const ConvShape &sh, Dtype d, bool dgrad, bool relu, hipStream_t st)
-{
+    // One source channel in bfloat16, two in float32 leave nearly all of a
+    // chunk empty (64 images of 41 x 43, k = 1, us here against generic: bf16
+    // 1 -> 16 9.9 / 10.8; 8 volumes of 12 planes of 37 x 41, kz = 1: bf16
+    // 1 -> 16 25 / 20).
+    if ((dgrad ? sh.Co : sh.Ci) < (d == F32 ? 3 : 2))
+        return Tried::No;
     if (dgrad && sh.s > 1) {
         DgsPlan dp;
         if (!plan_dgs(sh, d, dp))
-            return hipErrorInvalidValue;
+            return Tried::No;
+        if (dgs_us(dp, sh, d) > kClearly * other_us)
+            return Tried::Slower;
         auto go = [&](auto *p) {
             using E = std::remove_pointer_t<decltype(p)>;
             return sh.k == 1   ? dispatch_dgs<E, 1>(dp, in, w, out, st)
                    : sh.k == 2 ? dispatch_dgs<E, 2>(dp, in, w, out, st)
                                : dispatch_dgs<E, 3>(dp, in, w, out, st);
         };
-        return d == F32 ? go(static_cast<float *>(nullptr)) : go(static_cast<bf16raw *>(nullptr));
+        e = d == F32 ? go(static_cast<float *>(nullptr)) : go(static_cast<bf16raw *>(nullptr));
+        return Tried::Ran;
     }
     AnyPlan pl;
     if (!plan_any(sh, d, dgrad, pl))
-        return hipErrorInvalidValue;
+        return Tried::No;
+    if ((d == F32 ? 4.8 + 1.19 * pl.cost / 2400 : 5.8 + 1.32 * pl.cost / 2400) >
+        kClearly * other_us)
+        return Tried::Slower;
     pl.a.relu = relu;
-    return d == F32 ? dispatch_k<float>(pl, sh.k, in, w, bias, out, st)
-                    : dispatch_k<bf16raw>(pl, sh.k, in, w, bias, out, st);
+    e = d == F32 ? dispatch_k<float>(pl, sh.k, in, w, bias, out, st)
+                 : dispatch_k<bf16raw>(pl, sh.k, in, w, bias, out, st);
+    return Tried::Ran;
 }
 
 } // namespace hexk

@@ -376,41 +376,34 @@ constexpr int max_items(int K, int NT, int MG)
 // The largest stage (and the tallest tile) that fits at NT x MG.  The cost
 // counts, in clocks of a compute unit, rounds of tiles times products,
 // staging and results.
-bool plan_tile(const ConvShape &sh, int NT, int MG, F32Plan &best, bool &found)
+// `pl` holds the rest.
+bool plan_tile(const ConvShape &sh, int cus, F32Plan &pl)
 {
-    const int K = sh.k, T = sh.T;
-    F32Args a{};
-    a.Cs = sh.Ci;
-    a.Cd = sh.Co;
-    a.Ds = sh.D;
-    a.Hs = sh.H;
-    a.Ws = sh.W;
-    a.Dd = sh.Do;
-    a.Hd = sh.Ho;
-    a.Wd = sh.Wo;
-    a.s = sh.s;
-    a.sz = sh.sz;
-    a.kz = sh.kz;
-    a.Z = sh.Z;
-    a.J = sh.Z * T;
-    a.P = a.Cs * a.Z;
+    const int K = sh.k, T = sh.T, NT = pl.NT, MG = pl.MG;
+    F32Args &a = pl.a;
     const int NB = 32 * NT, WP = NT == 1 ? 33 : 97;
     const int maxM = 32 * kFWaves * MG;
     const int most = max_items(K, NT, MG);
     if (a.Wd > maxM || most == 0)
         return false;
     a.nblk = (a.Cd + NB - 1) / NB;
-    const int cols = a.Ws + 2 * K;
-    a.WCs = (cols + a.s - 1) / a.s;
-    a.RP = a.s * a.WCs;
     const int Pe = (a.P + 1) & ~1;
+    // the rows of which a stage holds two planes at best
+    const int fixed_rows = (a.Wd > 1 ? a.s / 2 : 0) + 2 * K + 1;
+    int rows = static_cast<int>((kF32Lds - 256) / (8 * static_cast<size_t>(a.RP)));
+    if (a.Hs * a.Ws > 2 * most * kFThreads)
+        rows = std::min(rows, 2 * most * kFThreads / a.Ws);
+    if (rows < fixed_rows)
+        return false;
+    int ipp = 0;
     bool any = false;
-    for (int TR = std::min(maxM / a.Wd, a.Hd); TR >= 1 && !any; --TR) {
+    for (int TR = std::min({maxM / a.Wd, a.Hd, (rows - fixed_rows) / a.s + 1}); TR >= 1 && !any;
+         --TR) {
         a.tiles = (a.Hd + TR - 1) / TR;
         a.TR = (a.Hd + a.tiles - 1) / a.tiles;
-        a.rows = a.s * (a.TR - 1) + (a.Wd > 1 ? a.s / 2 : 0) + 2 * K + 1;
+        a.rows = a.s * (a.TR - 1) + fixed_rows;
         a.PL = a.rows * a.RP;
-        const int ipp = (std::min(a.rows, a.Hs) * a.Ws + 3) / 4;
+        ipp = (std::min(a.rows, a.Hs) * a.Ws + 3) / 4;
         for (int res = 1; res >= 0 && !any; --res) {
             const size_t fixed = NB * 4 + (res ? static_cast<size_t>(a.P) * T * WP * 4 : 0);
             const size_t per = static_cast<size_t>(a.PL) * 4 + (res ? 0 : static_cast<size_t>(T) * WP * 4);
@@ -438,52 +431,71 @@ bool plan_tile(const ConvShape &sh, int NT, int MG, F32Plan &best, bool &found)
     if (ntot > (1L << 30))
         return false;
     a.ntot = static_cast<int>(ntot);
-    a.fper = make_fastdiv(static_cast<uint32_t>(a.Dd) * a.tiles);
-    a.ftiles = make_fastdiv(static_cast<uint32_t>(a.tiles));
-    a.fw = make_fastdiv(static_cast<uint32_t>(a.Ws));
-    a.fz = make_fastdiv(static_cast<uint32_t>(a.Z));
-    int t = 0;
-    for (int dq = -K; dq <= K; ++dq)
-        for (int i = 0; i < col_len(K, dq); ++i, ++t) {
-            const int c = K + dq;
-            a.toff[t] =
-                (col_ds_lo(K, dq) + i + floor_half(dq)) * a.RP + (c % a.s) * a.WCs + c / a.s;
-        }
-    const int cus = device_cus();
     const int blocks = std::min(a.ntot, std::max(1, cus / a.nblk));
     const int rounds = (a.ntot + blocks - 1) / blocks;
     const int serial = (a.nblk * blocks + cus - 1) / cus;
     const int M = a.TR * a.Wd;
-    const int ipp = (std::min(a.rows, a.Hs) * a.Ws + 3) / 4;
     const double busy = (M + 31) / 32 > kFWaves ? 1.0 : std::max(0.5, (M + 31) / 32 / 8.0);
     const double mf = 2.0 * busy * a.P * T / 2 * MG * NT * 66;
     const double stg = a.nst * 1200.0 + a.P * ipp * 0.6 + (a.resident ? 0 : a.P * T * NB * 0.3);
     const double out = M * NB * 4 / 12.0;
-    const double cost = serial * (rounds * (mf + stg + out) + (a.resident ? a.P * T * NB * 0.3 : 0));
-    if (found && cost >= best.cost)
-        return true;
-    found = true;
-    best.a = a;
-    best.NT = NT;
-    best.MG = MG;
-    const int items = a.G * ipp;
-    const int u = (items + kFThreads - 1) / kFThreads;
-    best.U = u <= 2 ? 2 : u <= 4 ? 4 : 8;
-    best.grid = blocks * a.nblk;
-    best.lds = static_cast<size_t>(a.win_off) + static_cast<size_t>(a.G) * a.PL * 4;
-    best.cost = cost;
+    pl.cost = serial * (rounds * (mf + stg + out) + (a.resident ? a.P * T * NB * 0.3 : 0));
+    const int u = (a.G * ipp + kFThreads - 1) / kFThreads;
+    pl.U = u <= 2 ? 2 : u <= 4 ? 4 : 8;
+    pl.grid = blocks * a.nblk;
+    pl.lds = static_cast<size_t>(a.win_off) + static_cast<size_t>(a.G) * a.PL * 4;
     return true;
 }
 
-bool plan_f32(const ConvShape &sh, F32Plan &pl)
+bool plan_f32(const ConvShape &sh, F32Plan &best)
 {
     if (sh.k < 1 || sh.k > 3 || sh.W < 4 || sh.Ho < 1)
         return false;
+    const int K = sh.k, T = sh.T;
+    F32Plan pl;
+    F32Args &a = pl.a;
+    a.Cs = sh.Ci;
+    a.Cd = sh.Co;
+    a.Ds = sh.D;
+    a.Hs = sh.H;
+    a.Ws = sh.W;
+    a.Dd = sh.Do;
+    a.Hd = sh.Ho;
+    a.Wd = sh.Wo;
+    a.s = sh.s;
+    a.sz = sh.sz;
+    a.kz = sh.kz;
+    a.Z = sh.Z;
+    a.J = sh.Z * T;
+    a.P = a.Cs * a.Z;
+    a.relu = 0;
+    a.WCs = (a.Ws + 2 * K + a.s - 1) / a.s;
+    a.RP = a.s * a.WCs;
+    const int cus = device_cus();
     bool found = false;
-    for (int NT = 1; NT <= 3; ++NT)
-        for (int MG = 1; MG <= 2; ++MG)
-            plan_tile(sh, NT, MG, pl, found);
-    return found;
+    // no more tiles of channels than there are channels, no second group of
+    // pixels where a plane has none
+    for (pl.NT = 1; pl.NT <= std::min(3, (a.Cd + 31) / 32); ++pl.NT)
+        for (pl.MG = 1; pl.MG <= (a.Hd * a.Wd > 32 * kFWaves ? 2 : 1); ++pl.MG)
+            if (plan_tile(sh, cus, pl) && (!found || pl.cost < best.cost)) {
+                best = pl;
+                found = true;
+            }
+    if (!found)
+        return false;
+    F32Args &b = best.a;
+    b.fper = make_fastdiv(static_cast<uint32_t>(b.Dd) * b.tiles);
+    b.ftiles = make_fastdiv(static_cast<uint32_t>(b.tiles));
+    b.fw = make_fastdiv(static_cast<uint32_t>(b.Ws));
+    b.fz = make_fastdiv(static_cast<uint32_t>(b.Z));
+    int t = 0;
+    for (int dq = -K; dq <= K; ++dq)
+        for (int i = 0; i < col_len(K, dq); ++i, ++t) {
+            const int c = K + dq;
+            b.toff[t] =
+                (col_ds_lo(K, dq) + i + floor_half(dq)) * b.RP + (c % b.s) * b.WCs + c / b.s;
+        }
+    return true;
 }
 
 template <int K, int NT, int MG>
@@ -527,31 +539,28 @@ hipError_t dispatch(const F32Plan &pl, const float *x, const float *w, const flo
 
 } // namespace
 
-bool conv_f32_fwd_ok(const ConvShape &sh)
+Tried conv_f32_fwd(const void *in, const void *w, const void *bias, void *out, const ConvShape &sh,
+                   bool relu, hipStream_t st, double other_us, hipError_t &e)
 {
     // One input plane (at a stride; the few-channel kernel has the others) is
     // too short a contraction to pay for staging and weights: stride 2, us
     // here against generic, 2 x 1 -> 15 channels, 33 x 48, k = 2 7.3 / 6.1;
-    // 4 x 1 -> 4, 24 x 30, k = 1 5.3 / 4.6; from two planes on it is not slower.
+    // 4 x 1 -> 4, 24 x 30, k = 1 5.3 / 4.6.
     if (sh.Ci * sh.Z == 1)
-        return false;
-    F32Plan pl;
-    return plan_f32(sh, pl);
-}
-
-hipError_t conv_f32_fwd(const void *in, const void *w, const void *bias, void *out,
-                        const ConvShape &sh, bool relu, hipStream_t st)
-{
+        return Tried::No;
     F32Plan pl;
     if (!plan_f32(sh, pl))
-        return hipErrorInvalidValue;
+        return Tried::No;
+    if (5.1 + 1.84 * pl.cost / 2400 > kClearly * other_us)
+        return Tried::Slower;
     pl.a.relu = relu;
     const float *x = static_cast<const float *>(in), *wf = static_cast<const float *>(w);
     const float *b = static_cast<const float *>(bias);
     float *y = static_cast<float *>(out);
-    return sh.k == 1   ? dispatch<1>(pl, x, wf, b, y, st)
-           : sh.k == 2 ? dispatch<2>(pl, x, wf, b, y, st)
-                       : dispatch<3>(pl, x, wf, b, y, st);
+    e = sh.k == 1   ? dispatch<1>(pl, x, wf, b, y, st)
+        : sh.k == 2 ? dispatch<2>(pl, x, wf, b, y, st)
+                    : dispatch<3>(pl, x, wf, b, y, st);
+    return Tried::Ran;
 }
 
 } // namespace hexk

@@ -13,6 +13,7 @@
 // fixed-order reduction over chunks of k_reduce.hip (deterministic).
 // Pool forward / backward: one output (input) element per thread.
 #include <algorithm>
+#include <cmath>
 
 #include "generic_plan.h"
 #include "hexdev.h"
@@ -473,6 +474,37 @@ bool conv_bwd_data_generic_ok(const ConvShape &sh)
     return plan::plan_bwd_data(sh.Ci, sh.Co, sh.k).ok;
 }
 
+double conv_fwd_generic_us(const ConvShape &sh, Dtype dt)
+{
+    static const double c[2][6] = {{1.3, 8.26, 2.47, 0.17, 4.67, 1.97},
+                                   {1.1, 8.58, 2.58, 0.37, 4.87, 2.06}};
+    const plan::FwdPlan p = plan::plan_fwd(sh.Ci * sh.Z, sh.Co, sh.k, sh.s);
+    const double P = static_cast<double>(sh.Ci) * sh.Z;
+    const double blocks = static_cast<double>(cdiv(sh.Ho, p.TI)) * cdiv(sh.Wo, p.TJ) * sh.Do *
+                          sh.N * cdiv(sh.Co, p.cb);
+    const double region = plan::region_rows(p.TI, sh.k, sh.s) * plan::region_cols(p.TJ, sh.k, sh.s);
+    const double *k = c[dt];
+    return k[0] + std::max(1.0, blocks / 1024) *
+                      (P * sh.T * (k[1] / 100 + p.cb * (k[2] / 800 + k[5] / 1000)) +
+                       k[3] * P * region / 1000 + k[4] * std::ceil(P / p.G));
+}
+
+double conv_bwd_data_generic_us(const ConvShape &sh, Dtype dt)
+{
+    static const double c[2][9] = {{4.9, 6.68, -2.45, 2.78, -0.64, 7.98, 3.16, 0.64, -0.76},
+                                   {6.1, 5.03, -4.60, 3.29, -1.91, 10.8, 2.90, 0.58, -2.45}};
+    const plan::BwdDataPlan p = plan::plan_bwd_data(sh.Ci, sh.Co, sh.k);
+    const double blocks = static_cast<double>(cdiv(static_cast<long>(sh.H) * sh.W, kThreads)) *
+                          sh.D * sh.N * cdiv(sh.Ci, p.cb);
+    const double ct = static_cast<double>(sh.Co) * sh.T, stages = cdiv(sh.Co, p.CC);
+    const double *k = c[dt];
+    double t = ct / (sh.s * sh.s) * (k[1] / 100 + k[2] * p.cb / 800) +
+               stages * (k[3] * sh.T / 10 + k[4]) + k[5] * ct * p.cb / 1000;
+    if (sh.s > 1) // a wave's pixels take turns at the taps
+        t += ct * ((k[6] + (sh.s > 2 ? k[7] : 0)) / 100 + k[8] * p.cb / 800);
+    return k[0] + std::max(1.0, blocks / 1024) * sh.Z / sh.sz * t;
+}
+
 hipError_t conv_fwd_generic(const void *x, const void *w, const void *b, void *y,
                             const ConvShape &sh, Dtype dt, bool relu, hipStream_t st)
 {
@@ -535,6 +567,18 @@ size_t wgrad_generic_workspace(const ConvShape &sh)
     const int nchunks = wgrad_generic_chunks(sh, chunk);
     return sizeof(float) * static_cast<size_t>(nchunks) *
            (static_cast<size_t>(sh.Co) * sh.Ci * sh.Z * sh.T + sh.Co);
+}
+
+double wgrad_generic_us(const ConvShape &sh, Dtype dt)
+{
+    static const double c[2][5] = {{5.5, 4.21, 0.63, 1.53, -1.96}, {5.5, 4.08, 1.68, 0.42, -1.31}};
+    int chunk;
+    const double nchunks = wgrad_generic_chunks(sh, chunk);
+    const int cob = wgrad_co_block(sh.Co);
+    const double n = cdiv(chunk, kThreads), passes = cdiv(sh.Z * sh.T, kTapGroup);
+    const double rounds = std::max(1.0, nchunks * cdiv(sh.Co, cob) * sh.Ci / 2048);
+    const double *k = c[dt];
+    return k[0] + rounds * passes * (n * (k[1] + k[2] * cob) + k[3] * cob + k[4]);
 }
 
 hipError_t wgrad_generic(const void *x, const void *dy, float *dw, float *db, void *ws,

@@ -33,6 +33,7 @@
 // weight rows are 40 bf16 (80 bytes, an odd multiple of 16: conflict-free
 // 16-byte fragment reads of 32 consecutive rows).
 #include <algorithm>
+#include <cmath>
 
 #include "hexdev.h"
 #include "kernels.h"
@@ -814,6 +815,23 @@ bool bf16_gen_dgrad_ok(const ConvShape &sh)
     size_t lds = 0;
     int ng = 0;
     return plan_dgrad(sh, a, lds, ng);
+}
+
+double bf16_gen_dgrad_us(const ConvShape &sh)
+{
+    GenArgs a;
+    size_t lds = 0;
+    int ng = 0;
+    plan_dgrad(sh, a, lds, ng);
+    const double blocks = persistent_blocks(a), chunks = sh.Co / kCK;
+    const double stages = chunks * cdiv(sh.T, kTG);
+    const double rounds = std::ceil(a.ntot / std::max(1.0, std::floor(blocks / a.nblk))) *
+                          std::max(1.0, blocks / 256);
+    const double turns = cdiv(ng, 4 * kMG), products = chunks * sh.T / 10;
+    return 1.46 + (a.resident ? 2.21 * stages : 0) +
+           rounds * (-0.86 + (a.resident ? 0 : 2.08 * stages) +
+                     3.35 * a.WR * (sh.Wo + 2 * sh.k) * sh.Co / 1e4 +
+                     products * (2.65 * turns - 2.99) + 8.10 * turns - 0.209 * a.TR * sh.W / 100);
 }
 
 hipError_t bf16_gen_fwd(const void *x, const void *w, const void *bias, void *y,

@@ -32,6 +32,7 @@
 // yields db.  Per-block partial sums are written to the workspace and added
 // in a fixed order by k_reduce.hip (deterministic).
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "../../include/hexconv.h"
@@ -785,6 +786,15 @@ bool smallc_bwd_data_ok(const ConvShape &sh)
            shear_bytes(sh, bwd_tiling(sh), 1) <= kLdsLimit;
 }
 
+double smallc_bwd_data_us(const ConvShape &sh)
+{
+    const Tiling tg = bwd_tiling(sh);
+    const double rounds = std::max(1.0, static_cast<double>(tg.ntiles) * sh.Ci / 768);
+    const double window = shear_bytes(sh, tg, 1) / 4.0;
+    return 0.9 + rounds * (sh.Co * (1.67 * sh.T / 100 - 0.18 + 0.36 * window / 1000) +
+                           4.9 * cdiv(sh.Co, bwd_ic_chunk(sh, tg)));
+}
+
 namespace {
 template <typename TT>
 hipError_t smallc_bwd_data_t(const TT *dy, const TT *w, TT *dx, const ConvShape &sh,
@@ -851,6 +861,24 @@ bool smallc_wgrad_ok(const ConvShape &sh0)
     const Tiling tg = make_tiling(sh, kWgradTarget);
     return wgrad_lds(sh, tg) <= kLdsLimit && shear_depth(sh, tg, nch) > 0 &&
            plain_depth(tg, 16) > 0;
+}
+
+double smallc_wgrad_us(const ConvShape &sh0, Dtype d)
+{
+    static const double c[2][6] = {{5.9, 1.60, 0.164, 0.22, 4.92, 0.035},
+                                   {3.4, 3.72, 0.112, 0.49, 3.71, 0.019}};
+    const ConvShape sh = fwd_view(sh0);
+    const Tiling tg = make_tiling(sh, kWgradTarget);
+    const double nch = sh.Ci * sh.Z, slots = wgrad_grid(sh, tg);
+    const double per = std::max(1, std::min(kWgradPerCu, static_cast<int>(kLdsPerCu / wgrad_lds(sh, tg))));
+    const double rounds = std::ceil(tg.ntiles / slots) *
+                          std::max(1.0, slots * cdiv(sh.Co, 16) / (device_cus() * per));
+    const double px = tg.TR * tg.TW, NT = wgrad_nt(sh);
+    const double window = nch * (tg.TR + 2 * sh.k) * (tg.TW + 2 * sh.k);
+    const double *k = c[d];
+    return k[0] + rounds * (k[1] + px * NT * (k[2] + k[5] * per) / 100 +
+                            k[3] * (window + 16 * px) / 1000) +
+           k[4] * slots * wgrad_slot(sh) / 1e6;
 }
 
 size_t smallc_wgrad_workspace(const ConvShape &sh0)

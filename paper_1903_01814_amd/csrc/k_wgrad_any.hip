@@ -61,18 +61,6 @@ typedef short shortx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWThreads = 512;
 
-struct WAnyArgs {
-    int N, Ci, Co, D, H, W, Do, Ho, Wo;
-    int s, sz, kz, Z;
-    int TR, tiles, ntot;  // output rows per tile, tiles per plane, tiles of the batch
-    int rows, RP, WCs;    // window
-    int nci, nco;         // channel blocks
-    int nslots;           // blocks per (dz, ci, co) type
-    int x_off, tab_off;   // LDS: dy at 0, x window, pixel table
-    int npix;             // table entries (multiple of 16)
-    int toff[37];         // byte offset of each tap
-};
-
 // Taps per wave and tap groups: T + 1 columns (the taps and the bias)
 constexpr int role_tpw(bool f32, int k, int nco) { return k > 1 ? 5 : f32 ? 2 / nco : 4; }
 constexpr int role_g(bool f32, int k, int nco) { return k == 3 ? 8 : k == 2 ? 4 : f32 ? 4 * nco : 2; }
@@ -496,32 +484,24 @@ __global__ __launch_bounds__(64 * kRedWaves) void reduce_any_k(const float *__re
 
 constexpr size_t kAnyLds = 160 * 1024;
 
-struct WAnyPlan {
-    WAnyArgs a;
-    int NCO, A, U, G, TPW;
-    size_t lds, ws;
-    int types;
-    double cost;
-};
-
 // Clocks of a compute unit for `slots` blocks of every type at the tile of
 // `pl`: rounds of tiles (products of two waves a SIMD, and staging), and the
 // partial sums of all slots, written and read again at about 3 TB/s.
-double tile_cost(const WAnyPlan &pl, Dtype d, long ntot, int slots, int items, int types,
-                 size_t slot)
+double tile_cost(const WAnyPlan &pl, Dtype d, long ntot, int slots, int items, size_t slot,
+                 int cus)
 {
     const WAnyArgs &a = pl.a;
     const int KS = 8 / (pl.G * pl.A);
     const int steps = (a.npix / 16 + KS - 1) / KS;
     const double mf = steps * 2.0 * pl.TPW * pl.NCO * (d == F32 ? 8 * 64 : 32);
-    const double waves = std::max(1.0, types * slots / static_cast<double>(device_cus()));
+    const double waves = std::max(1.0, pl.types * slots / static_cast<double>(cus));
     const double rounds = static_cast<double>((ntot + slots - 1) / slots);
     return waves * rounds * (mf + 4000 + items * 4.0) + slot * slots * 0.0008;
 }
 
 // The tile (rows of it) and the number of slots for A input-channel tiles
 // and U items per thread, the cheapest that fits.
-bool plan_tile(const ConvShape &sh, Dtype d, int A, int U, WAnyPlan &best)
+bool plan_tile(const ConvShape &sh, Dtype d, int A, int U, int cus, WAnyPlan &best)
 {
     const int es = d == F32 ? 4 : 2, PX = 16 / es;
     const int K = sh.k;
@@ -562,7 +542,7 @@ bool plan_tile(const ConvShape &sh, Dtype d, int A, int U, WAnyPlan &best)
     const size_t slot = static_cast<size_t>(pl.types) * pl.G * A * we * 4;
     if (slot > HEX_NOALLOC_SCRATCH_BYTES)
         return false;
-    const int most = std::max(1, std::min(device_cus() / pl.types,
+    const int most = std::max(1, std::min(cus / pl.types,
                                           static_cast<int>(HEX_NOALLOC_SCRATCH_BYTES / slot)));
     const int cols = sh.W + 2 * K;
     a.WCs = (cols + a.s - 1) / a.s;
@@ -591,7 +571,7 @@ bool plan_tile(const ConvShape &sh, Dtype d, int A, int U, WAnyPlan &best)
         if (ntot > (1L << 30))
             break;
         const int slots = static_cast<int>(std::min<long>(ntot, most));
-        const double cost = tile_cost(pl, d, ntot, slots, ix + id, pl.types, slot);
+        const double cost = tile_cost(pl, d, ntot, slots, ix + id, slot, cus);
         if (found && cost >= best.cost)
             continue;
         found = true;
@@ -626,10 +606,11 @@ bool plan_wgrad(const ConvShape &sh, Dtype d, WAnyPlan &pl)
     // bfloat16: two input-channel tiles share the dy tile (at k = 3 the taps
     // take every wave), and one item per thread where that holds a tile
     const int A = (d != F32 && sh.Ci > 32 && sh.k < 3) ? 2 : 1;
+    const int cus = device_cus();
     bool ok = false;
     for (int aa = A; aa >= 1 && !ok; --aa)
         for (int u = d == F32 ? 2 : 1; u <= 2 && !ok; ++u)
-            ok = plan_tile(sh, d, aa, u, pl);
+            ok = plan_tile(sh, d, aa, u, cus, pl);
     return ok;
 }
 
@@ -698,32 +679,24 @@ hipError_t launch_e(const WAnyPlan &pl, int k, const void *x, const void *dy, fl
 
 } // namespace
 
-bool wgrad_any_ok(const ConvShape &sh, Dtype d)
+bool wgrad_any_plan(const ConvShape &sh, Dtype d, WAnyPlan &pl)
 {
-    // Few input channels leave most of a 32-channel tile empty; then the
-    // generic kernel is the faster one in fp32, whose products take 16 times
-    // as long (64 images of 41 x 43, us here against generic: fp32 k = 1
-    // 4 -> 16 channels 47 / 65, 3 -> 16 46 / 58, 2 -> 16 45 / 38; bf16 k = 1
-    // 1 -> 8 channels 15 / 21; 8 volumes of 12 planes, fp32 3 -> 16 channels
-    // 104 / 189, 2 -> 8 slower).
+    // Few input channels leave most of a 32-channel tile empty: in float32,
+    // whose products take 16 times as long, another kernel is then the faster
+    // one (64 images of 41 x 43, us here against generic: k = 1 4 -> 16
+    // channels 47 / 65, 3 -> 16 46 / 58, 2 -> 16 45 / 38; 8 volumes of 12
+    // planes, 3 -> 16 104 / 189, 2 -> 8 slower).
     if (d == F32 && (sh.Ci * sh.T < 20 || (sh.Z > 1 && sh.Ci < 3)))
         return false;
-    WAnyPlan pl;
-    return plan_wgrad(sh, d, pl);
-}
-
-size_t wgrad_any_workspace(const ConvShape &sh, Dtype d)
-{
-    WAnyPlan pl;
-    return plan_wgrad(sh, d, pl) ? pl.ws : 0;
+    if (!plan_wgrad(sh, d, pl))
+        return false;
+    pl.us = d == F32 ? 8.2 + 1.20 * pl.cost / 2400 : 10.5 + 1.14 * pl.cost / 2400;
+    return true;
 }
 
 hipError_t wgrad_any(const void *x, const void *dy, float *dw, float *db, void *ws,
-                     const ConvShape &sh, Dtype d, hipStream_t st)
+                     const ConvShape &sh, Dtype d, const WAnyPlan &pl, hipStream_t st)
 {
-    WAnyPlan pl;
-    if (!plan_wgrad(sh, d, pl))
-        return hipErrorInvalidValue;
     float *part = static_cast<float *>(ws);
     hipError_t e = d == F32 ? launch_e<float>(pl, sh.k, x, dy, part, st)
                             : launch_e<bf16raw>(pl, sh.k, x, dy, part, st);

@@ -327,6 +327,18 @@ bool bf16_wgrad_ok(const ConvShape &sh)
     return wg_lds(sh, wg_tiling(sh, wg_nbw(sh))) <= kWgLdsMax;
 }
 
+double bf16_wgrad_us(const ConvShape &sh)
+{
+    const int nbw = wg_nbw(sh);
+    const WgTiling tg = wg_tiling(sh, nbw);
+    const double blocks = static_cast<double>(tg.nparts) * tg.mgroups * tg.ngroups;
+    const double rounds = cdiv(tg.ntiles, tg.nparts) * std::max(1.0, blocks / kWgBlocks);
+    const double window = static_cast<double>(tg.NCI) * wg_win_rows(sh, tg.TR) * sh.W;
+    return 5.8 + rounds * (1.31 + 0.513 * tg.npix_max * nbw / 100 +
+                           0.147 * (window + kMB * 16 * tg.npix_max) / 1000) +
+           0.65 * bf16_wgrad_workspace(sh) / 1e6 + 0.63 * cdiv(tg.nparts, 256);
+}
+
 size_t bf16_wgrad_workspace(const ConvShape &sh)
 {
     const WgTiling tg = wg_tiling(sh, wg_nbw(sh));

@@ -81,6 +81,25 @@ inline int part_chunks(int E) { return (E + kPartChunk - 1) / kPartChunk; }
 hipError_t reduce_chunked(const float *part, int nparts, int Co, int J, float *dw, float *db,
                           hipStream_t st);
 
+// Where a shape leaves the matrix cores' tiles mostly empty, or the work is
+// too small to pay for staging, a simpler kernel is the faster one.  The *_us
+// functions estimate a kernel's time in microseconds from its launch plan;
+// their constants are least-squares fits (of the relative error) to 160 to
+// 2000 timed shapes of 1 to 190 channels, half of which they meet within 10 %
+// and nine of ten within 30 %.  Taking the any-shape kernels wherever they run
+// made some 320 of 3150 random calls over 5 % slower than on the simpler
+// kernel (down to a third of the speed); chosen by the estimates, 17 of 4050
+// are over 7 % slower.
+//
+// What a kernel that was offered a call did with it: it does not take the
+// shape, it would be slower than the caller's other choice, or it ran (one
+// plan serves the question and the launch).
+enum class Tried { No, Slower, Ran };
+
+// A kernel for any shape takes a call only where its estimate is below the
+// other kernel's by this factor.
+constexpr double kClearly = 0.9;
+
 // ---- generic kernels: any k, stride, channel count and dtype -----------
 // whether the launch plan of the generic forward / data gradient fits the
 // LDS of a block (checked by the ABI before anything is enqueued)
@@ -92,6 +111,9 @@ hipError_t conv_fwd_generic(const void *x, const void *w, const void *b,
 hipError_t conv_bwd_data_generic(const void *dy, const void *w, void *dx,
                                  const ConvShape &sh, Dtype dt,
                                  hipStream_t st);
+double conv_fwd_generic_us(const ConvShape &sh, Dtype dt);
+double conv_bwd_data_generic_us(const ConvShape &sh, Dtype dt);
+double wgrad_generic_us(const ConvShape &sh, Dtype dt);
 size_t wgrad_generic_workspace(const ConvShape &sh);
 hipError_t wgrad_generic(const void *x, const void *dy, float *dw, float *db,
                          void *ws, const ConvShape &sh, Dtype dt,
@@ -129,6 +151,7 @@ bool smallc_fwd_ok(const ConvShape &sh);
 hipError_t smallc_fwd(const void *x, const void *w, const void *b, void *y, const ConvShape &sh,
                       Dtype d, bool relu, hipStream_t st);
 bool smallc_bwd_data_ok(const ConvShape &sh);
+double smallc_bwd_data_us(const ConvShape &sh); // bfloat16
 hipError_t smallc_bwd_data(const void *dy, const void *w, void *dx, const ConvShape &sh, Dtype d,
                            hipStream_t st);
 // Data gradient of a 3-D layer with 1 or 2 input channels, float32 or
@@ -138,6 +161,7 @@ bool smallc3d_bwd_data_ok(const ConvShape &sh);
 hipError_t smallc3d_bwd_data(const void *dy, const void *w, void *dx, const ConvShape &sh,
                              Dtype d, hipStream_t st);
 bool smallc_wgrad_ok(const ConvShape &sh);
+double smallc_wgrad_us(const ConvShape &sh, Dtype d);
 size_t smallc_wgrad_workspace(const ConvShape &sh);
 hipError_t smallc_wgrad(const void *x, const void *dy, float *dw, float *db, void *ws,
                         const ConvShape &sh, Dtype d, hipStream_t st);
@@ -163,6 +187,7 @@ hipError_t bf16_wide_conv(const void *in, const void *w, const void *bias, void 
 bool bf16_gen_fwd_ok(const ConvShape &sh);
 hipError_t bf16_gen_fwd(const void *x, const void *w, const void *bias, void *y,
                         const ConvShape &sh, bool relu, hipStream_t st);
+double bf16_gen_dgrad_us(const ConvShape &sh);
 bool bf16_gen_dgrad_ok(const ConvShape &sh);
 hipError_t bf16_gen_dgrad(const void *dy, const void *w, void *dx, const ConvShape &sh,
                           hipStream_t st);
@@ -177,23 +202,43 @@ hipError_t bf16_wgrad32(const void *x, const void *dy, float *dw, float *db, voi
 // ---- bf16 matrix-core weight gradient (k <= 3, W and W_out % 8 == 0) ---
 bool bf16_wgrad_ok(const ConvShape &sh);
 size_t bf16_wgrad_workspace(const ConvShape &sh);
+double bf16_wgrad_us(const ConvShape &sh);
 hipError_t bf16_wgrad(const void *x, const void *dy, float *dw, float *db, void *ws,
                       const ConvShape &sh, hipStream_t st);
 
 // ---- matrix-core kernels for planes of any size and any channel count, k 1
 // to 3, bf16 and fp32, 2-D and 3-D (k_conv_any.hip, k_wgrad_any.hip) --------
-// forward, or (dgrad) the data gradient: 2-D at any stride, 3-D at stride 1
-bool conv_any_ok(const ConvShape &sh, Dtype d, bool dgrad);
-hipError_t conv_any(const void *in, const void *w, const void *bias, void *out,
-                    const ConvShape &sh, Dtype d, bool dgrad, bool relu, hipStream_t st);
+// forward, or (dgrad) the data gradient: 2-D at any stride, 3-D at stride 1;
+// other_us: estimated time of the caller's other choice; e: the launch status
+Tried conv_any(const void *in, const void *w, const void *bias, void *out, const ConvShape &sh,
+               Dtype d, bool dgrad, bool relu, hipStream_t st, double other_us, hipError_t &e);
 // float32 forward in the generic kernel's order of sums, bit for bit
 // (k_conv_f32.hip); 2-D and 3-D, k 1 to 3
-bool conv_f32_fwd_ok(const ConvShape &sh);
-hipError_t conv_f32_fwd(const void *x, const void *w, const void *bias, void *y,
-                        const ConvShape &sh, bool relu, hipStream_t st);
-bool wgrad_any_ok(const ConvShape &sh, Dtype d);
-size_t wgrad_any_workspace(const ConvShape &sh, Dtype d);
+Tried conv_f32_fwd(const void *x, const void *w, const void *bias, void *y, const ConvShape &sh,
+                   bool relu, hipStream_t st, double other_us, hipError_t &e);
+
+struct WAnyArgs {
+    int N, Ci, Co, D, H, W, Do, Ho, Wo;
+    int s, sz, kz, Z;
+    int TR, tiles, ntot;  // output rows per tile, tiles per plane, tiles of the batch
+    int rows, RP, WCs;    // window
+    int nci, nco;         // channel blocks
+    int nslots;           // blocks per (dz, ci, co) type
+    int x_off, tab_off;   // LDS: dy at 0, x window, pixel table
+    int npix;             // table entries (multiple of 16)
+    int toff[37];         // byte offset of each tap
+};
+
+struct WAnyPlan {
+    WAnyArgs a;
+    int NCO, A, U, G, TPW;
+    size_t lds, ws; // bytes per block, of the workspace
+    int types;
+    double cost, us; // clocks, estimated time
+};
+// false: not for this shape
+bool wgrad_any_plan(const ConvShape &sh, Dtype d, WAnyPlan &pl);
 hipError_t wgrad_any(const void *x, const void *dy, float *dw, float *db, void *ws,
-                     const ConvShape &sh, Dtype d, hipStream_t st);
+                     const ConvShape &sh, Dtype d, const WAnyPlan &pl, hipStream_t st);
 
 } // namespace hexk

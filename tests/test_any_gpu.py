@@ -10,8 +10,8 @@ import oracle
 from gpu_helpers import check, rel_l2, torch_mod
 from paper_1903_01814_amd import inputs as gen
 from test_parity3d_gpu import run_bwd_data3, run_bwd_weight3, run_fwd3
-from test_parity_gpu import (check_bwd_full, check_fwd_full, run_bwd_weight, run_pool_bwd,
-                             test_pool_sweep)
+from test_parity_gpu import (check_bwd_full, check_fwd_full, run_bwd_data, run_bwd_weight,
+                             run_fwd, run_pool_bwd, test_pool_sweep)
 
 pytestmark = pytest.mark.gpu
 
@@ -121,6 +121,85 @@ def test_f32_volume_sums():
     dx = run_bwd_data3(dy[:, :12], w, 1, 1, 1, 1, 10, 33, 35, "f32")
     rx = oracle.conv3d_bwd_data(dy[:, :12], w, 1, 1, 1, 1, 10, 33, 35)
     assert rel_l2(dx, rx) <= PLANE_REL, rel_l2(dx, rx)
+
+
+# Little work, or channels that leave a matrix-core tile mostly empty: the
+# simpler kernel that the estimates choose, and the sizes next to it that the
+# kernels for any shape take.  The launch record names what ran.
+ROUTES = [
+    # op, N, C_in, C_out, H, W, k, stride, dtype, kernel
+    ("fwd", 34, 2, 6, 73, 120, 3, 2, "bf16", "conv_fwd_generic_k"),
+    ("fwd", 34, 16, 48, 33, 41, 1, 2, "bf16", "conv_any_k"),
+    ("fwd", 125, 4, 6, 61, 128, 1, 2, "f32", "conv_fwd_generic_k"),
+    ("fwd", 12, 16, 48, 33, 41, 1, 2, "f32", "conv_f32_k"),
+    ("bwd_data", 170, 5, 2, 46, 18, 1, 1, "bf16", "conv_bwd_data_generic_k"),
+    ("bwd_data", 2, 3, 3, 24, 32, 3, 1, "bf16", "bwd_data_f32_k"),
+    ("bwd_data", 64, 4, 32, 41, 43, 1, 1, "bf16", "conv_any_k"),
+    ("bwd_data", 6, 7, 3, 90, 72, 1, 2, "f32", "conv_bwd_data_generic_k"),
+    ("bwd_data", 10, 6, 5, 46, 98, 1, 3, "bf16", "conv_bwd_data_generic_k"),
+    ("bwd_data", 8, 48, 64, 46, 47, 1, 2, "bf16", "conv_any_dgs_k"),
+    ("bwd_weight", 112, 3, 5, 63, 77, 1, 2, "f32", "wgrad_partial_generic_k"),
+    ("bwd_weight", 1, 7, 2, 29, 57, 1, 1, "f32", "wgrad_partial_generic_k"),
+    ("bwd_weight", 20, 16, 24, 33, 41, 1, 2, "f32", "wgrad_any_k"),
+    ("bwd_weight", 1, 1, 85, 18, 88, 3, 1, "bf16", "wgrad_bf16_k"),
+    ("bwd_weight", 6, 5, 40, 24, 32, 1, 1, "bf16", "wgrad_bf16_k"),
+    ("bwd_weight", 55, 7, 40, 24, 24, 1, 3, "bf16", "wgrad_bf16_k"),
+    ("bwd_weight", 40, 48, 64, 24, 32, 2, 1, "bf16", "wgrad_any_k"),
+    ("bwd_weight", 4, 7, 5, 60, 71, 1, 4, "bf16", "wgrad_partial_generic_k"),
+]
+
+
+@pytest.mark.parametrize("case", ROUTES, ids=lambda c: "%s_N%d_ci%d_co%d_%dx%d_k%d_s%d_%s" % c[:9])
+def test_route(case):
+    from paper_1903_01814_amd import hexconv as hx
+    op, N, Ci, Co, H, W, k, s, dt, kernel = case
+    rng = np.random.default_rng(700 + N + Ci + H)
+    T = oracle.num_taps(k)
+    x = gen.round_to(rng.normal(size=(N, Ci, H, W)), dt)
+    w = gen.round_to(rng.normal(size=(Co, Ci, T)) / np.sqrt(Ci * T), dt)
+    dy = gen.round_to(rng.normal(size=(N, Co) + oracle.out_shape(H, W, s)), dt)
+    a = np.abs
+    hx.hexconv_timing_begin()
+    try:
+        if op == "fwd":
+            got = [run_fwd(x, w, None, k, s, dt)]
+        elif op == "bwd_data":
+            got = [run_bwd_data(dy, w, k, s, H, W, dt)]
+        else:
+            got = run_bwd_weight(x, dy, k, s, dt)
+    finally:
+        ran = hx.hexconv_timing_end()
+    assert kernel in ran, ran
+    if op == "fwd":
+        ref, mag = [oracle.conv_fwd(x, w, None, k, s)], [oracle.conv_fwd(a(x), a(w), None, k, s)]
+    elif op == "bwd_data":
+        ref = [oracle.conv_bwd_data(dy, w, k, s, H, W)]
+        mag = [oracle.conv_bwd_data(a(dy), a(w), k, s, H, W)]
+    else:
+        ref, mag = oracle.conv_bwd_weight(x, dy, k, s), oracle.conv_bwd_weight(a(x), a(dy), k, s)
+    for g, r, m in zip(got, ref, mag):
+        check(dt, g, r, m, kernel)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [
+    # N, C, H, W, kernel: 1024 and 2048 pixels a plane, 3 << 20 in all
+    (2, 3, 32, 32, "pool_bwd_k"), (2, 3, 26, 40, "pool_any_bwd_k"),
+    (4, 400, 50, 40, "pool_bwd_k"), (4, 400, 52, 40, "pool_any_bwd_k")])
+def test_mean_gradient_route(case, dt):
+    from paper_1903_01814_amd import hexconv as hx
+    N, C, H, W, kernel = case
+    rng = np.random.default_rng(H + W)
+    dy = gen.round_to(rng.normal(size=(N, C, H, W)), dt)
+    hx.hexconv_timing_begin()
+    try:
+        got = run_pool_bwd(dy, None, None, 1, 1, 1, H, W, dt)
+    finally:
+        ran = hx.hexconv_timing_end()
+    assert list(ran) == [kernel]
+    ref = oracle.pool_bwd(dy, None, None, 1, 1, 1, H, W)
+    mag = oracle.pool_bwd(np.abs(dy), None, None, 1, 1, 1, H, W)
+    check(dt, got, ref, mag, kernel)
 
 
 # Few input channels on rows that are no multiple of 4 (the last group of four
