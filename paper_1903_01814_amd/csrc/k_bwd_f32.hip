@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
                 (BY_TILE ? sum : tot)[i][j] += v;
             }
     };
-    auto kstep = [&](int i, int h) {
+    auto kstep = [&](const int (&bb)[NT], int i, int h) {
         const int pa = p0 + i * PSTEP;
         float a[MT], b[NT];
 #pragma unroll
@@ -298,13 +298,47 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
             a[ii] = lds[abase[ii] + pa];
 #pragma unroll
         for (int j = 0; j < NT; ++j)
-            b[j] = lds[bbase[j] + pa];
+            b[j] = lds[bb[j] + pa];
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
             for (int ii = 0; ii < MT; ++ii)
                 acc[h][ii][j] =
                     __builtin_amdgcn_mfma_f32_16x16x4f32(a[ii], b[j], acc[h][ii][j], 0, 0, 0);
+    };
+
+    // a tile's part of the weight gradient, x operands from bb
+    auto dw_tile = [&](const int (&bb)[NT]) {
+#pragma unroll
+        for (int ii = 0; ii < MT; ++ii)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                sum[ii][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        int i = 0;
+        auto group = [&](auto n) {
+            clear();
+#pragma unroll
+            for (int u = 0; u < decltype(n)::value; ++u)
+                kstep(bb, i + u, u % HC);
+            flush();
+            i += decltype(n)::value;
+        };
+        while (i + 4 * HC <= nsteps)
+            group(std::integral_constant<int, 4 * HC>{});
+        if (HC == 2 && i + 4 <= nsteps)
+            group(std::integral_constant<int, 4>{});
+        if (i < nsteps) {
+            clear();
+            for (; i < nsteps; ++i)
+                kstep(bb, i, 0);
+            flush();
+        }
+        if constexpr (BY_TILE)
+#pragma unroll
+            for (int ii = 0; ii < MT; ++ii)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    tot[ii][j] += sum[ii][j];
     };
 
     // once per block: zero halo columns of every channel, the zeros plane,
@@ -332,7 +366,9 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
     // One tile: stage it, start the loads of the tile two steps ahead into
     // the same registers, then the two roles work on the window at the same
     // time (VALU and matrix cores of each SIMD).  Rows past the image are
-    // zeros, so a short last tile needs no masking.
+    // zeros, so a short last tile needs no masking but for the x operand of
+    // such a row, whose taps may lie inside: an infinity there, times dy = 0,
+    // would be a NaN.
     auto tile_step = [&](StageBuf<TT, U> &buf, int tile) {
         const int n = tile / tpi;
         const int r0 = (tile - n * tpi) * kTR;
@@ -396,37 +432,16 @@ __global__ __launch_bounds__(kThreads) void bwd_smallc_k(
                     for (int r = 0; r < kTR; ++r)
                         dxp[((g * CI + ci) * kTR + r) * W + c] = gacc[ci][r];
             }
+        } else if (BY_TILE && rows == kTR) {
+            // (a path of its own: 1 -> 16 channels, 40 x 40, k = 2, N = 256
+            // 23.2 us by the other one; without BY_TILE two paths spill)
+            dw_tile(bbase);
         } else {
+            int bb[NT]; // the zeros plane for rows past the image
 #pragma unroll
-            for (int ii = 0; ii < MT; ++ii)
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-                    sum[ii][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-            int i = 0;
-            auto group = [&](auto n) {
-                clear();
-#pragma unroll
-                for (int u = 0; u < decltype(n)::value; ++u)
-                    kstep(i + u, u % HC);
-                flush();
-                i += decltype(n)::value;
-            };
-            while (i + 4 * HC <= nsteps)
-                group(std::integral_constant<int, 4 * HC>{});
-            if (HC == 2 && i + 4 <= nsteps)
-                group(std::integral_constant<int, 4>{});
-            if (i < nsteps) {
-                clear();
-                for (; i < nsteps; ++i)
-                    kstep(i, 0);
-                flush();
-            }
-            if constexpr (BY_TILE)
-#pragma unroll
-                for (int ii = 0; ii < MT; ++ii)
-#pragma unroll
-                    for (int j = 0; j < NT; ++j)
-                        tot[ii][j] += sum[ii][j];
+            for (int j = 0; j < NT; ++j)
+                bb[j] = 4 * (dwv & 1) + kq < rows ? bbase[j] : bt.zo;
+            dw_tile(bb);
         }
         __syncthreads(); // partials written; every read of the window done
         // dx: the groups' partials added in a fixed order, 16-byte stores.

@@ -349,3 +349,44 @@ def test_weight_gradient_keeps_infinities(dt):
     # corner (18, 26), an even column: the window centres that reach it inside
     # the tensor are itself and its neighbours (17, 26), (18, 25), (17, 25)
     assert hit[:, 3].sum(1).eq(4).all() and not hit[:, [0, 1, 2, 4, 5, 6, 7]].any()
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [
+    # N, C_in, C_out, H, W, kernel: planes that end inside a step of 16 pixels
+    # (few tiles a block and many), a row of tiles cut at the bottom
+    (20, 16, 24, 33, 41, "wgrad_any_k"), (60, 48, 40, 25, 45, "wgrad_any_k"),
+    (9, 8, 16, 19, 27, "wgrad_f32_k"), (9, 2, 12, 37, 41, "bwd_smallc_k"),
+    (9, 1, 20, 18, 40, "bwd_smallc_k")], ids=lambda c: "%d_%d_%d_%dx%d_%s" % c)
+def test_infinity_stays_with_its_taps(case, dt):
+    """An infinity in the last pixel of an image reaches the sums of the taps
+    that read it from a centre inside the tensor, as an infinity, and no other
+    sum: neither rows and pixels past a tile's end nor borders multiply it."""
+    torch = torch_mod()
+    from paper_1903_01814_amd import hexconv as hx
+    N, Ci, Co, H, W, kernel = case
+    tdt = torch.float32 if dt == "f32" else torch.bfloat16
+    g = torch.Generator().manual_seed(1)
+    x = torch.rand((N, Ci, H, W), generator=g).to(tdt)
+    dy = (torch.rand((N, Co, H, W), generator=g) + 0.5).to(tdt)
+    c = Ci // 2
+    for n in (0, N - 1):
+        x[n, c, H - 1, W - 1] = float("inf")
+    dw, db = torch.empty((Co, Ci, 7), device="cuda"), torch.empty(Co, device="cuda")
+    nws = hx.hexconv_bwd_weight_workspace(N, Ci, Co, H, W, 1, 1, 0 if dt == "f32" else 1)
+    ws = torch.empty(nws, dtype=torch.uint8, device="cuda")
+    hx.hexconv_timing_begin()
+    try:
+        hx.hexconv_bwd_weight(x.cuda(), dy.cuda(), dw, db, ws, 1, 1)
+    finally:
+        ran = hx.hexconv_timing_end()
+    assert kernel in ran, ran
+    dw = dw.cpu()
+    nan = torch.isnan(dw).sum().item()
+    assert nan == 0 and torch.isfinite(db).all().item()
+    # centres that reach the corner from inside: itself, the pixel above, and
+    # the left column's one (odd corner column) or two
+    hit, want = torch.isinf(dw), 4 if W % 2 else 3
+    assert hit[:, c].sum(1).unique().tolist() == [want]
+    hit[:, c] = False
+    assert hit.sum().item() == 0
