@@ -1053,8 +1053,7 @@ Tried conv_any(const void *in, const void *w, const void *bias, void *out, const
     AnyPlan pl;
     if (!plan_any(sh, d, dgrad, pl))
         return Tried::No;
-    if ((d == F32 ? 4.8 + 1.19 * pl.cost / 2400 : 5.8 + 1.32 * pl.cost / 2400) >
-        kClearly * other_us)
+    if ((d == F32 ? 4.8 + 1.19 * pl.cost / 2400 : 5.8 + 1.32 * pl.cost / 2400) > other_us)
         return Tried::Slower;
     pl.a.relu = relu;
     e = d == F32 ? dispatch_k<float>(pl, sh.k, in, w, bias, out, st)

@@ -31,6 +31,7 @@
 // matrix rate; 48 -> 96, 46 x 45, N = 15, k = 2: 370, 98, 36.  (Items' places
 // worked out once instead of per stage: 101 -> 115 us, the registers spill.)
 #include <algorithm>
+#include <cmath>
 
 #include "chanlast.h"
 #include "kernels.h"
@@ -498,6 +499,20 @@ bool plan_f32(const ConvShape &sh, F32Plan &best)
     return true;
 }
 
+// Estimated time: rounds, products, staging, results, weights.
+double f32_us(const F32Plan &pl, const ConvShape &sh)
+{
+    const F32Args &a = pl.a;
+    const double blocks = pl.grid / a.nblk, M = a.TR * a.Wd;
+    const double rounds = std::ceil(a.ntot / blocks) * std::max(1.0, pl.grid / 256.0);
+    const double busy = M > 32 * kFWaves ? 1.0 : std::max(0.5, std::ceil(M / 32) / kFWaves);
+    const double pt = static_cast<double>(a.P) * sh.T;
+    const double items = static_cast<double>(a.P) * ((std::min(a.rows, a.Hs) * a.Ws + 3) / 4);
+    return 2.6 + rounds * (2.87 + (0.93 * 66 * busy * pt * pl.MG * pl.NT + 3.79 * items +
+                                   0.80 * M * 32 * pl.NT / 3) / 2400) +
+           6.26 * 0.3 * pt * 32 * pl.NT / 2400;
+}
+
 template <int K, int NT, int MG>
 hipError_t launch(const F32Plan &pl, const float *x, const float *w, const float *b, float *y,
                   hipStream_t st)
@@ -551,7 +566,7 @@ Tried conv_f32_fwd(const void *in, const void *w, const void *bias, void *out, c
     F32Plan pl;
     if (!plan_f32(sh, pl))
         return Tried::No;
-    if (5.1 + 1.84 * pl.cost / 2400 > kClearly * other_us)
+    if (f32_us(pl, sh) > other_us)
         return Tried::Slower;
     pl.a.relu = relu;
     const float *x = static_cast<const float *>(in), *wf = static_cast<const float *>(w);

@@ -96,8 +96,10 @@ hipError_t reduce_chunked(const float *part, int nparts, int Co, int J, float *d
 // plan serves the question and the launch).
 enum class Tried { No, Slower, Ran };
 
-// A kernel for any shape takes a call only where its estimate is below the
-// other kernel's by this factor.
+// The any-shape weight gradient and strided data gradient, whose estimates
+// scatter most, take a call only where they are below the other kernel's by
+// this factor (wgrad, 838 bf16 and 800 float32 shapes: 22 and 10 over 5 %
+// slower at 1.0, 14 and 4 at 0.9; the mean gain 1 % less).
 constexpr double kClearly = 0.9;
 
 // ---- generic kernels: any k, stride, channel count and dtype -----------
