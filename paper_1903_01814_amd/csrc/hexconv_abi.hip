@@ -180,12 +180,26 @@ int launched(hipError_t e)
     return HEX_ERR_LAUNCH;
 }
 
-// HEXCONV_PATH=generic forces the generic kernels (used by tests to compare
-// the specialised kernels against them).
-bool force_generic()
+// HEXCONV_PATH puts one family of kernels before the choice by size, for
+// tests that compare the families on small tensors: "generic" takes nothing
+// else; "any" (planes of any size, k_conv_any, k_conv_f32, k_wgrad_any), "few"
+// (few input channels) and "rows" (bf16 rows of whole 16-byte vectors,
+// k_mfma_gen, k_wgrad_bf16) where the family takes the shape at all.
+bool forced(const char *family)
 {
     const char *v = getenv("HEXCONV_PATH");
-    return v != nullptr && strcmp(v, "generic") == 0;
+    return v != nullptr && strcmp(v, family) == 0;
+}
+
+bool force_generic() { return forced("generic"); }
+
+// Estimated time of a call's other choice as offered to the kernels for any
+// shape: strided = that choice is a kernel of the family "rows".
+double other_us(double us, bool strided)
+{
+    if (forced("any"))
+        return HUGE_VAL;
+    return strided && forced("rows") ? 0.0 : us;
 }
 
 // Weight-gradient kernel family for a shape, its workspace and, for the
@@ -203,6 +217,8 @@ WgradPath wgrad_path(const ConvShape &sh, Dtype d, hexk::WAnyPlan &any)
 {
     if (force_generic())
         return WgradPath::Generic;
+    if (forced("any") && hexk::wgrad_any_plan(sh, d, any))
+        return WgradPath::Any;
     // where the fused backward applies, it is also the fastest weight
     // gradient with its data-gradient waves off (fp32 1 -> 16 channels, 40x40,
     // k = 2: 18 -> 13 us; bf16 1 -> 32 channels, 48x48, N = 512: 69 -> 59 us
@@ -210,6 +226,8 @@ WgradPath wgrad_path(const ConvShape &sh, Dtype d, hexk::WAnyPlan &any)
     if (hexk::smallc_bwd_fused_ok(sh, d))
         return WgradPath::Fused;
     const bool small = hexk::smallc_wgrad_ok(sh);
+    if (small && forced("few"))
+        return WgradPath::Small;
     // few channels on rows of whole 4-column groups: float32 (43 shapes, all
     // faster than generic); bf16, for which the small-channel kernel stages x
     // once per 16 output channels, with one such block at k <= 2 (1 -> 16
@@ -231,6 +249,8 @@ WgradPath wgrad_path(const ConvShape &sh, Dtype d, hexk::WAnyPlan &any)
     // rows of whole 4-column groups or the generic one, unless the estimates
     // put another kernel clearly below it
     const bool mfma = d == hexk::BF16 && hexk::bf16_wgrad_ok(sh);
+    if (mfma && forced("rows"))
+        return WgradPath::Bf16Mfma;
     WgradPath best = WgradPath::Generic;
     double us = hexk::wgrad_generic_us(sh, d);
     const auto offer = [&](WgradPath path, double t) {
@@ -294,13 +314,13 @@ WgradPick wgrad3d_pick(const ConvShape &sh, Dtype d)
         return p;
     const double us = hexk::wgrad_generic_us(sh, d) * hexk::kClearly;
     if (hexk::smallc_wgrad_ok(sh)) {
-        if (sh.W % 4 == 0 || hexk::smallc_wgrad_us(sh, d) < us) {
+        if (sh.W % 4 == 0 || forced("few") || hexk::smallc_wgrad_us(sh, d) < us) {
             p.path = WgradPath::Small;
             p.ws = hexk::smallc_wgrad_workspace(sh);
         }
         return p;
     }
-    if (hexk::wgrad_any_plan(sh, d, p.any) && p.any.us < us) {
+    if (hexk::wgrad_any_plan(sh, d, p.any) && (p.any.us < us || forced("any"))) {
         p.path = WgradPath::Any;
         p.ws = p.any.ws;
     }
@@ -448,17 +468,19 @@ int hexconv_fwd(const void *x, const void *w, const void *bias, void *y, int N, 
     const bool relu = (flags & HEX_FLAG_RELU) != 0;
     const Dtype d = static_cast<Dtype>(dt);
     if (!force_generic()) {
-        if (hexk::smallc_fwd_ok(sh))
+        const bool any = forced("any");
+        if (!any && hexk::smallc_fwd_ok(sh))
             return launched(hexk::smallc_fwd(x, w, bias, y, sh, d, relu, st));
         // the tuned bf16 stride-1 kernels where they win, then the kernels
         // for any shape or, where the work is little, the generic one; the
         // other bf16 kernels only where the any-shape window does not fit
         const bool wide = d == hexk::BF16 && hexk::bf16_wide_ok(sh, sh.Ci, sh.Co);
-        if (wide && hexk::bf16_wide_first(sh, sh.Ci, sh.Co, false))
+        if (wide && !any && hexk::bf16_wide_first(sh, sh.Ci, sh.Co, false))
             return launched(hexk::bf16_wide_conv(x, w, bias, y, sh, false, relu, st));
         hipError_t e = hipSuccess;
         const bool strided = d == hexk::BF16 && hexk::bf16_gen_fwd_ok(sh);
-        const double other = wide || strided ? HUGE_VAL : fwd_generic_us(sh, d);
+        const double other =
+            other_us(wide || strided ? HUGE_VAL : fwd_generic_us(sh, d), strided);
         const Tried t = d == hexk::F32
                             ? hexk::conv_f32_fwd(x, w, bias, y, sh, relu, st, other, e)
                             : hexk::conv_any(x, w, bias, y, sh, d, false, relu, st, other, e);
@@ -496,10 +518,11 @@ int hexconv_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in, i
         // the vector units, 10 us here; 170 of 46 x 18, 5 -> 2: 8.6 on the
         // generic one, 13.4); fp32 of few channels on the vector units first
         const bool wide = d == hexk::BF16 && hexk::bf16_wide_ok(sh, sh.Co, sh.Ci);
-        if (wide && hexk::bf16_wide_first(sh, sh.Co, sh.Ci, true))
+        const bool any = forced("any");
+        if (wide && !any && hexk::bf16_wide_first(sh, sh.Co, sh.Ci, true))
             return launched(hexk::bf16_wide_conv(dy, w, nullptr, dx, sh, true, false, st));
         const bool small = hexk::smallc_bwd_data_ok(sh);
-        if (small && d == hexk::F32)
+        if (small && (forced("few") || (d == hexk::F32 && !any)))
             return launched(hexk::smallc_bwd_data(dy, w, dx, sh, d, st));
         hipError_t e = hipSuccess;
         // bf16 on rows of whole 16-byte vectors: one walk over dy for all
@@ -507,10 +530,11 @@ int hexconv_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in, i
         // 192 channels, 112 x 96, N = 2, k = 1, stride 2: 23 us, 50 here; 128
         // -> 96, 64 x 80, N = 9, k = 2: 112, 56)
         const bool strided = d == hexk::BF16 && !small && hexk::bf16_gen_dgrad_ok(sh);
-        const double other = wide      ? HUGE_VAL
-                             : small   ? hexk::smallc_bwd_data_us(sh)
-                             : strided ? hexk::bf16_gen_dgrad_us(sh)
-                                       : bwd_data_generic_us(sh, d);
+        const double other = other_us(wide      ? HUGE_VAL
+                                      : small   ? hexk::smallc_bwd_data_us(sh)
+                                      : strided ? hexk::bf16_gen_dgrad_us(sh)
+                                                : bwd_data_generic_us(sh, d),
+                                      strided);
         const Tried t = hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st, other, e);
         if (t == Tried::Ran)
             return launched(e);
@@ -730,7 +754,7 @@ int hexconv3d_fwd(const void *x, const void *w, const void *bias, void *y, int N
         if (hexk::smallc_fwd_ok(sh))
             return launched(hexk::smallc_fwd(x, w, bias, y, sh, d, relu, st));
         hipError_t e = hipSuccess;
-        const double gen = fwd_generic_us(sh, d);
+        const double gen = other_us(fwd_generic_us(sh, d), false);
         const Tried t = d == hexk::F32
                             ? hexk::conv_f32_fwd(x, w, bias, y, sh, relu, st, gen, e)
                             : hexk::conv_any(x, w, bias, y, sh, d, false, relu, st, gen, e);
@@ -762,8 +786,8 @@ int hexconv3d_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in,
         if (hexk::smallc3d_bwd_data_ok(sh))
             return launched(hexk::smallc3d_bwd_data(dy, w, dx, sh, d, st));
         hipError_t e = hipSuccess;
-        if (hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st, bwd_data_generic_us(sh, d),
-                           e) == Tried::Ran)
+        if (hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st,
+                           other_us(bwd_data_generic_us(sh, d), false), e) == Tried::Ran)
             return launched(e);
     }
     if (!hexk::conv_bwd_data_generic_ok(sh))

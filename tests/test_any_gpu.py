@@ -2,7 +2,9 @@
 (k_conv_any.hip, k_wgrad_any.hip) against the fp64 oracle, at the sizes where
 they can go wrong: rows of odd length and of the shortest length taken (8),
 one row, several tiles and a ragged last tile, channel counts just past a
-chunk or a 32-channel tile, k = 1 .. 3, strides, both dtypes, 3-D."""
+chunk or a 32-channel tile, k = 1 .. 3, strides, both dtypes, 3-D.  Work this
+little mostly goes to simpler kernels, so these cases run twice: as a call
+does, and with HEXCONV_PATH putting the family under test first."""
 import numpy as np
 import pytest
 
@@ -11,7 +13,8 @@ from gpu_helpers import check, rel_l2, torch_mod
 from paper_1903_01814_amd import inputs as gen
 from test_parity3d_gpu import run_bwd_data3, run_bwd_weight3, run_fwd3
 from test_parity_gpu import (check_bwd_full, check_fwd_full, run_bwd_data, run_bwd_weight,
-                             run_fwd, run_pool_bwd, test_pool_sweep)
+                             run_fwd, run_pool_bwd)
+import test_parity_gpu as parity
 
 pytestmark = pytest.mark.gpu
 
@@ -33,12 +36,17 @@ CASES = [
     (1, 12, 8, 33, 64, 2, 8), (1, 3, 8, 2, 17, 1, 2), (1, 64, 64, 32, 32, 1, 2),
     # whole 16-byte rows that the tuned bf16 kernels leave to this one
     (2, 64, 96, 40, 48, 1, 1), (1, 96, 96, 33, 40, 1, 1), (2, 32, 32, 64, 64, 2, 1),
+    # weight gradient: rows of 4 and of 8 pixels, more than 64 (channel, tap)
+    # pairs, planes that end inside a step of 16 pixels
+    (3, 12, 20, 9, 4, 1, 1), (2, 5, 33, 11, 4, 2, 1), (3, 12, 20, 9, 8, 1, 1),
+    (2, 5, 33, 11, 8, 2, 1), (3, 16, 8, 13, 12, 1, 3),
+    # weight gradient: fewer slots than tiles (k > 1), so that they fit the
+    # scratch array of a call that may not allocate
+    (30, 128, 128, 13, 17, 3, 1),
 ]
 
 
-@pytest.mark.parametrize("dt", ["f32", "bf16"])
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "N%d_ci%d_co%d_%dx%d_k%d_s%d" % c)
-def test_conv_any_shape(case, dt):
+def conv_case(case, dt):
     N, Ci, Co, H, W, k, s = case
     rng = np.random.default_rng(300 + sum(case))
     T = oracle.num_taps(k)
@@ -51,12 +59,15 @@ def test_conv_any_shape(case, dt):
     check_bwd_full(x, w, dy, k, s, dt, what="bwd")
 
 
+@pytest.mark.parametrize("path", ["", "any"])
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
-@pytest.mark.parametrize("case", [
-    # N, C_in, C_out, D, H, W, k, kz, stride, stride_z
-    (2, 6, 9, 3, 9, 11, 1, 1, 1, 1), (1, 17, 33, 4, 20, 19, 1, 1, 1, 1),
-    (1, 8, 8, 2, 10, 13, 2, 2, 1, 1), (1, 40, 12, 5, 11, 17, 1, 1, 2, 2)])
-def test_conv3d_any_shape(case, dt):
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "N%d_ci%d_co%d_%dx%d_k%d_s%d" % c)
+def test_conv_any_shape(case, dt, path, monkeypatch):
+    monkeypatch.setenv("HEXCONV_PATH", path)
+    conv_case(case, dt)
+
+
+def conv3d_case(case, dt):
     N, Ci, Co, D, H, W, k, kz, s, sz = case
     rng = np.random.default_rng(400 + sum(case))
     Z, T = 2 * kz + 1, oracle.num_taps(k)
@@ -76,6 +87,17 @@ def test_conv3d_any_shape(case, dt):
     mw, mb = oracle.conv3d_bwd_weight(a(x), a(dy), k, kz, s, sz)
     check(dt, dw, rw, mw, "dw")
     check(dt, db, rb, mb, "db")
+
+
+@pytest.mark.parametrize("path", ["", "any"])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [
+    # N, C_in, C_out, D, H, W, k, kz, stride, stride_z
+    (2, 6, 9, 3, 9, 11, 1, 1, 1, 1), (1, 17, 33, 4, 20, 19, 1, 1, 1, 1),
+    (1, 8, 8, 2, 10, 13, 2, 2, 1, 1), (1, 40, 12, 5, 11, 17, 1, 1, 2, 2)])
+def test_conv3d_any_shape(case, dt, path, monkeypatch):
+    monkeypatch.setenv("HEXCONV_PATH", path)
+    conv3d_case(case, dt)
 
 
 # Relative error of float32 sums whose terms are independent: a chain of n
@@ -138,6 +160,10 @@ ROUTES = [
     ("bwd_data", 6, 7, 3, 90, 72, 1, 2, "f32", "conv_bwd_data_generic_k"),
     ("bwd_data", 10, 6, 5, 46, 98, 1, 3, "bf16", "conv_bwd_data_generic_k"),
     ("bwd_data", 8, 48, 64, 46, 47, 1, 2, "bf16", "conv_any_dgs_k"),
+    # one walk over dy for all classes of pixels; too wide a row for the
+    # any-shape window, which the other bf16 kernel still holds
+    ("bwd_data", 2, 3, 192, 112, 96, 1, 2, "bf16", "conv_gen_dgrad_k"),
+    ("fwd", 2, 32, 32, 72, 128, 3, 4, "bf16", "conv_gen_fwd_k"),
     ("bwd_weight", 112, 3, 5, 63, 77, 1, 2, "f32", "wgrad_partial_generic_k"),
     ("bwd_weight", 1, 7, 2, 29, 57, 1, 1, "f32", "wgrad_partial_generic_k"),
     ("bwd_weight", 20, 16, 24, 33, 41, 1, 2, "f32", "wgrad_any_k"),
@@ -145,6 +171,8 @@ ROUTES = [
     ("bwd_weight", 6, 5, 40, 24, 32, 1, 1, "bf16", "wgrad_bf16_k"),
     ("bwd_weight", 55, 7, 40, 24, 24, 1, 3, "bf16", "wgrad_bf16_k"),
     ("bwd_weight", 40, 48, 64, 24, 32, 2, 1, "bf16", "wgrad_any_k"),
+    # rows of 4 pixels, 32 channels and more: several passes over x
+    ("bwd_weight", 40, 32, 160, 9, 4, 1, 1, "bf16", "wgrad32_k"),
     ("bwd_weight", 4, 7, 5, 60, 71, 1, 4, "bf16", "wgrad_partial_generic_k"),
 ]
 
@@ -214,8 +242,9 @@ SMALL = [
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("case", SMALL, ids=lambda c: "N%d_ci%d_co%d_%dx%d_k%d" % c)
-def test_few_channels_any_width(case, dt):
-    test_conv_any_shape(case + (1,), dt)
+def test_few_channels_any_width(case, dt, monkeypatch):
+    monkeypatch.setenv("HEXCONV_PATH", "few")
+    conv_case(case + (1,), dt)
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
@@ -223,8 +252,25 @@ def test_few_channels_any_width(case, dt):
     (2, 1, 8, 5, 20, 25, 1, 1, 1, 1), (1, 2, 16, 4, 13, 43, 1, 1, 1, 1),
     (1, 1, 16, 3, 9, 130, 1, 1, 1, 1), (1, 2, 40, 4, 15, 19, 1, 1, 1, 1),
     (1, 1, 8, 3, 10, 7, 2, 2, 1, 1), (1, 1, 12, 6, 17, 46, 1, 1, 1, 2)])
-def test_few_channels_any_width_3d(case, dt):
-    test_conv3d_any_shape(case, dt)
+def test_few_channels_any_width_3d(case, dt, monkeypatch):
+    monkeypatch.setenv("HEXCONV_PATH", "few")
+    conv3d_case(case, dt)
+
+
+# The general sweeps' shapes, whose work is as little: through the families
+# that a larger tensor of the same shape is given to.
+@pytest.mark.parametrize("dt,path", [("f32", "few"), ("bf16", "few"), ("bf16", "rows")])
+@pytest.mark.parametrize("case", parity.SWEEP, ids=lambda c: "N%d_ci%d_co%d_%dx%d_k%d_s%d" % c)
+def test_sweep_families(case, dt, path, monkeypatch):
+    monkeypatch.setenv("HEXCONV_PATH", path)
+    parity.test_conv_sweep(case, dt)
+
+
+@pytest.mark.parametrize("case", parity.GEN_CASES + [c for c in parity.LARGE_K_S if c[1] >= 32],
+                         ids=lambda c: "N%d_ci%d_co%d_%dx%d_k%d_s%d" % c)
+def test_rows_any_stride(case, monkeypatch):
+    monkeypatch.setenv("HEXCONV_PATH", "rows")
+    conv_case(case, "bf16")
 
 
 # Pools on planes that are no whole 16-byte rows, and 3-D pools: single rows and
@@ -241,7 +287,7 @@ POOL = [
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("case", POOL, ids=lambda c: "N%d_c%d_%dx%d_k%d_s%d" % c)
 def test_pool_any_shape(case, mode, dt):
-    test_pool_sweep(case, mode, dt)
+    parity.test_pool_sweep(case, mode, dt)
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
@@ -315,7 +361,7 @@ def test_f32_forward_order(case):
     o = hx.hex_out_shape3d(D, H, W, k, kz, s, sz) if vol else hx.hex_out_shape(H, W, k, s)
     got = []
     try:
-        for path in ("", "generic"):
+        for path in ("any", "generic"):
             os.environ["HEXCONV_PATH"] = path
             y = torch.full((N, Co) + tuple(o), float("nan"), device="cuda")
             if vol:
@@ -331,7 +377,8 @@ def test_f32_forward_order(case):
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_weight_gradient_keeps_infinities(dt):
     """An infinity in x next to a tile's end reaches the sums of its own taps
-    as an infinity, and no other sum: 19 x 27 pixels end inside a step."""
+    as an infinity, and no other sum: 19 x 27 pixels end inside a step (the
+    generic kernel here; the families with tiles in the test below)."""
     torch = torch_mod()
     from paper_1903_01814_amd import hexconv as hx
     tdt = torch.float32 if dt == "f32" else torch.bfloat16

@@ -375,8 +375,7 @@ SWEEP = [
     # blocks per row, ragged last tiles
     (2, 64, 64, 37, 128, 1, 1), (1, 32, 32, 19, 128, 2, 1), (3, 64, 64, 9, 64, 1, 1),
     (1, 32, 32, 10, 256, 2, 1),
-    # k = 3 (37 taps): matrix-core weight gradient (forward and data gradient
-    # on the generic kernels)
+    # k = 3 (37 taps)
     (2, 32, 32, 12, 16, 3, 1), (1, 64, 32, 9, 24, 3, 1), (1, 32, 64, 7, 40, 3, 1),
     # strided matrix-core weight gradient (W and W_out multiples of 8):
     # strides 2 and 3, k 1-3, ragged last tiles
@@ -468,7 +467,9 @@ def test_pool_large_k_and_stride(case, mode, dt):
 # stride.  Strides 1 (k = 3) to 8, several 32-channel chunks, 64-channel
 # blocks cut short, ragged row tiles, output widths that are not a multiple
 # of 8 (scalar stores), data-gradient tiles in several rounds of pixel
-# groups (strides 3 and 4 over wide rows).
+# groups (strides 3 and 4 over wide rows).  A call mostly goes to the kernels
+# for any shape instead; test_any_gpu.py runs these cases with
+# HEXCONV_PATH=rows, which puts k_mfma_gen.hip first.
 GEN_CASES = [
     # N, Ci, Co, H, W, k, s
     (2, 32, 32, 12, 16, 3, 1), (1, 64, 96, 9, 24, 3, 1), (1, 96, 32, 8, 40, 3, 1),
