@@ -103,6 +103,14 @@ int hex_tap_table(int k, int parity, int *dcol, int *drow);
  *   y[n][co][i][j] = bias[co] + sum_ci sum_t w[co][ci][t] * x[n][ci][p_t]
  * where p_t is tap t of the window centred on output (i, j), and x reads 0
  * outside the tensor.  bias may be NULL.  flags: HEX_FLAG_RELU.
+ *
+ * Weights that are infinite or NaN: an output whose tap lies inside the
+ * tensor follows the sum, and output channels without such a weight are not
+ * touched.  Whether a tap outside the tensor takes part, as a product with
+ * zero (NaN), or is left out depends on the kernel that runs, so such an
+ * output may be NaN or the sum of its other taps.  The same holds for
+ * hexconv_bwd_data, for taps of no window centre, and for the
+ * three-dimensional forms.
  */
 int hexconv_fwd(const void *x, const void *w, const void *bias, void *y,
                 int N, int C_in, int C_out, int H, int W, int k, int stride,
@@ -122,7 +130,8 @@ int hexconv_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in,
                      void *stream);
 
 /* Bytes of device workspace hexconv_bwd_weight needs for these sizes
- * (0 for invalid arguments). */
+ * (0 for invalid arguments).  It follows the kernel chosen for the sizes:
+ * ask again for every shape, dtype and version of the library. */
 size_t hexconv_bwd_weight_workspace(int N, int C_in, int C_out, int H, int W,
                                     int k, int stride, hex_dtype dt);
 

@@ -437,3 +437,40 @@ def test_infinity_stays_with_its_taps(case, dt):
     assert hit[:, c].sum(1).unique().tolist() == [want]
     hit[:, c] = False
     assert hit.sum().item() == 0
+
+
+@pytest.mark.parametrize("path", ["", "generic", "any", "few", "rows"])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [
+    # N, C_in, C_out, H, W, k: any width, few channels, whole 16-byte rows
+    (2, 6, 9, 19, 27, 1), (2, 2, 9, 14, 24, 2), (2, 32, 32, 12, 16, 1),
+    (2, 32, 32, 12, 16, 3)], ids=lambda c: "%d_%d_%d_%dx%d_k%d" % c)
+def test_infinite_weight(case, dt, path, monkeypatch):
+    """An infinite weight makes the outputs of its channel infinite where its
+    tap lies inside the tensor; where the tap is padding, they are NaN or the
+    sum of the other taps; other channels keep their sums.  Both directions."""
+    monkeypatch.setenv("HEXCONV_PATH", path)
+    N, Ci, Co, H, W, k = case
+    rng = np.random.default_rng(800 + sum(case))
+    T = oracle.num_taps(k)
+    x = gen.round_to(rng.uniform(0.5, 1.0, size=(N, Ci, H, W)), dt)
+    dy = gen.round_to(rng.uniform(0.5, 1.0, size=(N, Co, H, W)), dt)
+    w = gen.round_to(rng.uniform(0.5, 1.0, size=(Co, Ci, T)), dt)
+    co, ci, t = Co - 1, Ci // 2, 0
+    one = np.zeros((1, 1, T))
+    one[0, 0, t] = 1.0
+    ones = np.ones((1, 1, H, W))
+    wi, w0 = w.copy(), w.copy()
+    wi[co, ci, t], w0[co, ci, t] = np.inf, 0.0
+    for got, ref, inside, c in (
+            (run_fwd(x, wi, None, k, 1, dt), oracle.conv_fwd(x, w0, None, k, 1),
+             oracle.conv_fwd(ones, one, None, k, 1)[0, 0] > 0, co),
+            (run_bwd_data(dy, wi, k, 1, H, W, dt), oracle.conv_bwd_data(dy, w0, k, 1, H, W),
+             oracle.conv_bwd_data(ones, one, k, 1, H, W)[0, 0] > 0, ci)):
+        assert 0 < inside.sum() < H * W
+        hit = got[:, c]
+        assert np.isposinf(hit[:, inside]).all()
+        got[:, c][:, inside] = ref[:, c][:, inside]
+        edge = np.isnan(got)
+        assert not edge[:, np.arange(got.shape[1]) != c].any()
+        check(dt, np.where(edge, ref, got), ref, ref, "finite sums")
