@@ -473,21 +473,18 @@ int hexconv_fwd(const void *x, const void *w, const void *bias, void *y, int N, 
             return launched(hexk::smallc_fwd(x, w, bias, y, sh, d, relu, st));
         // the tuned bf16 stride-1 kernels where they win, then the kernels
         // for any shape or, where the work is little, the generic one; the
-        // other bf16 kernels only where the any-shape window does not fit
-        const bool wide = d == hexk::BF16 && hexk::bf16_wide_ok(sh, sh.Ci, sh.Co);
-        if (wide && !any && hexk::bf16_wide_first(sh, sh.Ci, sh.Co, false))
+        // strided bf16 kernel only where the any-shape window does not fit
+        if (d == hexk::BF16 && !any && hexk::bf16_wide_first(sh, sh.Ci, sh.Co, false))
             return launched(hexk::bf16_wide_conv(x, w, bias, y, sh, false, relu, st));
         hipError_t e = hipSuccess;
         const bool strided = d == hexk::BF16 && hexk::bf16_gen_fwd_ok(sh);
         const double other =
-            other_us(wide || strided ? HUGE_VAL : fwd_generic_us(sh, d), strided);
+            other_us(strided ? HUGE_VAL : fwd_generic_us(sh, d), strided);
         const Tried t = d == hexk::F32
                             ? hexk::conv_f32_fwd(x, w, bias, y, sh, relu, st, other, e)
                             : hexk::conv_any(x, w, bias, y, sh, d, false, relu, st, other, e);
         if (t == Tried::Ran)
             return launched(e);
-        if (wide && t == Tried::No)
-            return launched(hexk::bf16_wide_conv(x, w, bias, y, sh, false, relu, st));
         if (strided)
             return launched(hexk::bf16_gen_fwd(x, w, bias, y, sh, relu, st));
     }
@@ -517,9 +514,8 @@ int hexconv_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in, i
         // 52 us on the small-channel kernel, whose fp32 arithmetic runs on
         // the vector units, 10 us here; 170 of 46 x 18, 5 -> 2: 8.6 on the
         // generic one, 13.4); fp32 of few channels on the vector units first
-        const bool wide = d == hexk::BF16 && hexk::bf16_wide_ok(sh, sh.Co, sh.Ci);
         const bool any = forced("any");
-        if (wide && !any && hexk::bf16_wide_first(sh, sh.Co, sh.Ci, true))
+        if (d == hexk::BF16 && !any && hexk::bf16_wide_first(sh, sh.Co, sh.Ci, true))
             return launched(hexk::bf16_wide_conv(dy, w, nullptr, dx, sh, true, false, st));
         const bool small = hexk::smallc_bwd_data_ok(sh);
         if (small && (forced("few") || (d == hexk::F32 && !any)))
@@ -530,16 +526,13 @@ int hexconv_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in, i
         // 192 channels, 112 x 96, N = 2, k = 1, stride 2: 23 us, 50 here; 128
         // -> 96, 64 x 80, N = 9, k = 2: 112, 56)
         const bool strided = d == hexk::BF16 && !small && hexk::bf16_gen_dgrad_ok(sh);
-        const double other = other_us(wide      ? HUGE_VAL
-                                      : small   ? hexk::smallc_bwd_data_us(sh)
+        const double other = other_us(small     ? hexk::smallc_bwd_data_us(sh)
                                       : strided ? hexk::bf16_gen_dgrad_us(sh)
                                                 : bwd_data_generic_us(sh, d),
                                       strided);
         const Tried t = hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st, other, e);
         if (t == Tried::Ran)
             return launched(e);
-        if (wide && t == Tried::No)
-            return launched(hexk::bf16_wide_conv(dy, w, nullptr, dx, sh, true, false, st));
         if (small)
             return launched(hexk::smallc_bwd_data(dy, w, dx, sh, d, st));
         if (strided)

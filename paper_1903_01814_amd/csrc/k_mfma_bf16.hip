@@ -24,7 +24,7 @@
 // that is an odd multiple of 16 bytes, of 16 rows at 32 mod 64 bytes;
 // 8-byte writes of 16 or 32 rows at 8 mod 16 bytes.
 //
-// conv_bf16_wide32_k (preferred): v_mfma_f32_32x32x16_bf16, one block of 8
+// conv_bf16_wide32_k: v_mfma_f32_32x32x16_bf16, one block of 8
 // waves per CU, each block a contiguous run of row tiles, the next tile's
 // rows prefetched into registers while the current one is computed, the A
 // fragments of the next two K-steps in flight.  Where LDS holds it, the
@@ -32,10 +32,9 @@
 // tile after the first stages only its TR new rows) and the results are
 // staged in a region of their own.  The 32x32 instruction keeps the matrix
 // cores at about 2 PFLOP/s with one or two waves per SIMD, where the 16x16
-// one needs more waves than the registers allow.
-// conv_bf16_wide_k (fallback for other channel counts): 16x16x32, 4 waves,
-// two blocks per CU, pixel tiles handed out so that the blocks of one XCD
-// work on neighbouring tiles at the same time.
+// one needs more waves than the registers allow (96 -> 96 channels, 64 x 64,
+// N = 24: 55 us on a 16x16x32 kernel, 34 on the one for any shape, which takes
+// the channel counts that this one leaves).
 #include <algorithm>
 #include <type_traits>
 
@@ -47,23 +46,18 @@ namespace {
 
 using namespace hexgeom;
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / 64;
 constexpr int kXcd = 8;
 
 struct WideArgs {
     int N, H, W;
     int IC, OC;         // channels of the kernel's input and output tensors
-    int KS;             // K-steps: T * IC / 32
+    int KS;             // K-steps: T * IC / 16
     int TR, ntr;        // rows per pixel tile, pixel tiles per image
     int ptiles;         // pixel tiles in the batch
     int nocc;           // output-channel chunks
-    int spx;            // tile slots per XCD (per chunk)
-    int nslots;         // tile slots per chunk (= 8 * spx)
     int LCP, CS;        // input window: slots per row, bf16 per slot
     int OP;             // output staging pitch (bf16 per channel)
     int WP;             // weight row pitch in LDS (bf16 per output channel)
@@ -99,7 +93,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 //     8 consecutive (ic, t) per load;
 //   data gradient, w[ic][oc][t] (ic = the convolution's output channel):
 //     one run of nrow * T elements per ic, read element by element.
-template <int T, bool REFLECT, int NTHR = kThreads>
+template <int T, bool REFLECT, int NTHR>
 __device__ __forceinline__ void stage_weights(bf16raw *__restrict__ wl, const bf16raw *__restrict__ w,
                                               int o_lo, int nrow, int IC, int OC, int WP)
 {
@@ -161,128 +155,6 @@ __device__ __forceinline__ void stage_weights(bf16raw *__restrict__ wl, const bf
                     wl[dsti[u]] = v[u];
         }
     }
-}
-
-// Input window of a pixel tile (rows r0-K .. r0+rows+K-1 of one image, all
-// IC channels), staged channel-last into LDS at slot ((r - r0 + K) * LCP +
-// c + K).  The rows inside the image are one contiguous run of each NCHW
-// plane; a work item is one 8-channel group of one 8-element chunk of that
-// run (chunks aligned to 8 elements), consecutive items take consecutive
-// channel groups.  load() reads U items of this thread (items it0 + h *
-// 256) into registers, commit() transposes them (8 x 8 bf16) into 8 pixel
-// slots; zero_halo() clears the K columns on each side and the window rows
-// outside the image.
-struct WideWindow {
-    int e_lo, e_hi, e_al, items, rbase, ra, rb, rows;
-    __device__ __forceinline__ WideWindow(int K, int H, int W, int IC, int r0, int rows_)
-    {
-        rows = rows_;
-        rbase = r0 - K;
-        ra = max(r0 - K, 0);
-        rb = min(r0 + rows_ + K, H);
-        e_lo = ra * W;
-        e_hi = rb * W;
-        e_al = e_lo & ~7;
-        items = (IC >> 3) * ((e_hi - e_al + 7) >> 3);
-    }
-};
-
-template <int K, int U, int NTHR = kThreads> struct WideTileRegs {
-    uint4 v[U][8];
-    int eb[U], cg[U];
-
-    __device__ __forceinline__ void load(const bf16raw *__restrict__ src, const WideWindow &wd,
-                                         int HW, int IC, int it0)
-    {
-        const int ncg = IC >> 3;
-#pragma unroll
-        for (int h = 0; h < U; ++h) {
-            const int it = it0 + h * NTHR;
-            const bool live = it < wd.items;
-            const int ch = live ? it / ncg : 0;
-            cg[h] = live ? it - ch * ncg : 0;
-            // e_al + 8*ch is a multiple of 8 below e_hi <= H*W (a multiple
-            // of 8): all 8 elements lie inside the plane
-            const int e0 = wd.e_al + 8 * ch;
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                v[h][j] = *reinterpret_cast<const uint4 *>(
-                    src + static_cast<size_t>(cg[h] * 8 + j) * HW + e0);
-            eb[h] = live ? e0 : -1;
-        }
-    }
-
-    __device__ __forceinline__ void commit(bf16raw *__restrict__ tl, const WideWindow &wd, int W,
-                                           int LCP, int CS) const
-    {
-#pragma unroll
-        for (int h = 0; h < U; ++h) {
-            if (eb[h] < 0)
-                continue;
-            // the 8 pixels eb..eb+7 cross at most one row end (W >= 8); slot =
-            // window-relative element + 2K per row end crossed + K
-            const int r = eb[h] / W;
-            const int c = eb[h] - r * W;
-            const int base = (eb[h] - wd.rbase * W) + (r - wd.rbase) * 2 * K + K;
-#pragma unroll
-            for (int px = 0; px < 8; ++px) {
-                const int e = eb[h] + px;
-                const int brk = (c + px >= W) ? 1 : 0;
-                const uint32_t sel = (px & 1) ? 0x07060302u : 0x05040100u;
-                uint32_t w4[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t lo = reinterpret_cast<const uint32_t *>(&v[h][2 * q])[px >> 1];
-                    const uint32_t hi = reinterpret_cast<const uint32_t *>(&v[h][2 * q + 1])[px >> 1];
-                    w4[q] = perm(hi, lo, sel);
-                }
-                const int slot = base + px + brk * 2 * K;
-                if (e >= wd.e_lo && e < wd.e_hi)
-                    *reinterpret_cast<uint4 *>(tl + static_cast<size_t>(slot) * CS + cg[h] * 8) =
-                        make_uint4(w4[0], w4[1], w4[2], w4[3]);
-            }
-        }
-    }
-};
-
-template <int K, int NTHR = kThreads>
-__device__ __forceinline__ void zero_halo(bf16raw *__restrict__ tl, const WideWindow &wd, int W,
-                                          int IC, int LCP, int CS)
-{
-    const int LR = wd.rows + 2 * K;
-    const int v8 = IC >> 3; // 16-byte vectors per slot holding data
-    const int side = LR * 2 * K;
-    const int nlo = wd.ra - wd.rbase;                 // window rows above the image
-    const int out_rows = nlo + (wd.rbase + LR - wd.rb); // ... plus below it
-    const int total = (side + out_rows * LCP) * v8;
-    for (int e = threadIdx.x; e < total; e += NTHR) {
-        const int s = e / v8, q = e - s * v8;
-        int slot;
-        if (s < side) {
-            const int rr = s / (2 * K), j = s - rr * 2 * K;
-            slot = rr * LCP + (j < K ? j : W + j);
-        } else {
-            const int s2 = s - side;
-            const int orow = s2 / LCP, c = s2 - orow * LCP;
-            const int rr = orow < nlo ? orow : (wd.rb - wd.rbase) + (orow - nlo);
-            slot = rr * LCP + c;
-        }
-        *reinterpret_cast<uint4 *>(tl + static_cast<size_t>(slot) * CS + q * 8) = make_uint4(0, 0, 0, 0);
-    }
-}
-
-// Whole window, U items per thread per round.
-template <int K, int U>
-__device__ __forceinline__ void stage_tile(bf16raw *__restrict__ tl, const bf16raw *__restrict__ src,
-                                           int H, int W, int IC, int r0, int rows, int LCP, int CS)
-{
-    const WideWindow wd(K, H, W, IC, r0, rows);
-    for (int it0 = threadIdx.x; it0 < wd.items; it0 += U * kThreads) {
-        WideTileRegs<K, U> g;
-        g.load(src, wd, H * W, IC, it0);
-        g.commit(tl, wd, W, LCP, CS);
-    }
-    zero_halo<K>(tl, wd, W, IC, LCP, CS);
 }
 
 // Ring window of the 32x32 kernel.  The window of a tile (rows r0 - K ..
@@ -381,41 +253,13 @@ __device__ __forceinline__ void ring_zero(bf16raw *__restrict__ tl, bool cols, i
     }
 }
 
-// Epilogue of a pixel tile, first half: bias, ReLU and bf16 rounding of
-// this wave's MT x NT accumulator tiles into LDS as [oc][pixel] with pitch
-// OP (OP = 4 mod 8: the 8-byte writes of 16 channel rows hit distinct
-// banks).  Rows of pixels past the tile's end hold garbage, never stored.
-template <int NT, int PW, int MT>
-__device__ __forceinline__ void wide_epilogue(bf16raw *__restrict__ outl, int OP,
-                                              const floatx4 (&acc)[MT][NT], const float (&bv)[NT],
-                                              int ocl0, int pg, int m, int kq, int relu)
-{
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-        const int ocl = ocl0 + j * 16 + m;
-#pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            const int q0 = (pg + PW * i) * 16 + 4 * kq;
-            float v[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                v[r] = acc[i][j][r] + bv[j];
-                if (relu)
-                    v[r] = fmaxf(v[r], 0.f);
-            }
-            *reinterpret_cast<uint2 *>(outl + ocl * OP + q0) =
-                make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-        }
-    }
-}
-
-// Second half: 16-byte stores of noc channel rows of npix pixels (npix % 8
+// 16-byte stores of noc channel rows of npix pixels (npix % 8
 // == 0) from the LDS tile (row pitch OP, rows 8-byte aligned) to y_base +
 // ocl * HW.  Every thread issues exactly NST stores (NV = 16-byte vectors per
 // full row); lanes past the end repeat a valid vector -- the same data to the
 // same address -- so the number of outstanding memory operations is known at
 // compile time and a later wait for loads does not wait for these stores.
-template <int NST, int NV, int NTHR = kThreads>
+template <int NST, int NV, int NTHR>
 __device__ __forceinline__ void wide_store(bf16raw *__restrict__ y_base, size_t HW,
                                            const bf16raw *__restrict__ outl, int OP, int noc,
                                            int npix)
@@ -435,7 +279,7 @@ __device__ __forceinline__ void wide_store(bf16raw *__restrict__ y_base, size_t 
 }
 
 // Scalar variant for tiles whose rows do not start on 8-element boundaries.
-template <int NTHR = kThreads>
+template <int NTHR>
 __device__ __forceinline__ void wide_store_scalar(bf16raw *__restrict__ y_base, size_t HW,
                                                   const bf16raw *__restrict__ outl, int OP,
                                                   int noc, int npix)
@@ -443,169 +287,6 @@ __device__ __forceinline__ void wide_store_scalar(bf16raw *__restrict__ y_base, 
     for (int e = threadIdx.x; e < noc * npix; e += NTHR) {
         const int ocl = e / npix, p = e - ocl * npix;
         y_base[static_cast<size_t>(ocl) * HW + p] = outl[ocl * OP + p];
-    }
-}
-
-// One K-step for the wave's MT pixel tiles and NT channel tiles: the tap
-// (dq, ds) of step ks, read at each A row's centre slot plus the tap's slot
-// offset (one window row further for odd tap columns when the lane's pixel
-// column is odd).  Rows past the tile's last pixel read a clamped, valid
-// centre; their results are never stored.
-template <int K, int NT, int MT>
-__device__ __forceinline__ void wide_kstep(floatx4 (&acc)[MT][NT], const bf16x8 (&bq)[NT],
-                                           const unsigned char *__restrict__ tlb,
-                                           const int (&adr)[MT], int oddoff, int t, int icoff,
-                                           int rowb, int slotb)
-{
-    int dq = 0, ds = 0;
-    tap_axial(K, t, dq, ds);
-    const int toff = (ds + floor_half(dq)) * rowb + dq * slotb + icoff + ((dq & 1) ? oddoff : 0);
-    uint4 qa[MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-        qa[i] = *reinterpret_cast<const uint4 *>(tlb + adr[i] + toff);
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-        const bf16x8 av = __builtin_bit_cast(bf16x8, qa[i]);
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bq[j], acc[i][j], 0, 0, 0);
-    }
-}
-
-// KS > 0: B fragments of all KS K-steps held in registers; KS == 0: read
-// from the LDS-resident weights every K-step (a.KS K-steps).
-// Wave w: pixel group w % PW (pixel tiles w % PW + PW * i, i < MT) and
-// output-channel group w / PW (NT tiles of 16 channels).
-template <int K, int KS, int NT, int PW, int MT, bool REFLECT>
-__global__ __launch_bounds__(kThreads, KS > 0 ? 2 : 1) void conv_bf16_wide_k(
-    const bf16raw *__restrict__ xin, const bf16raw *__restrict__ w, const bf16raw *__restrict__ bias,
-    bf16raw *__restrict__ y, WideArgs a, int relu)
-{
-    constexpr int T = num_taps(K);
-    constexpr bool WL = KS == 0;
-    constexpr int OG = kWaves / PW;
-    constexpr int OCB = OG * NT * 16;
-    constexpr int ICB = WL ? 1 : KS / T; // 32-channel blocks per tap (registers mode)
-    extern __shared__ __align__(16) unsigned char smem[];
-    bf16raw *wl = reinterpret_cast<bf16raw *>(smem);
-    bf16raw *tl = reinterpret_cast<bf16raw *>(smem + a.tile_off);
-
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m = lane & 15, kq = lane >> 4;
-    const int pg = wave % PW, og = wave / PW;
-
-    // persistent work: a fixed channel chunk and strided pixel-tile slots
-    const int b = blockIdx.x;
-    const int xcd = b % kXcd, jj = b / kXcd;
-    const int occ = jj % a.nocc, sj = jj / a.nocc;
-    const int slot0 = xcd * a.spx + sj;
-    const int oc_base = occ * OCB;
-    const bool wave_live = oc_base + og * NT * 16 < a.OC;
-
-    // ---- weights
-    bf16x8 bfr[WL ? 1 : KS][NT];
-    if constexpr (WL) {
-        stage_weights<T, REFLECT>(wl, w, oc_base, OCB, a.IC, a.OC, a.WP);
-    } else {
-        // through the tile region: all channel groups at once if they fit
-        // (a.wgroups == OG), else one group at a time
-        for (int g = 0; g < OG; g += a.wgroups) {
-            __syncthreads();
-            stage_weights<T, REFLECT>(tl, w, oc_base + g * NT * 16, a.wgroups * NT * 16, a.IC,
-                                      a.OC, a.WP);
-            __syncthreads();
-            if (og >= g && og < g + a.wgroups) {
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                    for (int j = 0; j < NT; ++j)
-                        bfr[ks][j] = *reinterpret_cast<const bf16x8 *>(
-                            tl + ((og - g) * NT * 16 + j * 16 + m) * a.WP + ks * 32 + 8 * kq);
-            }
-        }
-    }
-
-    const int H = a.H, W = a.W;
-    const int HW = H * W;
-    const int rowb = a.LCP * a.CS * 2; // bytes per window row
-    const int slotb = a.CS * 2;        // bytes per slot
-    const unsigned char *tlb = reinterpret_cast<const unsigned char *>(tl);
-    float bv[NT];
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-        const int oc = oc_base + og * NT * 16 + j * 16 + m;
-        bv[j] = (bias != nullptr && oc < a.OC) ? to_f(bias[oc]) : 0.f;
-    }
-
-    for (int pt = slot0; pt < a.ptiles; pt += a.nslots) {
-        const int n = pt / a.ntr;
-        const int r0 = (pt - n * a.ntr) * a.TR;
-        const int rows = min(a.TR, H - r0);
-        const int npix = rows * W;
-
-        __syncthreads(); // the previous tile's (or the weight copy's) LDS reads are done
-        stage_tile<K, (KS >= 14) ? 1 : 2>(tl, xin + static_cast<size_t>(n) * a.IC * HW, H, W, a.IC, r0, rows, a.LCP,
-                      a.CS);
-        __syncthreads();
-
-        // centre-slot byte address of this lane's A row in each tile (W is
-        // even and tiles start on multiples of 16 pixels, so the column
-        // parity of the lane's pixel is the parity of m)
-        int adr[MT];
-#pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            const int p = min((pg + PW * i) * 16 + m, npix - 1);
-            const int pr = p / W, pc = p - pr * W;
-            adr[i] = ((pr + K) * a.LCP + pc + K) * slotb + kq * 16;
-        }
-        const int oddoff = (m & 1) ? rowb : 0;
-        floatx4 acc[MT][NT];
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-                acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-        if (wave_live) {
-            if constexpr (WL) {
-                const int icb = a.IC >> 5;
-                const bf16raw *wrow = wl + (og * NT * 16 + m) * a.WP + 8 * kq;
-                for (int ks = 0; ks < a.KS; ++ks) {
-                    const int t = ks / icb;
-                    bf16x8 bq[NT];
-#pragma unroll
-                    for (int j = 0; j < NT; ++j)
-                        bq[j] = *reinterpret_cast<const bf16x8 *>(wrow + j * 16 * a.WP + ks * 32);
-                    wide_kstep<K, NT, MT>(acc, bq, tlb, adr, oddoff, t, (ks - t * icb) * 64,
-                                          rowb, slotb);
-                }
-            } else {
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    // bound the scheduler's hoisting of fragment loads to one
-                    // K-step (the weights already hold most registers)
-                    __builtin_amdgcn_sched_barrier(0);
-                    wide_kstep<K, NT, MT>(acc, bfr[ks], tlb, adr, oddoff, ks / ICB,
-                                          (ks % ICB) * 64, rowb, slotb);
-                }
-            }
-        }
-
-        // epilogue: bias, ReLU, bf16 into LDS as [oc][pixel], then 16-byte stores
-        __syncthreads();
-        bf16raw *outl = tl;
-        if (wave_live)
-            wide_epilogue<NT, PW, MT>(outl, a.OP, acc, bv, og * NT * 16, pg, m, kq, relu);
-        __syncthreads();
-        const int noc = min(OCB, a.OC - oc_base);
-        bf16raw *ybase =
-            y + (static_cast<size_t>(n) * a.OC + oc_base) * HW + static_cast<size_t>(r0) * W;
-        if (a.vec_out)
-            wide_store<(OCB * PW * MT * 2 + kThreads - 1) / kThreads, PW * MT * 2>(ybase, HW, outl,
-                                                                                  a.OP, noc, npix);
-        else
-            wide_store_scalar(ybase, HW, outl, a.OP, noc, npix);
     }
 }
 
@@ -1152,21 +833,17 @@ conv_bf16_pipe_k(const bf16raw *xin, const bf16raw *__restrict__ w,
 
 inline int cdiv(long a, long b) { return static_cast<int>((a + b - 1) / b); }
 
-constexpr size_t kLds2 = 80 * 1024;  // two blocks per CU
-constexpr size_t kLds1 = 160 * 1024; // one block per CU
+constexpr size_t kLdsMax = 160 * 1024; // one block per CU
 
-// A kernel configuration.
-//   E32 = 1: 32x32x16 kernel, 8 waves, OG channel groups of 32 x PW pixel
-//            groups, MT tiles of 32 pixels per wave;
-//   E32 = 0: 16x16x32 kernel, 4 waves, NT channel tiles of 16 x PW pixel
-//            groups, MT tiles of 16 pixels per wave.
-//   KSR = K-steps held in registers (0: weights resident in LDS).
+// A configuration of the 32x32 kernel: 8 waves, 8 / PW channel groups of 32 x
+// PW pixel groups, MT tiles of 32 pixels per wave.
 struct WideCfg {
-    int E32, NT, PW, MT, KSR; // KSR: K-steps held in registers, 0 = weights in LDS
-    int WLK;                  // E32 with weights in LDS: instantiated K-step count
-    int waves() const { return E32 ? 8 : kWaves; }
-    int OCB() const { return E32 ? (waves() / PW) * 32 : (waves() / PW) * NT * 16; }
-    int pix() const { return PW * MT * (E32 ? 32 : 16); }
+    int PW, MT;
+    int KSR; // K-steps held in registers, 0 = weights resident in LDS
+    int WLK; // weights in LDS: instantiated K-step count
+    int og() const { return kThreads32 / 64 / PW; }
+    int OCB() const { return og() * 32; }
+    int pix() const { return PW * MT * 32; }
 };
 
 struct WidePlan {
@@ -1178,40 +855,25 @@ struct WidePlan {
 };
 
 // Row pitch (bf16) of LDS-resident weights whose 16-byte B fragments are
-// read by 16 (E32 = 0) or 32 (E32 = 1) consecutive rows without bank
-// conflicts: 32 mod 64 bytes, respectively an odd multiple of 16 bytes.
-int resident_pitch(int Kc, bool e32)
+// read by 32 consecutive rows without bank conflicts: an odd multiple of 16
+// bytes.
+int resident_pitch(int Kc)
 {
-    if (e32) {
-        int p = (Kc + 7) / 8 * 8;
-        if ((p / 8) % 2 == 0)
-            p += 8;
-        return p;
-    }
-    int p = (Kc + 15) / 16 * 16;
-    if ((p / 16) % 2 == 0)
-        p += 16;
+    int p = (Kc + 7) / 8 * 8;
+    if ((p / 8) % 2 == 0)
+        p += 8;
     return p;
 }
 
 // Configurations with an instantiated kernel (see dispatch_wide).
 bool instantiated(int k, const WideCfg &c)
 {
-    if (c.E32) {
-        if (c.NT != 1)
-            return false;
-        if (c.PW == 4 && c.MT == 2) // 64 channels
-            return (c.KSR == 0 && k == 2 && c.WLK == 38) ||
-                   (k == 1 && (c.KSR == 14 || c.KSR == 28));
-        if (c.PW == 2 && c.MT == 2) // 128 channels
-            return k == 1 && c.KSR == 28;
-        if (c.PW == 8 && c.MT == 1) // 32 channels, weights in LDS
-            return c.KSR == 0 && ((k == 2 && c.WLK == 76) || (k == 1 && c.WLK == 56));
-        return false;
-    }
-    if (c.NT == 2 && c.PW == 2 && c.MT == 4)
-        return k == 1 && (c.KSR == 7 || c.KSR == 14);
-    return c.KSR == 0 && c.NT == 2 && c.PW == 4 && c.MT == 4;
+    if (c.PW == 4 && c.MT == 2) // 64 channels
+        return (c.KSR == 0 && k == 2 && c.WLK == 38) || (k == 1 && (c.KSR == 14 || c.KSR == 28));
+    if (c.PW == 2 && c.MT == 2) // 128 channels
+        return k == 1 && c.KSR == 28;
+    // 32 channels, weights in LDS
+    return c.KSR == 0 && ((k == 2 && c.WLK == 76) || (k == 1 && c.WLK == 56));
 }
 
 bool plan_cfg(const ConvShape &sh, int IC, int OC, const WideCfg &c, WidePlan &pl)
@@ -1224,7 +886,7 @@ bool plan_cfg(const ConvShape &sh, int IC, int OC, const WideCfg &c, WidePlan &p
     a.W = sh.W;
     a.IC = IC;
     a.OC = OC;
-    a.KS = sh.T * IC / (c.E32 ? 16 : 32);
+    a.KS = sh.T * IC / 16;
     a.TR = std::min(sh.H, c.pix() / sh.W);
     // 16-byte output rows need tile origins on 8-element boundaries
     while (a.TR > 1 && (a.TR * sh.W) % 8 != 0)
@@ -1234,16 +896,12 @@ bool plan_cfg(const ConvShape &sh, int IC, int OC, const WideCfg &c, WidePlan &p
     a.nocc = cdiv(OC, c.OCB());
     a.vec_out = ((a.TR * sh.W) % 8 == 0) ? 1 : 0;
     a.LCP = sh.W + 2 * sh.k;
-    // slot pitch: odd multiple of 16 bytes for 32-row fragment reads,
-    // 32 mod 64 bytes for 16-row ones
-    a.CS = c.E32 ? IC + 8 : IC + 16;
+    a.CS = IC + 8; // slot pitch: odd multiple of 16 bytes
     a.OP = c.pix() + 4; // 8 mod 16 bytes: conflict-free 8-byte epilogue writes
     const size_t tile_in = 2ull * (a.TR + 2 * sh.k) * a.LCP * a.CS;
     const size_t tile_out = 2ull * c.OCB() * a.OP;
-    const int og = c.waves() / c.PW;
-    const bool two_per_cu = !c.E32 && c.KSR > 0;
-    const size_t limit = two_per_cu ? kLds2 : kLds1;
-    // 32x32 kernel: the input window and the output staging side by side
+    const int og = c.og();
+    // the input window and the output staging side by side
     // (the window rows carry over from tile to tile) if LDS holds both,
     // else the staging overlays the window
     auto layout = [&](bool ring, size_t &lds) {
@@ -1256,37 +914,29 @@ bool plan_cfg(const ConvShape &sh, int IC, int OC, const WideCfg &c, WidePlan &p
             a.wgroups = (wgroup * og <= tiles) ? og : 1;
             lds = std::max(tiles, wgroup * a.wgroups);
         } else {
-            a.WP = resident_pitch(sh.T * IC, c.E32 != 0);
+            a.WP = resident_pitch(sh.T * IC);
             a.tile_off = static_cast<int>((2ull * c.OCB() * a.WP + 255) / 256 * 256);
             a.wgroups = 1;
             lds = a.tile_off + tiles;
         }
         a.ring = ring ? 1 : 0;
         a.out_off = a.tile_off + (ring ? static_cast<int>(in_r) : 0);
-        return lds <= limit;
+        return lds <= kLdsMax;
     };
     size_t lds = 0;
-    if (!(c.E32 && layout(true, lds)) && !layout(false, lds))
+    if (!layout(true, lds) && !layout(false, lds))
         return false;
-    if (c.E32) {
-        // staged window items of one tile: at most one per thread
-        const int slack = (sh.W % 8 == 0) ? 0 : 1;
-        const long items = static_cast<long>(IC / 8) *
-                           ((static_cast<long>(a.TR + 2 * sh.k) * sh.W + 7) / 8 + slack);
-        if (items > kThreads32)
-            return false;
-        // runs of consecutive tiles, 8 * nocc blocks per round of XCDs
-        const int runs = std::max(1, std::min(device_cus() / a.nocc, a.ptiles));
-        a.per_block = cdiv(a.ptiles, runs);
-        const int nrun = cdiv(a.ptiles, a.per_block);
-        pl.grid = cdiv(nrun, kXcd) * kXcd * a.nocc; // blocks past the last run exit at once
-    } else {
-        const int per_cu = c.KSR > 0 ? 2 : 1;
-        const int want = std::max(1, device_cus() * per_cu / (kXcd * a.nocc));
-        a.spx = std::max(1, std::min(want, cdiv(a.ptiles, kXcd)));
-        a.nslots = kXcd * a.spx;
-        pl.grid = a.nslots * a.nocc;
-    }
+    // staged window items of one tile: at most one per thread
+    const int slack = (sh.W % 8 == 0) ? 0 : 1;
+    const long items = static_cast<long>(IC / 8) *
+                       ((static_cast<long>(a.TR + 2 * sh.k) * sh.W + 7) / 8 + slack);
+    if (items > kThreads32)
+        return false;
+    // runs of consecutive tiles, 8 * nocc blocks per round of XCDs
+    const int runs = std::max(1, std::min(device_cus() / a.nocc, a.ptiles));
+    a.per_block = cdiv(a.ptiles, runs);
+    const int nrun = cdiv(a.ptiles, a.per_block);
+    pl.grid = cdiv(nrun, kXcd) * kXcd * a.nocc; // blocks past the last run exit at once
     pl.cfg = c;
     pl.a = a;
     pl.lds = lds;
@@ -1298,17 +948,15 @@ WidePlan plan_wide(const ConvShape &sh, int IC, int OC)
 {
     WidePlan pl{};
     pl.ok = false;
-    const int KS32 = sh.T * IC / 16, KS16 = sh.T * IC / 32;
+    const int KS = sh.T * IC / 16;
     const WideCfg cands[] = {
-        {1, 1, 2, 2, KS32, 0}, // 32x32: 128 channels, weights in registers
-        {1, 1, 4, 2, KS32, 0}, // 32x32: 64 channels, weights in registers
-        {1, 1, 4, 2, 0, KS32}, // 32x32: 64 channels, weights in LDS
-        {1, 1, 8, 1, 0, KS32}, // 32x32: 32 channels, weights in LDS
-        {0, 2, 2, 4, KS16, 0}, // 16x16 fallbacks
-        {0, 2, 4, 4, 0, 0},
+        {2, 2, KS, 0}, // 128 channels, weights in registers
+        {4, 2, KS, 0}, // 64 channels, weights in registers
+        {4, 2, 0, KS}, // 64 channels, weights in LDS
+        {8, 1, 0, KS}, // 32 channels, weights in LDS
     };
     for (const WideCfg &c : cands) {
-        if (c.E32 && c.PW == 2 && OC <= 64)
+        if (c.PW == 2 && OC <= 64)
             continue; // 128-channel blocks only for more than 64 channels
         if (!instantiated(sh.k, c))
             continue;
@@ -1316,15 +964,6 @@ WidePlan plan_wide(const ConvShape &sh, int IC, int OC)
             return pl;
     }
     return pl;
-}
-
-template <int K, int KS, int NT, int PW, int MT, bool R>
-hipError_t launch_wide(const WidePlan &pl, const bf16raw *x, const bf16raw *w, const bf16raw *b,
-                       bf16raw *y, bool relu, hipStream_t st)
-{
-    HEX_LAUNCH((conv_bf16_wide_k<K, KS, NT, PW, MT, R>), dim3(pl.grid), dim3(kThreads),
-                       pl.lds, st, x, w, b, y, pl.a, relu ? 1 : 0);
-    return hipGetLastError();
 }
 
 template <int K, int KS, bool WL, int OG, int PW, int MT, bool R>
@@ -1341,24 +980,16 @@ hipError_t dispatch_wide(const WidePlan &pl, int k, const bf16raw *x, const bf16
                          const bf16raw *b, bf16raw *y, bool relu, hipStream_t st)
 {
     const WideCfg &c = pl.cfg;
-    if (c.E32) {
-        if (c.PW == 8)
-            return k == 1 ? launch_wide32<1, 56, true, 1, 8, 1, R>(pl, x, w, b, y, relu, st)
-                          : launch_wide32<2, 76, true, 1, 8, 1, R>(pl, x, w, b, y, relu, st);
-        if (c.PW == 2)
-            return launch_wide32<1, 28, false, 4, 2, 2, R>(pl, x, w, b, y, relu, st);
-        if (c.KSR == 0)
-            return launch_wide32<2, 38, true, 2, 4, 2, R>(pl, x, w, b, y, relu, st);
-        if (c.KSR == 14)
-            return launch_wide32<1, 14, false, 2, 4, 2, R>(pl, x, w, b, y, relu, st);
-        return launch_wide32<1, 28, false, 2, 4, 2, R>(pl, x, w, b, y, relu, st);
-    }
+    if (c.PW == 8)
+        return k == 1 ? launch_wide32<1, 56, true, 1, 8, 1, R>(pl, x, w, b, y, relu, st)
+                      : launch_wide32<2, 76, true, 1, 8, 1, R>(pl, x, w, b, y, relu, st);
+    if (c.PW == 2)
+        return launch_wide32<1, 28, false, 4, 2, 2, R>(pl, x, w, b, y, relu, st);
     if (c.KSR == 0)
-        return k == 1 ? launch_wide<1, 0, 2, 4, 4, R>(pl, x, w, b, y, relu, st)
-                      : launch_wide<2, 0, 2, 4, 4, R>(pl, x, w, b, y, relu, st);
-    if (c.KSR == 7)
-        return launch_wide<1, 7, 2, 2, 4, R>(pl, x, w, b, y, relu, st);
-    return launch_wide<1, 14, 2, 2, 4, R>(pl, x, w, b, y, relu, st);
+        return launch_wide32<2, 38, true, 2, 4, 2, R>(pl, x, w, b, y, relu, st);
+    if (c.KSR == 14)
+        return launch_wide32<1, 14, false, 2, 4, 2, R>(pl, x, w, b, y, relu, st);
+    return launch_wide32<1, 28, false, 2, 4, 2, R>(pl, x, w, b, y, relu, st);
 }
 
 bool pipe_plan(const ConvShape &sh, int IC, int OC, PipeArgs &a, size_t &lds, int &grid)
@@ -1379,7 +1010,7 @@ bool pipe_plan(const ConvShape &sh, int IC, int OC, PipeArgs &a, size_t &lds, in
     const size_t ring = 2ull * (2 * K + 2) * a.LCP * a.CS;
     a.out_off = static_cast<int>((ring + 255) / 256 * 256);
     lds = std::max(static_cast<size_t>(a.out_off) + 2ull * 2 * 64 * a.OP, 2ull * 64 * a.WP);
-    if (lds > kLds1)
+    if (lds > kLdsMax)
         return false;
     const int cus = device_cus();
     a.runs_per_img = std::max(cdiv(sh.H, kPipeMaxRows), std::min(sh.H, cdiv(cus, sh.N)));
@@ -1405,14 +1036,6 @@ hipError_t launch_pipe(const PipeArgs &a, size_t lds, int grid, const bf16raw *x
 
 } // namespace
 
-bool bf16_wide_ok(const ConvShape &sh, int IC, int OC)
-{
-    if (sh.s != 1 || (sh.k != 1 && sh.k != 2) || IC % 32 != 0 || IC > 128 || sh.W % 2 != 0 ||
-        sh.W < 8 || (static_cast<long>(sh.H) * sh.W) % 8 != 0)
-        return false;
-    return plan_wide(sh, IC, OC).ok;
-}
-
 // Whether these kernels go before the one for any shape (k_conv_any.hip).
 // Pipelined rows do (64 -> 64 channels, 128 x 128, N = 64: 67 / 77 us forward /
 // data gradient; 128 x 127 there 122). The 32x32 kernel does on small planes,
@@ -1421,19 +1044,20 @@ bool bf16_wide_ok(const ConvShape &sh, int IC, int OC)
 // 128, 12 x 12, k = 1 31 / 32 against 38 / 42), and in the forward of up to 64
 // channels out (64 x 64 planes, 64 -> 64, N = 32: 20.4 against 20.7; but 64 ->
 // 96, 45 x 48, N = 96 51 against 42); not in the data gradient of larger planes
-// (30 against 23; 77 against 44). The 16x16 kernel does nowhere (96 -> 96,
-// 64 x 64, N = 24: 55 against 34).
+// (30 against 23; 77 against 44).
 bool bf16_wide_first(const ConvShape &sh, int IC, int OC, bool reflect)
 {
+    if (sh.s != 1 || (sh.k != 1 && sh.k != 2) || IC % 32 != 0 || IC > 128 || sh.W % 2 != 0 ||
+        sh.W < 8 || (static_cast<long>(sh.H) * sh.W) % 8 != 0)
+        return false;
     PipeArgs pa{};
     size_t lds = 0;
     int grid = 0;
     if (pipe_plan(sh, IC, OC, pa, lds, grid))
         return true;
-    const WidePlan pl = plan_wide(sh, IC, OC);
-    if (!pl.ok || !pl.cfg.E32)
+    if (sh.H * sh.W >= 1024 && (reflect || OC > 64))
         return false;
-    return sh.H * sh.W < 1024 || (!reflect && OC <= 64);
+    return plan_wide(sh, IC, OC).ok;
 }
 
 hipError_t bf16_wide_conv(const void *in, const void *w, const void *bias, void *out,

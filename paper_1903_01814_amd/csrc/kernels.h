@@ -52,9 +52,9 @@ enum Dtype { F32 = 0, BF16 = 1 };
 
 // Sizes of one call.  Three-dimensional calls add D planes along z, a
 // window of Z = 2kz+1 planes and a plane stride sz (D_out output planes);
-// 2-D calls have D = Do = Z = sz = 1, kz = 0.  Only the generic kernels
-// read the depth fields; the specialised kernels are chosen for 2-D calls
-// only.
+// 2-D calls have D = Do = Z = sz = 1, kz = 0.  The generic, few-channel and
+// any-shape kernels read the depth fields; those for bf16 rows of whole
+// 16-byte vectors are chosen for 2-D calls only.
 struct ConvShape {
     int N, Ci, Co, H, W, k, s, Ho, Wo, T;
     int D, Do, kz, Z, sz;
@@ -175,9 +175,8 @@ hipError_t smallc_bwd_fused(const void *x, const void *dy, const void *w, void *
 
 // ---- bf16 matrix-core convolution, input channels a multiple of 32 -----
 // forward (reflect = false: IC = C_in, OC = C_out) or stride-1 data
-// gradient (reflect = true: IC = C_out, OC = C_in)
-bool bf16_wide_ok(const ConvShape &sh, int IC, int OC);
-// (bf16_wide_ok shapes) before the kernel for any shape?
+// gradient (reflect = true: IC = C_out, OC = C_in), for the shapes that go
+// here before the kernel for any shape
 bool bf16_wide_first(const ConvShape &sh, int IC, int OC, bool reflect);
 hipError_t bf16_wide_conv(const void *in, const void *w, const void *bias, void *out,
                           const ConvShape &sh, bool reflect, bool relu, hipStream_t st);
