@@ -24,9 +24,10 @@
 // banks), for the block's life where all fit, else per stage.  The next
 // stage's rows are loaded into registers during the products.
 //
-// Bound by the float32 matrix rate (64 clocks per 32x32x2 product and SIMD; a
-// pair costs MG + NT four-byte reads for MG NT products) and, with few
-// products per staged pixel, by the staging's instructions.  32 -> 64 channels,
+// Bound by the turns of staging and products, which a barrier parts: at 32 ->
+// 64 channels, 40 x 40, N = 128, k = 1 the matrix cores are busy 0.37 of the
+// time (64 clocks per 32x32x2 product and SIMD; a pair costs MG + NT four-byte
+// reads for MG NT products), LDS 0.15 and the vector units 0.07.  32 -> 64 channels,
 // 40 x 40, N = 128, k = 1: 356 us on the generic kernel, 101 here, 39 at the
 // matrix rate; 48 -> 96, 46 x 45, N = 15, k = 2: 370, 98, 36.  (Items' places
 // worked out once instead of per stage: 101 -> 115 us, the registers spill.)

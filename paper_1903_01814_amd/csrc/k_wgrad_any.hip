@@ -1,8 +1,11 @@
 // k_wgrad_any.hip -- weight and bias gradient on the matrix cores for planes
-// of any size, any channel count and any stride, in bfloat16 and float32,
-// two- and three-dimensional; takes what the tuned bfloat16 kernels
-// (k_wgrad32.hip, k_wgrad_bf16.hip: whole 16-byte rows) and the small-channel
-// kernels do not.
+// of odd sizes, any channel count and any stride, k = 1 to 3, in bfloat16 and
+// float32, two- and three-dimensional: output rows of 4 (float32) or 8
+// (bfloat16) pixels and more whose x window and dy row fit LDS (x rows to
+// 170 / 102 / 73 pixels in float32 and 624 / 409 / 292 in bfloat16 at k = 1 /
+// 2 / 3 and stride 1, 128 / 85 / 64 and 512 / 341 / 256 at stride 2).  Takes
+// what the tuned bfloat16 kernels (k_wgrad32.hip, k_wgrad_bf16.hip: whole
+// 16-byte rows) and the small-channel kernels do not.
 //
 //   D_t[co][ci] = sum over output pixels p of dy[co][p] x[ci][p + tap t]
 //
