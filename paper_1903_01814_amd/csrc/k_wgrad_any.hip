@@ -34,8 +34,11 @@
 //
 // float32 sums: a chain of n additions of independent terms is off by about
 // 2.5e-8 sqrt(n / 2) of the sum, and a block's run of tiles is long.  So the
-// matrix cores add 16 pixels at a time, from zero, eight of these sums are
-// added up, and those are added over the run: three short chains.  Off the
+// matrix cores add 16 pixels at a time, from zero, eight of these sums (or
+// the root of their number, which makes the two chains equal, where that is
+// more: 512 -> 512 channels, k = 3, 16 of 57 x 57, whose one slot a type has
+// 3 600 of them: dw 3.9e-7 with eight, 2.1e-7 now, generic kernel 2.6e-7)
+// are added up, and those are added over the run: three short chains.  Off the
 // sum in 64 bits (generic kernel, one chain, now): 4 -> 8 channels, k = 2, 227
 // images of 41 x 39, dw 1.1e-7, 1.8e-7, 0.85e-7, db 1.8e-7, 4.4e-7, 1.4e-7; 64
 // -> 96, 28 x 29 x 33, dw 1.4e-7, 2.1e-7, 1.0e-7; 22 volumes of 12 -> 32, dw
@@ -47,6 +50,7 @@
 // Pixels past a tile's end: both operands are zeroed (by masks), so that no
 // product of a stray infinity reaches a sum.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "../../include/hexconv.h"
@@ -67,7 +71,7 @@ constexpr int kWThreads = 512;
 // Taps per wave and tap groups: T + 1 columns (the taps and the bias)
 constexpr int role_tpw(bool f32, int k, int nco) { return k > 1 ? 5 : f32 ? 2 / nco : 4; }
 constexpr int role_g(bool f32, int k, int nco) { return k == 3 ? 8 : k == 2 ? 4 : f32 ? 4 * nco : 2; }
-constexpr int kRunSteps = 8; // float32: steps of 16 pixels per chain of step sums
+constexpr int kRunSteps = 8; // float32: least steps of 16 pixels per chain of step sums
 
 // Four pixels of a channel from a0 and four from a1, transposed (see above)
 __device__ __forceinline__ bf16x8 tr_read(unsigned char *a0, unsigned char *a1)
@@ -208,7 +212,7 @@ __global__ __launch_bounds__(kWThreads) void wgrad_any_k(const E *x, const E *dy
 #pragma unroll
         for (int t = 0; t < TPW; ++t)
             acc[c][t] = floatx16{};
-    // float32: sums of up to kRunSteps steps, not yet in acc
+    // float32: sums of up to run_steps steps, not yet in acc
     constexpr int RC = F32 ? NCO : 1, RT = F32 ? TPW : 1;
     floatx16 run[RC][RT];
     int nrun = 0;
@@ -307,7 +311,7 @@ __global__ __launch_bounds__(kWThreads) void wgrad_any_k(const E *x, const E *dy
 #pragma unroll
             for (int c = 0; c < NCO; ++c)
                 run[c][TPW - 1] += s[(TPW - 1) & 1][c];
-            if (++nrun == kRunSteps) {
+            if (++nrun == a.run_steps) {
                 nrun = 0;
                 end_run();
             }
@@ -592,6 +596,10 @@ bool plan_tile(const ConvShape &sh, Dtype d, int A, int U, int cus, WAnyPlan &be
     if (!found)
         return false;
     WAnyArgs &b = best.a;
+    const int split = 8 / (best.G * best.A);
+    const double steps = std::ceil(static_cast<double>(b.ntot) / b.nslots) *
+                         ((b.npix / 16 + split - 1) / split);
+    b.run_steps = std::max(kRunSteps, static_cast<int>(std::lround(std::sqrt(steps))));
     int t = 0;
     for (int dq = -K; dq <= K; ++dq)
         for (int i = 0; i < col_len(K, dq); ++i, ++t) {

@@ -227,6 +227,7 @@ struct WAnyArgs {
     int nslots;           // blocks per (dz, ci, co) type
     int x_off, tab_off;   // LDS: dy at 0, x window, pixel table
     int npix;             // table entries (multiple of 16)
+    int run_steps;        // float32: steps of 16 pixels per chain of step sums
     int toff[37];         // byte offset of each tap
 };
 

@@ -129,6 +129,21 @@ def test_f32_weight_gradient_sums(case):
     assert max(err) <= SUM_REL, err
 
 
+def test_f32_weight_gradient_sums_of_one_slot():
+    """So many channels that the scratch array holds one slot of each type:
+    one block adds all 3 600 steps of 16 pixels, as chains of 16, 60 and 60
+    (2.5e-8 sqrt(136 / 2) = 2.1e-7, a fifth more allowed; chains of 8 and 450
+    3.8e-7).  Eight output channels are checked."""
+    N, C, H, W, k = 16, 512, 57, 57, 3
+    rng = np.random.default_rng(550)
+    x = rng.normal(size=(N, C, H, W)).astype(np.float32)
+    dy = rng.normal(size=(N, C, H, W)).astype(np.float32)
+    got = run_bwd_weight(x, dy, k, 1, "f32")
+    ref = oracle.conv_bwd_weight(x, dy[:, 100:108], k, 1)
+    err = rel_l2(got[0][100:108], ref[0])
+    assert err <= 2.5e-7, err
+
+
 def test_f32_volume_sums():
     rng = np.random.default_rng(600)
     got, ref = [], []
