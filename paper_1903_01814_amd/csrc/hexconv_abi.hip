@@ -185,21 +185,29 @@ int launched(hipError_t e)
 // else; "any" (planes of any size, k_conv_any, k_conv_f32, k_wgrad_any), "few"
 // (few input channels) and "rows" (bf16 rows of whole 16-byte vectors,
 // k_mfma_gen, k_wgrad_bf16) where the family takes the shape at all.
-bool forced(const char *family)
+enum class Force { None, Generic, Any, Few, Rows };
+
+Force forced()
 {
     const char *v = getenv("HEXCONV_PATH");
-    return v != nullptr && strcmp(v, family) == 0;
+    if (v == nullptr)
+        return Force::None;
+    return strcmp(v, "generic") == 0 ? Force::Generic
+           : strcmp(v, "any") == 0   ? Force::Any
+           : strcmp(v, "few") == 0   ? Force::Few
+           : strcmp(v, "rows") == 0  ? Force::Rows
+                                     : Force::None;
 }
 
-bool force_generic() { return forced("generic"); }
+bool force_generic() { return forced() == Force::Generic; }
 
 // Estimated time of a call's other choice as offered to the kernels for any
 // shape: strided = that choice is a kernel of the family "rows".
-double other_us(double us, bool strided)
+double other_us(Force f, double us, bool strided)
 {
-    if (forced("any"))
+    if (f == Force::Any)
         return HUGE_VAL;
-    return strided && forced("rows") ? 0.0 : us;
+    return strided && f == Force::Rows ? 0.0 : us;
 }
 
 // Weight-gradient kernel family for a shape, its workspace and, for the
@@ -215,9 +223,10 @@ struct WgradPick {
 
 WgradPath wgrad_path(const ConvShape &sh, Dtype d, hexk::WAnyPlan &any)
 {
-    if (force_generic())
+    const Force f = forced();
+    if (f == Force::Generic)
         return WgradPath::Generic;
-    if (forced("any") && hexk::wgrad_any_plan(sh, d, any))
+    if (f == Force::Any && hexk::wgrad_any_plan(sh, d, any))
         return WgradPath::Any;
     // where the fused backward applies, it is also the fastest weight
     // gradient with its data-gradient waves off (fp32 1 -> 16 channels, 40x40,
@@ -226,7 +235,7 @@ WgradPath wgrad_path(const ConvShape &sh, Dtype d, hexk::WAnyPlan &any)
     if (hexk::smallc_bwd_fused_ok(sh, d))
         return WgradPath::Fused;
     const bool small = hexk::smallc_wgrad_ok(sh);
-    if (small && forced("few"))
+    if (small && f == Force::Few)
         return WgradPath::Small;
     // few channels on rows of whole 4-column groups: float32 (43 shapes, all
     // faster than generic); bf16, for which the small-channel kernel stages x
@@ -249,7 +258,7 @@ WgradPath wgrad_path(const ConvShape &sh, Dtype d, hexk::WAnyPlan &any)
     // rows of whole 4-column groups or the generic one, unless the estimates
     // put another kernel clearly below it
     const bool mfma = d == hexk::BF16 && hexk::bf16_wgrad_ok(sh);
-    if (mfma && forced("rows"))
+    if (mfma && f == Force::Rows)
         return WgradPath::Bf16Mfma;
     WgradPath best = WgradPath::Generic;
     double us = hexk::wgrad_generic_us(sh, d);
@@ -310,17 +319,18 @@ WgradPick wgrad3d_pick(const ConvShape &sh, Dtype d)
 {
     WgradPick p;
     p.ws = hexk::wgrad_generic_workspace(sh);
-    if (force_generic())
+    const Force f = forced();
+    if (f == Force::Generic)
         return p;
     const double us = hexk::wgrad_generic_us(sh, d) * hexk::kClearly;
     if (hexk::smallc_wgrad_ok(sh)) {
-        if (sh.W % 4 == 0 || forced("few") || hexk::smallc_wgrad_us(sh, d) < us) {
+        if (sh.W % 4 == 0 || f == Force::Few || hexk::smallc_wgrad_us(sh, d) < us) {
             p.path = WgradPath::Small;
             p.ws = hexk::smallc_wgrad_workspace(sh);
         }
         return p;
     }
-    if (hexk::wgrad_any_plan(sh, d, p.any) && (p.any.us < us || forced("any"))) {
+    if (hexk::wgrad_any_plan(sh, d, p.any) && (p.any.us < us || f == Force::Any)) {
         p.path = WgradPath::Any;
         p.ws = p.any.ws;
     }
@@ -467,8 +477,9 @@ int hexconv_fwd(const void *x, const void *w, const void *bias, void *y, int N, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool relu = (flags & HEX_FLAG_RELU) != 0;
     const Dtype d = static_cast<Dtype>(dt);
-    if (!force_generic()) {
-        const bool any = forced("any");
+    const Force f = forced();
+    if (f != Force::Generic) {
+        const bool any = f == Force::Any;
         if (!any && hexk::smallc_fwd_ok(sh))
             return launched(hexk::smallc_fwd(x, w, bias, y, sh, d, relu, st));
         // the tuned bf16 stride-1 kernels where they win, then the kernels
@@ -479,7 +490,7 @@ int hexconv_fwd(const void *x, const void *w, const void *bias, void *y, int N, 
         hipError_t e = hipSuccess;
         const bool strided = d == hexk::BF16 && hexk::bf16_gen_fwd_ok(sh);
         const double other =
-            other_us(strided ? HUGE_VAL : fwd_generic_us(sh, d), strided);
+            other_us(f, strided ? HUGE_VAL : fwd_generic_us(sh, d), strided);
         const Tried t = d == hexk::F32
                             ? hexk::conv_f32_fwd(x, w, bias, y, sh, relu, st, other, e)
                             : hexk::conv_any(x, w, bias, y, sh, d, false, relu, st, other, e);
@@ -508,17 +519,18 @@ int hexconv_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in, i
         return HEX_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Dtype d = static_cast<Dtype>(dt);
-    if (!force_generic() && sh.Ho > 0) {
+    const Force f = forced();
+    if (f != Force::Generic && sh.Ho > 0) {
         // bf16 on the matrix cores, by the tuned kernels where they win, unless
         // the work is little (64 images of 41 x 43, 4 -> 32 channels, k = 1:
         // 52 us on the small-channel kernel, whose fp32 arithmetic runs on
         // the vector units, 10 us here; 170 of 46 x 18, 5 -> 2: 8.6 on the
         // generic one, 13.4); fp32 of few channels on the vector units first
-        const bool any = forced("any");
+        const bool any = f == Force::Any;
         if (d == hexk::BF16 && !any && hexk::bf16_wide_first(sh, sh.Co, sh.Ci, true))
             return launched(hexk::bf16_wide_conv(dy, w, nullptr, dx, sh, true, false, st));
         const bool small = hexk::smallc_bwd_data_ok(sh);
-        if (small && (forced("few") || (d == hexk::F32 && !any)))
+        if (small && (f == Force::Few || (d == hexk::F32 && !any)))
             return launched(hexk::smallc_bwd_data(dy, w, dx, sh, d, st));
         hipError_t e = hipSuccess;
         // bf16 on rows of whole 16-byte vectors: one walk over dy for all
@@ -526,7 +538,8 @@ int hexconv_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in, i
         // 192 channels, 112 x 96, N = 2, k = 1, stride 2: 23 us, 50 here; 128
         // -> 96, 64 x 80, N = 9, k = 2: 112, 56)
         const bool strided = d == hexk::BF16 && !small && hexk::bf16_gen_dgrad_ok(sh);
-        const double other = other_us(small     ? hexk::smallc_bwd_data_us(sh)
+        const double other = other_us(f,
+                                      small     ? hexk::smallc_bwd_data_us(sh)
                                       : strided ? hexk::bf16_gen_dgrad_us(sh)
                                                 : bwd_data_generic_us(sh, d),
                                       strided);
@@ -741,13 +754,14 @@ int hexconv3d_fwd(const void *x, const void *w, const void *bias, void *y, int N
     const Dtype d = static_cast<Dtype>(dt);
     const bool relu = (flags & HEX_FLAG_RELU) != 0;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (!force_generic()) {
+    const Force f = forced();
+    if (f != Force::Generic) {
         // few input channels: the small-channel forward with the 2kz + 1
         // planes around each output plane staged as extra input channels
         if (hexk::smallc_fwd_ok(sh))
             return launched(hexk::smallc_fwd(x, w, bias, y, sh, d, relu, st));
         hipError_t e = hipSuccess;
-        const double gen = other_us(fwd_generic_us(sh, d), false);
+        const double gen = other_us(f, fwd_generic_us(sh, d), false);
         const Tried t = d == hexk::F32
                             ? hexk::conv_f32_fwd(x, w, bias, y, sh, relu, st, gen, e)
                             : hexk::conv_any(x, w, bias, y, sh, d, false, relu, st, gen, e);
@@ -775,12 +789,13 @@ int hexconv3d_bwd_data(const void *dy, const void *w, void *dx, int N, int C_in,
         return HEX_ERR_INVALID_ARG;
     const Dtype d = static_cast<Dtype>(dt);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (!force_generic() && sh.Ho > 0) {
+    const Force f = forced();
+    if (f != Force::Generic && sh.Ho > 0) {
         if (hexk::smallc3d_bwd_data_ok(sh))
             return launched(hexk::smallc3d_bwd_data(dy, w, dx, sh, d, st));
         hipError_t e = hipSuccess;
         if (hexk::conv_any(dy, w, nullptr, dx, sh, d, true, false, st,
-                           other_us(bwd_data_generic_us(sh, d), false), e) == Tried::Ran)
+                           other_us(f, bwd_data_generic_us(sh, d), false), e) == Tried::Ran)
             return launched(e);
     }
     if (!hexk::conv_bwd_data_generic_ok(sh))
